@@ -44,7 +44,7 @@ int gemm_rows_per_wg(bool single_pass) {
 }
 
 hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pass, const void* a,
-                       const void* b, void* c, int m, int n, int k, float alpha,
+                       const void* b, void* c, int64_t batch, int m, int n, int k, float alpha,
                        const int32_t* d_worker_ptr, const bsm_item* d_items, int n_wg, void* trace,
                        hipStream_t stream) {
     Shape s;
@@ -54,14 +54,13 @@ hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pas
     s.a_batch = static_cast<int64_t>(m) * k;
     s.b_batch = static_cast<int64_t>(n) * k;
     s.c_batch = static_cast<int64_t>(m) * n;
+    s.a_total = static_cast<int64_t>(batch) * s.a_batch;
+    s.b_total = static_cast<int64_t>(batch) * s.b_batch;
     s.alpha = alpha;
-    // 16-byte operand pieces and 16-byte output stores (4 fp32 or 8 bf16 columns): rows of A
-    // (and NT's B) of k elements, rows of NN's B and of C of n elements, every base 16-byte
-    // aligned
-    const uintptr_t ptrs = reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) |
-                           reinterpret_cast<uintptr_t>(c);
-    const bool vec = (ptrs & 15) == 0 && k % 8 == 0 &&
-                     n % ((layout == bsm_mm::kNN || bf16_out) ? 8 : 4) == 0;
+    // operands of aligned whole 16-byte pieces: rows of A (and NT's B) of k elements, rows of
+    // NN's B of n elements, both bases 16-byte aligned (C is stored at any element boundary)
+    const uintptr_t ptrs = reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b);
+    const bool vec = (ptrs & 15) == 0 && k % 8 == 0 && (layout != bsm_mm::kNN || n % 8 == 0);
     const bool areg = bsm_mm::use_areg(vec, n, k);
 #define BSM_G(M, O, V, T, R) launch_g<M, O, V, T, R>(a, b, c, s, d_worker_ptr, d_items, n_wg, trace, stream)
 #define BSM_GV(M, O, T) (!vec ? BSM_G(M, O, false, T, false) \

@@ -38,6 +38,11 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// 16-byte accesses at any element boundary (the same instructions as the aligned ones; a
+// misaligned access touches one cache line more)
+typedef u16x8 u16x8_any __attribute__((aligned(2)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
 
 enum { kNT = 0, kNN = 1 };
 constexpr int kWaves = 4;    // waves per workgroup
@@ -48,6 +53,7 @@ constexpr int kTileK = 16;   // reduction depth per MFMA
 struct Shape {
     int m, n, k;
     int64_t a_batch, b_batch, c_batch;  // elements between consecutive batch indices
+    int64_t a_total, b_total;           // elements of the whole operands
     float alpha;
 };
 
@@ -84,44 +90,66 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
     return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
 }
 
-// Eight consecutive bf16 of a row-major operand row (`len` columns) from column c, or from
-// the row's last whole piece when c is past the row (the caller zeroes such pieces when it
-// writes them to LDS).  VEC: one unconditional 16-byte load (len % 8 == 0, 16-byte aligned
-// rows), so that no branch or select on the loaded data sits between a step's loads and the
-// wait before their use; the scalar form (any len) loads element by element.  Ordinary
-// (cache-resident) loads where the data is read again (B by every row round of its batch, A
-// by every column block), nontemporal (STREAM) where it is read once.
+// Eight consecutive bf16 of a row-major operand of `total` elements, from column c of the row
+// that starts at element `row` (rows of `len` elements).
+// VEC (len % 8 == 0, 16-byte aligned operands): one unconditional 16-byte load, from the row's
+// last whole piece when c is past the row (the caller zeroes such pieces when it writes them to
+// LDS), so that no branch or select on the loaded data sits between a step's loads and the wait
+// before their use.
+// Otherwise (any len, any element-aligned operand): the same single load at its element
+// boundary.  It may run on into the following rows; the operand's last piece is loaded so that
+// it ends with the operand instead, and keep8 moves it into place.  Element loads, eight per
+// piece, took 105 us for the context product of 192 x (333 x 333)(333 x 64).  An operand of
+// fewer than eight elements is loaded element by element.
+// Ordinary (cache-resident) loads where the data is read again (B by every row round of its
+// batch, A by every column block), nontemporal (STREAM) where it is read once.
 template <bool VEC, bool STREAM = false>
-__device__ __forceinline__ u16x8 load8(const uint16_t* row, int c, int len) {
+__device__ __forceinline__ u16x8 load8(const uint16_t* base, int64_t row, int c, int len, int64_t total) {
     if constexpr (VEC) {
-        const u16x8* p = reinterpret_cast<const u16x8*>(row + (c < len ? c : len - 8));
+        const u16x8* p = reinterpret_cast<const u16x8*>(base + row + (c < len ? c : len - 8));
         if constexpr (STREAM) return __builtin_nontemporal_load(p);
         return *p;
     } else {
+        const int64_t i = row + c;
+        if (total >= 8) {  // the same for every lane of the launch
+            const u16x8_any* p = reinterpret_cast<const u16x8_any*>(base + (i < total - 8 ? i : total - 8));
+            if constexpr (STREAM) return __builtin_nontemporal_load(p);
+            return *p;
+        }
         u16x8 v;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = row[c + e < len ? c + e : len - 1];
+        for (int e = 0; e < 8; ++e) v[e] = base[i + e < total ? i + e : total - 1];
         return v;
     }
 }
 
-// Zeroes the elements of a piece loaded from columns [c, c + 8) that lie past `len`, or all
-// of them when !ok.  VEC (len % 8 == 0, c % 8 == 0): the piece is wholly in or wholly out,
-// four 32-bit selects.
+// Zeroes the elements of a piece loaded by load8 that lie past `len`, or all of them when !ok.
+// VEC: the piece is wholly in or wholly out, four 32-bit selects.  Otherwise the piece may hold
+// any number of the row's elements (`whole`, the same for the wave: the step's columns all lie
+// inside the rows, so that only !ok is left), and the operand's last piece is first moved down
+// by the elements it was loaded early.
 template <bool VEC>
-__device__ __forceinline__ u16x8 keep8(u16x8 v, int c, int len, bool ok) {
-    if constexpr (VEC) {
-        const bool in = ok && c < len;
-        u32x4 w = __builtin_bit_cast(u32x4, v);
+__device__ __forceinline__ u16x8 keep8(u16x8 v, int64_t row, int c, int len, int64_t total, bool ok, bool whole) {
+    u32x4 w = __builtin_bit_cast(u32x4, v);
+    if (VEC || whole) {
+        const bool in = ok && (whole || c < len);
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = in ? w[e] : 0u;
         return __builtin_bit_cast(u16x8, w);
-    } else {
-        u16x8 z;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) z[e] = (ok && c + e < len) ? v[e] : static_cast<unsigned short>(0);
-        return z;
     }
+    const int left = ok ? len - c : 0;  // the row's elements from the piece's first one on
+    const int64_t early = total >= 8 ? row + c - (total - 8) : 0;
+    if (early > 0 && left > 0) {  // early <= 7 here: the row has an element in the piece
+        if (early & 4) w = u32x4{w[2], w[3], 0u, 0u};
+        if (early & 2) w = u32x4{w[1], w[2], w[3], 0u};
+        if (early & 1)
+            w = u32x4{(w[0] >> 16) | (w[1] << 16), (w[1] >> 16) | (w[2] << 16),
+                      (w[2] >> 16) | (w[3] << 16), w[3] >> 16};
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        w[e] = left >= 2 * e + 2 ? w[e] : (left == 2 * e + 1 ? (w[e] & 0xFFFFu) : 0u);
+    return __builtin_bit_cast(u16x8, w);
 }
 
 // The operand pieces of one step, held in registers between their loads and their LDS writes
@@ -164,73 +192,80 @@ __device__ __forceinline__ bf16x8 nn_row_operand(const uint16_t* lb, int t, int 
     return __builtin_bit_cast(bf16x8, v);
 }
 
-// A's pieces of the reduction slice [k0, k0 + 64) of the wave's rows, and their LDS writes
-// (rows past `rows` and columns past k zeroed).
+// A's pieces of the reduction slice [k0, k0 + 64) of the wave's rows (a_row: element of the
+// first), and their LDS writes (rows past `rows` and columns past k zeroed).
 template <bool VEC>
-__device__ __forceinline__ void load_a(const uint16_t* a_blk, const Shape& s, int rows, int k0,
+__device__ __forceinline__ void load_a(const uint16_t* a, int64_t a_row, const Shape& s, int rows, int k0,
                                        int lane, bool stream, u16x8 (&pa)[kAPieces]) {
 #pragma unroll
     for (int q = 0; q < kAPieces; ++q) {
         const int r = piece_row(lane, q);
-        const uint16_t* row = a_blk + static_cast<int64_t>(r < rows ? r : (rows > 0 ? rows - 1 : 0)) * s.k;
+        const int64_t row = a_row + static_cast<int64_t>(r < rows ? r : (rows > 0 ? rows - 1 : 0)) * s.k;
         const int c = k0 + piece_col(lane, q);
-        pa[q] = stream ? load8<VEC, true>(row, c, s.k) : load8<VEC, false>(row, c, s.k);
+        pa[q] = stream ? load8<VEC, true>(a, row, c, s.k, s.a_total) : load8<VEC, false>(a, row, c, s.k, s.a_total);
     }
 }
 
 template <bool VEC>
-__device__ __forceinline__ void write_a(const u16x8 (&pa)[kAPieces], const Shape& s, int rows,
+__device__ __forceinline__ void write_a(const u16x8 (&pa)[kAPieces], int64_t a_row, const Shape& s, int rows,
                                         int k0, int lane, uint16_t* la) {
 #pragma unroll
     for (int q = 0; q < kAPieces; ++q) {
         const int r = piece_row(lane, q), c = piece_col(lane, q);
-        *reinterpret_cast<u16x8*>(la + r * kLdk + c) = keep8<VEC>(pa[q], k0 + c, s.k, r < rows);
+        *reinterpret_cast<u16x8*>(la + r * kLdk + c) =
+            keep8<VEC>(pa[q], a_row + static_cast<int64_t>(r) * s.k, k0 + c, s.k, s.a_total, r < rows,
+                       k0 + kChunkK <= s.k);
     }
 }
 
 // The wave's quarter of the B block of step (j0, k0): pieces q = kBPieces * wave + 0, 1, of
-// the block's 64 x 64 as 64 lanes x 8 pieces (B's rows for NT, B's rows k0.. for NN).
+// the block's 64 x 64 as 64 lanes x 8 pieces (B's rows for NT, B's rows k0.. for NN).  b_row:
+// element of the batch's first.
 template <int LAYOUT, bool VEC, bool WITH_A>
-__device__ __forceinline__ void load_step(const uint16_t* a_blk, const uint16_t* b_blk,
+__device__ __forceinline__ void load_step(const uint16_t* a, int64_t a_row, const uint16_t* b, int64_t b_row,
                                           const Shape& s, int rows, int j0, int k0, int wave,
                                           int lane, bool stream_a, Pieces<WITH_A>& p) {
-    if constexpr (WITH_A) load_a<VEC>(a_blk, s, rows, k0, lane, stream_a, p.a);
+    if constexpr (WITH_A) load_a<VEC>(a, a_row, s, rows, k0, lane, stream_a, p.a);
 #pragma unroll
     for (int q = 0; q < kBPieces; ++q) {
         const int qg = kBPieces * wave + q;
         if constexpr (LAYOUT == kNT) {
             const int j = j0 + piece_row(lane, qg);
-            p.b[q] = load8<VEC>(b_blk + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k,
-                                k0 + piece_col(lane, qg), s.k);
+            p.b[q] = load8<VEC>(b, b_row + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k,
+                                k0 + piece_col(lane, qg), s.k, s.b_total);
         } else {
             const int kr = k0 + piece_nn_row(lane, qg);
-            p.b[q] = load8<VEC>(b_blk + static_cast<int64_t>(kr < s.k ? kr : s.k - 1) * s.n,
-                                j0 + piece_nn_col(lane, qg), s.n);
+            p.b[q] = load8<VEC>(b, b_row + static_cast<int64_t>(kr < s.k ? kr : s.k - 1) * s.n,
+                                j0 + piece_nn_col(lane, qg), s.n, s.b_total);
         }
     }
 }
 
 template <int LAYOUT, bool VEC, bool WITH_A>
-__device__ __forceinline__ void write_step(const Pieces<WITH_A>& p, const Shape& s, int rows,
-                                           int j0, int k0, int wave, int lane, uint16_t* la,
+__device__ __forceinline__ void write_step(const Pieces<WITH_A>& p, int64_t a_row, int64_t b_row, const Shape& s,
+                                           int rows, int j0, int k0, int wave, int lane, uint16_t* la,
                                            uint16_t* lb) {
-    if constexpr (WITH_A) write_a<VEC>(p.a, s, rows, k0, lane, la);
+    if constexpr (WITH_A) write_a<VEC>(p.a, a_row, s, rows, k0, lane, la);
 #pragma unroll
     for (int q = 0; q < kBPieces; ++q) {
         const int qg = kBPieces * wave + q;
         if constexpr (LAYOUT == kNT) {
             const int r = piece_row(lane, qg), c = piece_col(lane, qg);
-            *reinterpret_cast<u16x8*>(lb + r * kLdk + c) = keep8<VEC>(p.b[q], k0 + c, s.k, j0 + r < s.n);
+            *reinterpret_cast<u16x8*>(lb + r * kLdk + c) =
+                keep8<VEC>(p.b[q], b_row + static_cast<int64_t>(j0 + r) * s.k, k0 + c, s.k, s.b_total,
+                           j0 + r < s.n, k0 + kChunkK <= s.k);
         } else {
             const int kr = piece_nn_row(lane, qg), c = piece_nn_col(lane, qg);
-            *reinterpret_cast<u16x8*>(lb + kr * kLdv + c) = keep8<VEC>(p.b[q], j0 + c, s.n, k0 + kr < s.k);
+            *reinterpret_cast<u16x8*>(lb + kr * kLdv + c) =
+                keep8<VEC>(p.b[q], b_row + static_cast<int64_t>(k0 + kr) * s.n, j0 + c, s.n, s.b_total,
+                           k0 + kr < s.k, j0 + kBlockN <= s.n);
         }
     }
 }
 
 // Stores a staged output block (rows [i0, i0 + rows), columns [j0, j0 + jn)) as whole rows:
-// 16 lanes x 4 fp32 columns, four rows per instruction.
-template <bool VEC, bool TEMPORAL>
+// 16 lanes x 4 fp32 columns, four rows per instruction, 16 bytes per lane at any alignment.
+template <bool TEMPORAL>
 __device__ __forceinline__ void store_block_f32(float* c, const Shape& s, int64_t bidx, int i0, int rows,
                                             int j0, int jn, int lane, const float* lc) {
     const int col = (lane & 15) * 4;
@@ -239,7 +274,7 @@ __device__ __forceinline__ void store_block_f32(float* c, const Shape& s, int64_
     const int64_t off0 = bidx * s.c_batch + static_cast<int64_t>(i0 + rq) * s.n + j0 + col;
     const int64_t step = 4 * static_cast<int64_t>(s.n);
     const bool col_ok = col < jn;
-    const bool whole = VEC && col + 3 < jn;
+    const bool whole = col + 3 < jn;
 #pragma unroll
     for (int r0 = 0; r0 < kTileM; r0 += 4) {
         const int r = r0 + rq;
@@ -248,9 +283,9 @@ __device__ __forceinline__ void store_block_f32(float* c, const Shape& s, int64_
             float* cp = c + off0 + (r0 / 4) * step;
             if (whole) {
                 if constexpr (TEMPORAL)
-                    *reinterpret_cast<f32x4*>(cp) = v;
+                    *reinterpret_cast<f32x4_any*>(cp) = v;
                 else
-                    __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(cp));
+                    __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any*>(cp));
             } else {
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -262,7 +297,7 @@ __device__ __forceinline__ void store_block_f32(float* c, const Shape& s, int64_
 
 // The same for a block staged as bf16 ([32][kLdh]): 8 lanes x 8 columns, eight rows per
 // instruction.
-template <bool VEC, bool TEMPORAL>
+template <bool TEMPORAL>
 __device__ __forceinline__ void store_block_bf16(uint16_t* c, const Shape& s, int64_t bidx, int i0,
                                              int rows, int j0, int jn, int lane, const uint16_t* lh) {
     const int col = (lane & 7) * 8;
@@ -270,7 +305,7 @@ __device__ __forceinline__ void store_block_bf16(uint16_t* c, const Shape& s, in
     const int64_t off0 = bidx * s.c_batch + static_cast<int64_t>(i0 + rq) * s.n + j0 + col;
     const int64_t step = 8 * static_cast<int64_t>(s.n);
     const bool col_ok = col < jn;
-    const bool whole = VEC && col + 7 < jn;
+    const bool whole = col + 7 < jn;
 #pragma unroll
     for (int r0 = 0; r0 < kTileM; r0 += 8) {
         const int r = r0 + rq;
@@ -279,9 +314,9 @@ __device__ __forceinline__ void store_block_bf16(uint16_t* c, const Shape& s, in
             uint16_t* cp = c + off0 + (r0 / 8) * step;
             if (whole) {
                 if constexpr (TEMPORAL)
-                    *reinterpret_cast<u32x4*>(cp) = __builtin_bit_cast(u32x4, v);
+                    *reinterpret_cast<u32x4_any*>(cp) = __builtin_bit_cast(u32x4, v);
                 else
-                    __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4*>(cp));
+                    __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), reinterpret_cast<u32x4_any*>(cp));
             } else {
 #pragma unroll
                 for (int e = 0; e < 8; ++e)
@@ -337,8 +372,8 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
     const int li = lane & 31;
     const int h = lane >> 5;
     uint16_t* const la = lw;
-    const uint16_t* a_blk = rows > 0 ? a + bidx * s.a_batch + static_cast<int64_t>(i0) * s.k : a;
-    const uint16_t* b_blk = b + bidx * s.b_batch;
+    const int64_t a_row = rows > 0 ? bidx * s.a_batch + static_cast<int64_t>(i0) * s.k : 0;
+    const int64_t b_row = bidx * s.b_batch;
     const int nk = (s.k + kChunkK - 1) / kChunkK;  // k > 0 here
     const int nj = (s.n + kBlockN - 1) / kBlockN;
     const int nsteps = nk * nj;
@@ -353,8 +388,8 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
     u16x8 a_reg[AREG ? kChunkK / kTileK : 1];
     if constexpr (AREG) {  // A once, through the wave's LDS into its MFMA layout
         u16x8 pa[kAPieces];
-        load_a<VEC>(a_blk, s, rows, 0, lane, !TEMPORAL, pa);  // read once
-        write_a<VEC>(pa, s, rows, 0, lane, la);
+        load_a<VEC>(a, a_row, s, rows, 0, lane, !TEMPORAL, pa);  // read once
+        write_a<VEC>(pa, a_row, s, rows, 0, lane, la);
         wave_lds_sync();
 #pragma unroll
         for (int q = 0; q < kChunkK / kTileK; ++q)
@@ -367,7 +402,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
     // on the last step once it gets there (its loads are then issued again, unused).
     int ld_st = 0, ld_j = 0, ld_k = 0;
     auto load = [&](Pieces<!AREG>& pp) {
-        load_step<LAYOUT, VEC, !AREG>(a_blk, b_blk, s, rows, ld_j * kBlockN, ld_k * kChunkK, wave, lane,
+        load_step<LAYOUT, VEC, !AREG>(a, a_row, b, b_row, s, rows, ld_j * kBlockN, ld_k * kChunkK, wave, lane,
                                       !TEMPORAL && nj == 1, pp);  // A read once when one column block
         if (ld_st + 1 < nall) {
             ++ld_st;
@@ -416,7 +451,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
         const int j0 = jb * kBlockN;
         // lb (buffer st % 2) was last read at step st - 2; every wave finished that step
         // before the barrier of step st - 1, so one barrier per step orders both uses.
-        write_step<LAYOUT, VEC, !AREG>(pp, s, rows, j0, kb * kChunkK, wave, lane, la, lb);
+        write_step<LAYOUT, VEC, !AREG>(pp, a_row, b_row, s, rows, j0, kb * kChunkK, wave, lane, la, lb);
         __syncthreads();
         // issued on every step (past the last step: the last step's operands again, cache
         // hits, unused), so that every path has the same loads in flight
@@ -531,7 +566,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
                               pack_bf16(scale * acc[t][4 * g + 2], scale * acc[t][4 * g + 3])};
             }
             wave_lds_sync();
-            store_block_bf16<VEC, TEMPORAL>(static_cast<uint16_t*>(c), s, bidx, i0, rows, j0, jn, lane, lh);
+            store_block_bf16<TEMPORAL>(static_cast<uint16_t*>(c), s, bidx, i0, rows, j0, jn, lane, lh);
         } else {
             float* const lc = reinterpret_cast<float*>(lw);
 #pragma unroll
@@ -543,7 +578,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
                               scale * acc[t][4 * g + 2], scale * acc[t][4 * g + 3]};
             }
             wave_lds_sync();
-            store_block_f32<VEC, TEMPORAL>(static_cast<float*>(c), s, bidx, i0, rows, j0, jn, lane, lc);
+            store_block_f32<TEMPORAL>(static_cast<float*>(c), s, bidx, i0, rows, j0, jn, lane, lc);
         }
         wave_lds_sync();  // the next step rewrites the region
         if constexpr (!AREG) {
@@ -638,14 +673,14 @@ struct S1Pieces {
 
 // The wave's quarter of B's rows [j0, j0 + 128), reduction slice [k0, k0 + 64), and its LDS
 // write (rows past n and columns past k zeroed).
-__device__ __forceinline__ void s1_load(const uint16_t* b_blk, const Shape& s, int j0, int k0, int wave,
+__device__ __forceinline__ void s1_load(const uint16_t* b, int64_t b_row, const Shape& s, int j0, int k0, int wave,
                                         int lane, S1Pieces& p) {
 #pragma unroll
     for (int q = 0; q < kS1BPieces; ++q) {
         const int qg = kS1BPieces * wave + q;
         const int j = j0 + piece_row(lane, qg);
-        p.b[q] = load8<true>(b_blk + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k,
-                             k0 + piece_col(lane, qg), s.k);
+        p.b[q] = load8<true>(b, b_row + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k,
+                             k0 + piece_col(lane, qg), s.k, s.b_total);
     }
 }
 
@@ -655,7 +690,7 @@ __device__ __forceinline__ void s1_write(const S1Pieces& p, const Shape& s, int 
     for (int q = 0; q < kS1BPieces; ++q) {
         const int qg = kS1BPieces * wave + q;
         const int r = piece_row(lane, qg), c = piece_col(lane, qg);
-        *reinterpret_cast<u16x8*>(lb + r * kLdk + c) = keep8<true>(p.b[q], k0 + c, s.k, j0 + r < s.n);
+        *reinterpret_cast<u16x8*>(lb + r * kLdk + c) = keep8<true>(p.b[q], 0, k0 + c, s.k, s.b_total, j0 + r < s.n, false);
     }
 }
 
@@ -675,7 +710,7 @@ __device__ __forceinline__ void s1_store_block(const f32x16 (&v)[kBlockTiles], f
                     u32x2{pack_bf16(scale * v[t][4 * g], scale * v[t][4 * g + 1]),
                           pack_bf16(scale * v[t][4 * g + 2], scale * v[t][4 * g + 3])};
         wave_lds_sync();
-        store_block_bf16<true, TEMPORAL>(static_cast<uint16_t*>(c), s, bidx, i0, rows, j0, jn, lane, lw);
+        store_block_bf16<TEMPORAL>(static_cast<uint16_t*>(c), s, bidx, i0, rows, j0, jn, lane, lw);
     } else {
         float* const lc = reinterpret_cast<float*>(lw);
 #pragma unroll
@@ -686,7 +721,7 @@ __device__ __forceinline__ void s1_store_block(const f32x16 (&v)[kBlockTiles], f
                     f32x4{scale * v[t][4 * g], scale * v[t][4 * g + 1], scale * v[t][4 * g + 2],
                           scale * v[t][4 * g + 3]};
         wave_lds_sync();
-        store_block_f32<true, TEMPORAL>(static_cast<float*>(c), s, bidx, i0, rows, j0, jn, lane, lc);
+        store_block_f32<TEMPORAL>(static_cast<float*>(c), s, bidx, i0, rows, j0, jn, lane, lc);
     }
     wave_lds_sync();  // the next block rewrites the region
 }
@@ -702,8 +737,8 @@ __device__ __forceinline__ void round_rows_s1(const uint16_t* a, const uint16_t*
     const int li = lane & 31;
     const int h = lane >> 5;
     const int q = wave & 1;
-    const uint16_t* a_blk = rows > 0 ? a + bidx * s.a_batch + static_cast<int64_t>(i0) * s.k : a;
-    const uint16_t* b_blk = b + bidx * s.b_batch;
+    const int64_t a_row = rows > 0 ? bidx * s.a_batch + static_cast<int64_t>(i0) * s.k : 0;
+    const int64_t b_row = bidx * s.b_batch;
     const int nj = (s.n + kBlockN - 1) / kBlockN;  // 2 .. 8
     const int ns = (nj + 1) / 2;                   // steps: 1 .. 4
     // Sub-steps: chunk kc (64 deep) of step st is sub-step NK st + kc (NK = 2 with DEEP).
@@ -715,10 +750,10 @@ __device__ __forceinline__ void round_rows_s1(const uint16_t* a, const uint16_t*
     // ordinary loads, so that the second finds them in cache.
     u16x8 pa[NK][kAPieces];
 #pragma unroll
-    for (int kc = 0; kc < NK; ++kc) load_a<true>(a_blk, s, rows, kc * kChunkK, lane, false, pa[kc]);
+    for (int kc = 0; kc < NK; ++kc) load_a<true>(a, a_row, s, rows, kc * kChunkK, lane, false, pa[kc]);
     S1Pieces p[kDepth];
-    s1_load(b_blk, s, sub_j0(0), sub_k0(0), wave, lane, p[0]);
-    s1_load(b_blk, s, sub_j0(nu > 1 ? 1 : 0), sub_k0(nu > 1 ? 1 : 0), wave, lane, p[1]);
+    s1_load(b, b_row, s, sub_j0(0), sub_k0(0), wave, lane, p[0]);
+    s1_load(b, b_row, s, sub_j0(nu > 1 ? 1 : 0), sub_k0(nu > 1 ? 1 : 0), wave, lane, p[1]);
     // A through the wave's LDS into its MFMA layout: into registers (k <= 64), or kept there
     // for the round (DEEP, row pitch kLdA)
     constexpr int LDA = DEEP ? kLdA : kLdk;
@@ -728,7 +763,7 @@ __device__ __forceinline__ void round_rows_s1(const uint16_t* a, const uint16_t*
         for (int qq = 0; qq < kAPieces; ++qq) {
             const int r = piece_row(lane, qq), cc = piece_col(lane, qq);
             *reinterpret_cast<u16x8*>(lw + r * LDA + kc * kChunkK + cc) =
-                keep8<true>(pa[kc][qq], kc * kChunkK + cc, s.k, r < rows);
+                keep8<true>(pa[kc][qq], 0, kc * kChunkK + cc, s.k, s.a_total, r < rows, false);
         }
     }
     wave_lds_sync();
@@ -753,7 +788,7 @@ __device__ __forceinline__ void round_rows_s1(const uint16_t* a, const uint16_t*
             s1_write(p[u & 1], s, sub_j0(u), sub_k0(u), wave, lane, lb);
             __syncthreads();
             // sub-step u + 2's operands (none past the last)
-            if (u + 2 < nu) s1_load(b_blk, s, sub_j0(u + 2), sub_k0(u + 2), wave, lane, p[u & 1]);
+            if (u + 2 < nu) s1_load(b, b_row, s, sub_j0(u + 2), sub_k0(u + 2), wave, lane, p[u & 1]);
 #pragma unroll
             for (int kk = 0; kk < kChunkK; kk += kTileK) {
                 bf16x8 av;
@@ -962,10 +997,9 @@ extern __shared__ uint16_t bsm_gemm_lds[];  // wg_lds_bytes() per workgroup
 
 constexpr int kGemmThreads = 64 * kWaves;
 
-// The element-wise (unaligned / odd-size) form is compiled for two waves per SIMD: its
-// registers do not fit three; so is the single-pass softmax, whose held products take 128, and
-// the two-pass softmax with A staged through LDS (k > 64): capped at three waves it spilled 149
-// registers and took 157 us at 192 x 512 x 512 x 128, against 83 us at two.
+// Compiled for two waves per SIMD: the single-pass softmax, whose held products take 128
+// registers, and the two-pass softmax with A staged through LDS (k > 64): capped at three waves
+// it spilled 149 registers and took 157 us at 192 x 512 x 512 x 128, against 83 us at two.
 // TEMPORAL: ordinary stores of C and loads of A (a consumer finds C in the Infinity Cache)
 // instead of nontemporal ones; a compile-time choice, so the default instance carries no
 // branch for it.  AREG (A's operands held in registers, k <= 64 < n, 16-byte form only): a
@@ -973,7 +1007,7 @@ constexpr int kGemmThreads = 64 * kWaves;
 constexpr bool use_areg(bool vec, int n, int k) { return vec && k <= kChunkK && n > kBlockN; }
 template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, bool AREG>
 __global__ void __launch_bounds__(kGemmThreads,
-                                  (MODE == kModeNtSoftmax1 || !VEC || (MODE == kModeNtSoftmax && !AREG))
+                                  (MODE == kModeNtSoftmax1 || (MODE == kModeNtSoftmax && !AREG))
                                       ? kS1WavesPerSimd : kWavesPerSimd)
 bsm_gemm_kernel(const uint16_t* a, const uint16_t* b, void* c, Shape s,
                 const int32_t* __restrict__ worker_ptr, const bsm_item* __restrict__ items,

@@ -57,7 +57,7 @@ int gemm_rows_per_wg(bool single_pass);
 // single_pass (layout 2): the one-pass form where the shape and 16-byte operands allow it,
 // else the two-pass form.
 hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pass, const void* a,
-                       const void* b, void* c, int m, int n, int k, float alpha,
+                       const void* b, void* c, int64_t batch, int m, int n, int k, float alpha,
                        const int32_t* d_worker_ptr, const bsm_item* d_items, int n_wg, void* trace,
                        hipStream_t stream);
 
