@@ -326,7 +326,8 @@ typedef enum {
 
 /* Build a matrix-product plan (out_dtype is C's type; home_xcd, topology and device as for
  * bsm_plan_create; topology->wg_threads must be 0 or 256, wg_per_cu defaults to 3, or to
- * 2 for the one-pass form of BSM_GEMM_NT_SOFTMAX).  A plan
+ * 2 for the one-pass form of BSM_GEMM_NT_SOFTMAX, for its two-pass form with 64 < k <= 128
+ * (k % 8 == 0, n > 64) and for BSM_GEMM_NN with n > 64 and k > 64 or odd).  A plan
  * made here runs only with bsm_gemm_execute.  Its stats report per_wave 0 (worker =
  * workgroup). */
 bsm_status bsm_gemm_plan_create(bsm_plan* out_plan, int64_t batch, int32_t m, int32_t n,

@@ -38,6 +38,7 @@ struct bsm_plan_s {
     bool gemm = false;
     int gemm_m = 0, gemm_n = 0, gemm_k = 0, gemm_layout = 0;
     bool gemm_single = false;  // layout 2 in one pass (products held in registers)
+    bool gemm_wide = false;    // the CU's LDS holds its workgroups' 128-wide B blocks
     int64_t gemm_batch = 0;
     int lds_floats_per_wave = 0;  // one-wave long-row staging (kernel classes 4, 5 on a device)
     int32_t flags = 0;            // BSM_FLAG_* bits
@@ -469,9 +470,9 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     if (static_cast<double>(batch) * std::max({m, n, k}) * std::max({m, n, k}) > 1.0e18)
         return fail(BSM_ERR_INVALID_ARG, "operands too large");
     // The kernel runs workgroups of gemm_wg_threads() threads whose waves share staged operands,
-    // gemm_waves_per_simd() per CU by default; each workgroup is one worker of the table.  The
-    // score softmax of k <= 128 and 64 < n <= 512 runs in one pass, two workgroups per CU (its
-    // LDS does not fit three), unless the topology asks for more.
+    // gemm_default_wgs_per_cu() per CU by default; each workgroup is one worker of the table.
+    // The score softmax of k <= 128 and 64 < n <= 512 runs in one pass, two workgroups per CU
+    // (its LDS does not fit three), unless the topology asks for more.
     bsm_topology t{};
     if (topology) t = *topology;
     const int wg_threads = bsm::gemm_wg_threads();
@@ -480,8 +481,9 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
                     wg_threads, t.wg_threads);
     const bool single = layout == BSM_GEMM_NT_SOFTMAX && bsm::gemm_single_pass_shape(n, k) &&
                         (t.wg_per_cu == 0 || t.wg_per_cu <= bsm::gemm_waves_per_simd(true));
-    if (t.wg_per_cu == 0) t.wg_per_cu = bsm::gemm_waves_per_simd(single);
+    if (t.wg_per_cu == 0) t.wg_per_cu = bsm::gemm_default_wgs_per_cu(layout, n, k, single);
     const bool bf16_out = out_dtype == BSM_BF16;
+    bool wide = false;
     if (device >= 0) {
         DeviceGuard g;
         hipError_t e = g.enter(device);
@@ -493,6 +495,8 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
             per_wg * t.wg_per_cu > static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor))
             return fail(BSM_ERR_INVALID_ARG, "wg_per_cu %d: %lld bytes of LDS per workgroup do not fit",
                         t.wg_per_cu, static_cast<long long>(per_wg));
+        wide = static_cast<int64_t>(bsm::gemm_wide_lds_bytes_per_wg(bf16_out)) * t.wg_per_cu <=
+               static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor);
     }
     // planned with one-wave workgroups, so that every worker is a workgroup (same index, same
     // XCD); the launch then runs the real workgroup size
@@ -515,6 +519,7 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     p->gemm_k = k;
     p->gemm_layout = layout;
     p->gemm_single = single;
+    p->gemm_wide = wide;
     p->gemm_batch = batch;
     p->table.stats.algorithmic_bytes =
         batch * (2 * (static_cast<int64_t>(m) * k + static_cast<int64_t>(n) * k) +
@@ -550,7 +555,7 @@ bsm_status execute_gemm(bsm_plan p, const void* a, const void* b, void* c, float
     hipStream_t s = static_cast<hipStream_t>(stream);
     // k == 0 runs the same kernel: an empty reduction stores zeros
     e = bsm::launch_gemm(p->gemm_layout, p->dtype == BSM_BF16, (p->flags & BSM_FLAG_TEMPORAL) != 0,
-                         p->gemm_single, a, b, c, p->gemm_batch, p->gemm_m, p->gemm_n,
+                         p->gemm_single, p->gemm_wide, a, b, c, p->gemm_batch, p->gemm_m, p->gemm_n,
                          p->gemm_k, alpha, p->d_worker_ptr, p->d_items, p->topo.n_wg(), trace, s);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     p->used = true;

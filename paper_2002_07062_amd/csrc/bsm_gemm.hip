@@ -1,6 +1,7 @@
 // Host launch wrappers of the batched matrix-product kernels (device code in bsm_gemm.hpp).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "bsm.h"
@@ -11,7 +12,7 @@ namespace {
 
 using bsm_mm::Shape;
 
-template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, bool AREG>
+template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, int FORM>
 hipError_t launch_g(const void* a, const void* b, void* c, const Shape& s, const int32_t* worker_ptr,
                     const bsm_item* items, int n_wg, void* trace, hipStream_t stream) {
     const uint16_t* a_a = static_cast<const uint16_t*>(a);
@@ -20,10 +21,11 @@ hipError_t launch_g(const void* a, const void* b, void* c, const Shape& s, const
     Shape a_s = s;
     bsm_trace_rec* a_trace = static_cast<bsm_trace_rec*>(trace);
     void* args[] = {&a_a, &a_b, &a_c, &a_s, &worker_ptr, &items, &a_trace};
-    // single-pass instances: the last flag selects the deep form (64 < k <= 128)
-    const size_t lds = static_cast<size_t>(MODE == bsm_mm::kModeNtSoftmax1 ? bsm_mm::s1_lds_bytes(BF16OUT, AREG)
-                                                                         : bsm_mm::wg_lds_bytes(BF16OUT));
-    return hipLaunchKernel(reinterpret_cast<const void*>(&bsm_mm::bsm_gemm_kernel<MODE, BF16OUT, VEC, TEMPORAL, AREG>),
+    constexpr int layout = MODE == bsm_mm::kModeNn ? bsm_mm::kNN : bsm_mm::kNT;
+    const size_t lds = static_cast<size_t>(MODE == bsm_mm::kModeNtSoftmax1
+                                               ? bsm_mm::s1_lds_bytes(BF16OUT, FORM == bsm_mm::kFormA2)
+                                               : bsm_mm::wg_bytes<layout, FORM>(BF16OUT));
+    return hipLaunchKernel(reinterpret_cast<const void*>(&bsm_mm::bsm_gemm_kernel<MODE, BF16OUT, VEC, TEMPORAL, FORM>),
                            dim3(n_wg), dim3(bsm_mm::kGemmThreads), args, lds, stream);
 }
 
@@ -34,16 +36,26 @@ namespace bsm {
 int gemm_wg_threads() { return bsm_mm::kGemmThreads; }
 bool gemm_single_pass_shape(int n, int k) { return bsm_mm::single_pass_shape(n, k); }
 int gemm_lds_bytes_per_wg(bool bf16_out, bool single_pass) {
-    return single_pass ? bsm_mm::s1_lds_bytes(bf16_out, true) : bsm_mm::wg_lds_bytes(bf16_out);
+    return single_pass ? bsm_mm::s1_lds_bytes(bf16_out, true)
+                       : bsm_mm::wg_bytes<bsm_mm::kNT, bsm_mm::kFormStep>(bf16_out);
+}
+int gemm_wide_lds_bytes_per_wg(bool bf16_out) {
+    return std::max(bsm_mm::wg_bytes<bsm_mm::kNT, bsm_mm::kFormA2>(bf16_out),
+                    bsm_mm::wg_bytes<bsm_mm::kNN, bsm_mm::kFormWide>(bf16_out));
 }
 int gemm_waves_per_simd(bool single_pass) {
     return single_pass ? bsm_mm::kS1WavesPerSimd : bsm_mm::kWavesPerSimd;
+}
+int gemm_default_wgs_per_cu(int layout, int n, int k, bool single_pass) {
+    if (single_pass) return bsm_mm::kS1WavesPerSimd;
+    const int form = bsm_mm::form_of(layout, k % 8 == 0, true, n, k);
+    return form == bsm_mm::kFormStep ? bsm_mm::kWavesPerSimd : bsm_mm::waves_per_simd(layout, form);
 }
 int gemm_rows_per_wg(bool single_pass) {
     return single_pass ? bsm_mm::kS1Rows : bsm_mm::kWaves * bsm_mm::kTileM;
 }
 
-hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pass, const void* a,
+hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pass, bool wide, const void* a,
                        const void* b, void* c, int64_t batch, int m, int n, int k, float alpha,
                        const int32_t* d_worker_ptr, const bsm_item* d_items, int n_wg, void* trace,
                        hipStream_t stream) {
@@ -61,29 +73,41 @@ hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pas
     // NN's B of n elements, both bases 16-byte aligned (C is stored at any element boundary)
     const uintptr_t ptrs = reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b);
     const bool vec = (ptrs & 15) == 0 && k % 8 == 0 && (layout != bsm_mm::kNN || n % 8 == 0);
-    const bool areg = bsm_mm::use_areg(vec, n, k);
-#define BSM_G(M, O, V, T, R) launch_g<M, O, V, T, R>(a, b, c, s, d_worker_ptr, d_items, n_wg, trace, stream)
-#define BSM_GV(M, O, T) (!vec ? BSM_G(M, O, false, T, false) \
-                              : (areg ? BSM_G(M, O, true, T, true) : BSM_G(M, O, true, T, false)))
-#define BSM_G1(M, T) (bf16_out ? BSM_GV(M, true, T) : BSM_GV(M, false, T))
-#define BSM_G2(M) (temporal ? BSM_G1(M, true) : BSM_G1(M, false))
+    const int form = bsm_mm::form_of(layout, vec, wide, n, k);
+    const int out = (bf16_out ? 1 : 0) | (temporal ? 2 : 0);
+#define BSM_G(M, V, F)                                                                                        \
+    switch (out) {                                                                                            \
+        case 0: return launch_g<M, false, V, false, F>(a, b, c, s, d_worker_ptr, d_items, n_wg, trace, stream); \
+        case 1: return launch_g<M, true, V, false, F>(a, b, c, s, d_worker_ptr, d_items, n_wg, trace, stream);  \
+        case 2: return launch_g<M, false, V, true, F>(a, b, c, s, d_worker_ptr, d_items, n_wg, trace, stream);  \
+        default: return launch_g<M, true, V, true, F>(a, b, c, s, d_worker_ptr, d_items, n_wg, trace, stream);  \
+    }
+    using namespace bsm_mm;
     // the one-pass softmax takes alpha != 0 only (with alpha = 0 every logit is 0, which the
     // two-pass form handles)
-    if (layout == bsm_mm::kModeNtSoftmax && single_pass && vec && alpha != 0.0f &&
-        bsm_mm::single_pass_shape(n, k)) {
-        // the last flag of the single-pass instance: 64 < k <= 128 (A kept in LDS)
-#define BSM_G1P(O, T) (k > bsm_mm::kChunkK ? BSM_G(bsm_mm::kModeNtSoftmax1, O, true, T, true) \
-                                           : BSM_G(bsm_mm::kModeNtSoftmax1, O, true, T, false))
-        if (bf16_out) return temporal ? BSM_G1P(true, true) : BSM_G1P(true, false);
-        return temporal ? BSM_G1P(false, true) : BSM_G1P(false, false);
-#undef BSM_G1P
+    if (layout == kModeNtSoftmax && single_pass && vec && alpha != 0.0f && single_pass_shape(n, k)) {
+        if (k > kChunkK) BSM_G(kModeNtSoftmax1, true, kFormA2)
+        BSM_G(kModeNtSoftmax1, true, kFormA1)
     }
-    if (layout == bsm_mm::kNN) return BSM_G2(bsm_mm::kModeNn);
-    if (layout == bsm_mm::kModeNtSoftmax) return BSM_G2(bsm_mm::kModeNtSoftmax);
-    return BSM_G2(bsm_mm::kModeNt);
-#undef BSM_G2
-#undef BSM_G1
-#undef BSM_GV
+    if (layout == kNN) {
+        if (form == kFormA1) BSM_G(kModeNn, true, kFormA1)
+        if (form == kFormWide) {
+            if (vec) BSM_G(kModeNn, true, kFormWide)
+            BSM_G(kModeNn, false, kFormWide)
+        }
+        if (vec) BSM_G(kModeNn, true, kFormStep)
+        BSM_G(kModeNn, false, kFormStep)
+    }
+    if (layout == kModeNtSoftmax) {
+        if (form == kFormA1) BSM_G(kModeNtSoftmax, true, kFormA1)
+        if (form == kFormA2) BSM_G(kModeNtSoftmax, true, kFormA2)
+        if (vec) BSM_G(kModeNtSoftmax, true, kFormStep)
+        BSM_G(kModeNtSoftmax, false, kFormStep)
+    }
+    if (form == kFormA1) BSM_G(kModeNt, true, kFormA1)
+    if (form == kFormA2) BSM_G(kModeNt, true, kFormA2)
+    if (vec) BSM_G(kModeNt, true, kFormStep)
+    BSM_G(kModeNt, false, kFormStep)
 #undef BSM_G
 }
 

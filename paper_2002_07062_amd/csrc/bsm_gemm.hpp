@@ -66,19 +66,48 @@ constexpr int kChunkK = 64;                 // reduction indices per step
 constexpr int kLdk = kChunkK + 8;           // padded LDS row, elements
 constexpr int kBlockN = 64;                 // output columns per block (two tiles)
 constexpr int kBlockTiles = kBlockN / kTileN;
-constexpr int kLdc = kBlockN + 4;           // padded LDS row of the staged output, floats
-constexpr int kLdh = kBlockN + 8;           // ... staged as bf16, elements
-constexpr int kLdv = kBlockN + 8;           // padded LDS row of NN's B (rows = reduction index)
-static_assert(kChunkK * kLdv <= kBlockN * kLdk, "NN's B fits the B buffer");
-constexpr int kBBufElems = kBlockN * kLdk;  // one shared B buffer
+constexpr int kLdh = kBlockN + 8;           // padded LDS row of the staged output as bf16, elements
 constexpr int kDepth = 2;                   // steps of operands in flight = shared B buffers
-constexpr int wave_lds_bytes(bool bf16_out) {
-    return (bf16_out ? kTileM * kLdh * 2 : kTileM * kLdc * 4) > kTileM * kLdk * 2
-               ? (bf16_out ? kTileM * kLdh * 2 : kTileM * kLdc * 4) : kTileM * kLdk * 2;
+constexpr int kAPieces = kTileM * kChunkK / 8 / 64;  // 16-byte pieces of A per lane per slice
+
+// Forms of a product (one compiled instance each).
+//   kFormStep  A staged at every step, with B
+//   kFormA1    A's operands held in registers for every column block: k <= 64 (64 < n)
+//   kFormA2    the same for 64 < k <= 128; a step is the whole reduction (128 deep)
+//   kFormWide  NN with blocks of 128 columns (64 < n): A is read once for n <= 128 instead of
+//              once per 64 columns
+// Against kFormStep (bf16 output): 32 x (2048 x 128)(128 x 2048) with the row softmax, whose
+// 32 column blocks each staged A again, twice, 303 -> 147 us; 32 x (2048 x 2048)(2048 x 128)
+// 122 -> 76 us.
+enum { kFormStep = 0, kFormA1 = 1, kFormA2 = 2, kFormWide = 3 };
+
+// Block and LDS geometry of a form.
+template <int LAYOUT, int FORM>
+struct Geo {
+    static constexpr bool kAReg = FORM == kFormA1 || FORM == kFormA2;
+    static constexpr int kStepK = FORM == kFormA2 ? 2 * kChunkK : kChunkK;  // reduction per step
+    static constexpr int kTiles = FORM == kFormWide ? 4 : 2;                // 32-column tiles per block
+    static constexpr int kN = kTiles * kTileN;                              // output columns per block
+    static constexpr int kBRows = LAYOUT == kNT ? kN : kStepK;  // B's block in LDS, as in memory
+    static constexpr int kBCols = LAYOUT == kNT ? kStepK : kN;
+    static constexpr int kLdb = kBCols + 8;                     // padded LDS row
+    static constexpr int kBBuf = kBRows * kLdb;                 // one shared B buffer, elements
+    static constexpr int kBPieces = kBRows * kBCols / 8 / 64 / kWaves;  // of B per lane (a quarter)
+    // fp32 output columns staged at a time: the forms with a 128-wide B block stage 32, so that
+    // three workgroups' LDS fits a CU
+    static constexpr int kStageF = kBCols > kChunkK ? kTileN : kBlockN;
+    static constexpr int kLdc = kStageF + 4;                    // padded LDS row of it, floats
+};
+template <int LAYOUT, int FORM>
+constexpr int wave_bytes(bool bf16_out) {
+    using G = Geo<LAYOUT, FORM>;
+    const int out = bf16_out ? kTileM * kLdh * 2 : kTileM * G::kLdc * 4;
+    return out > kTileM * kLdk * 2 ? out : kTileM * kLdk * 2;
 }
-constexpr int wg_lds_bytes(bool bf16_out) { return kWaves * wave_lds_bytes(bf16_out) + kDepth * kBBufElems * 2; }
-constexpr int kAPieces = kTileM * kChunkK / 8 / 64;            // 16-byte pieces of A per lane per step
-constexpr int kBPieces = kBlockN * kChunkK / 8 / 64 / kWaves;  // ... of B per lane (a quarter)
+template <int LAYOUT, int FORM>
+constexpr int wg_bytes(bool bf16_out) {
+    return kWaves * wave_bytes<LAYOUT, FORM>(bf16_out) + kDepth * Geo<LAYOUT, FORM>::kBBuf * 2;
+}
 
 __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -154,20 +183,18 @@ __device__ __forceinline__ u16x8 keep8(u16x8 v, int64_t row, int c, int len, int
 
 // The operand pieces of one step, held in registers between their loads and their LDS writes
 // so that a step's loads are in flight while earlier steps compute.
-template <bool WITH_A>
+template <class G>
 struct Pieces {
-    u16x8 a[WITH_A ? kAPieces : 1];
-    u16x8 b[kBPieces];
+    u16x8 a[G::kAReg ? 1 : kAPieces];
+    u16x8 b[G::kBPieces];
 };
 
-// Piece q of a lane.  A and NT's B: lanes walk rows 8 pieces (128 bytes) at a time.  NN's B:
-// lane = reduction index, piece q = columns 8q .. 8q+7, so that the transposed LDS writes of
-// consecutive lanes fall in consecutive bytes.
-__device__ __forceinline__ int piece_row(int lane, int q) { return (lane + 64 * q) / (kChunkK / 8); }
-__device__ __forceinline__ int piece_col(int lane, int q) { return ((lane + 64 * q) % (kChunkK / 8)) * 8; }
-// NN's B: rows of kBlockN columns, kBlockN / 8 pieces each
-__device__ __forceinline__ int piece_nn_row(int lane, int q) { return (lane + 64 * q) / (kBlockN / 8); }
-__device__ __forceinline__ int piece_nn_col(int lane, int q) { return ((lane + 64 * q) % (kBlockN / 8)) * 8; }
+// Piece q of a lane, of a block whose rows have COLS elements: lanes walk a row's pieces, then
+// the next row's.
+template <int COLS = kChunkK>
+__device__ __forceinline__ int piece_row(int lane, int q) { return (lane + 64 * q) / (COLS / 8); }
+template <int COLS = kChunkK>
+__device__ __forceinline__ int piece_col(int lane, int q) { return ((lane + 64 * q) % (COLS / 8)) * 8; }
 
 typedef short i16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
@@ -177,12 +204,13 @@ typedef __attribute__((address_space(3))) i16x4 lds_i16x4;
 // receives element i % 4 of the 8-byte loads of the group's lanes 4r + i / 4, r = 0..3; so
 // group lane s points at row kb + s / 4, columns jb + 4 (s % 4) .. +3, and lane i ends with
 // column jb + i of rows kb .. kb+3.  Two reads (kb and kb + 4) give the eight rows.
+template <int LDB>
 __device__ __forceinline__ bf16x8 nn_row_operand(const uint16_t* lb, int t, int kk, int lane) {
     const int g = lane >> 4, sl = lane & 15;
     const int kb = kk + 8 * (g >> 1), jb = t * kTileN + 16 * (g & 1);
-    const uint16_t* p0 = lb + (kb + (sl >> 2)) * kLdv + jb + 4 * (sl & 3);
+    const uint16_t* p0 = lb + (kb + (sl >> 2)) * LDB + jb + 4 * (sl & 3);
     const i16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p0));
-    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p0 + 4 * kLdv));
+    const i16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_i16x4*)(p0 + 4 * LDB));
     u16x8 v;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -218,69 +246,68 @@ __device__ __forceinline__ void write_a(const u16x8 (&pa)[kAPieces], int64_t a_r
     }
 }
 
-// The wave's quarter of the B block of step (j0, k0): pieces q = kBPieces * wave + 0, 1, of
-// the block's 64 x 64 as 64 lanes x 8 pieces (B's rows for NT, B's rows k0.. for NN).  b_row:
-// element of the batch's first.
-template <int LAYOUT, bool VEC, bool WITH_A>
+// The wave's quarter of the B block of step (j0, k0): pieces q = kBPieces * wave + 0, 1, .. of
+// the block (B's rows j0.. for NT, B's rows k0.. for NN).  b_row: element of the batch's first.
+template <int LAYOUT, bool VEC, class G>
 __device__ __forceinline__ void load_step(const uint16_t* a, int64_t a_row, const uint16_t* b, int64_t b_row,
                                           const Shape& s, int rows, int j0, int k0, int wave,
-                                          int lane, bool stream_a, Pieces<WITH_A>& p) {
-    if constexpr (WITH_A) load_a<VEC>(a, a_row, s, rows, k0, lane, stream_a, p.a);
+                                          int lane, bool stream_a, Pieces<G>& p) {
+    if constexpr (!G::kAReg) load_a<VEC>(a, a_row, s, rows, k0, lane, stream_a, p.a);
 #pragma unroll
-    for (int q = 0; q < kBPieces; ++q) {
-        const int qg = kBPieces * wave + q;
+    for (int q = 0; q < G::kBPieces; ++q) {
+        const int r = piece_row<G::kBCols>(lane, G::kBPieces * wave + q);
+        const int c = piece_col<G::kBCols>(lane, G::kBPieces * wave + q);
         if constexpr (LAYOUT == kNT) {
-            const int j = j0 + piece_row(lane, qg);
-            p.b[q] = load8<VEC>(b, b_row + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k,
-                                k0 + piece_col(lane, qg), s.k, s.b_total);
+            const int j = j0 + r;
+            p.b[q] = load8<VEC>(b, b_row + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k, k0 + c, s.k, s.b_total);
         } else {
-            const int kr = k0 + piece_nn_row(lane, qg);
-            p.b[q] = load8<VEC>(b, b_row + static_cast<int64_t>(kr < s.k ? kr : s.k - 1) * s.n,
-                                j0 + piece_nn_col(lane, qg), s.n, s.b_total);
+            const int kr = k0 + r;
+            p.b[q] = load8<VEC>(b, b_row + static_cast<int64_t>(kr < s.k ? kr : s.k - 1) * s.n, j0 + c, s.n, s.b_total);
         }
     }
 }
 
-template <int LAYOUT, bool VEC, bool WITH_A>
-__device__ __forceinline__ void write_step(const Pieces<WITH_A>& p, int64_t a_row, int64_t b_row, const Shape& s,
+template <int LAYOUT, bool VEC, class G>
+__device__ __forceinline__ void write_step(const Pieces<G>& p, int64_t a_row, int64_t b_row, const Shape& s,
                                            int rows, int j0, int k0, int wave, int lane, uint16_t* la,
                                            uint16_t* lb) {
-    if constexpr (WITH_A) write_a<VEC>(p.a, a_row, s, rows, k0, lane, la);
+    if constexpr (!G::kAReg) write_a<VEC>(p.a, a_row, s, rows, k0, lane, la);
 #pragma unroll
-    for (int q = 0; q < kBPieces; ++q) {
-        const int qg = kBPieces * wave + q;
-        if constexpr (LAYOUT == kNT) {
-            const int r = piece_row(lane, qg), c = piece_col(lane, qg);
-            *reinterpret_cast<u16x8*>(lb + r * kLdk + c) =
+    for (int q = 0; q < G::kBPieces; ++q) {
+        const int r = piece_row<G::kBCols>(lane, G::kBPieces * wave + q);
+        const int c = piece_col<G::kBCols>(lane, G::kBPieces * wave + q);
+        if constexpr (LAYOUT == kNT)
+            *reinterpret_cast<u16x8*>(lb + r * G::kLdb + c) =
                 keep8<VEC>(p.b[q], b_row + static_cast<int64_t>(j0 + r) * s.k, k0 + c, s.k, s.b_total,
-                           j0 + r < s.n, k0 + kChunkK <= s.k);
-        } else {
-            const int kr = piece_nn_row(lane, qg), c = piece_nn_col(lane, qg);
-            *reinterpret_cast<u16x8*>(lb + kr * kLdv + c) =
-                keep8<VEC>(p.b[q], b_row + static_cast<int64_t>(k0 + kr) * s.n, j0 + c, s.n, s.b_total,
-                           k0 + kr < s.k, j0 + kBlockN <= s.n);
-        }
+                           j0 + r < s.n, k0 + G::kStepK <= s.k);
+        else
+            *reinterpret_cast<u16x8*>(lb + r * G::kLdb + c) =
+                keep8<VEC>(p.b[q], b_row + static_cast<int64_t>(k0 + r) * s.n, j0 + c, s.n, s.b_total,
+                           k0 + r < s.k, j0 + G::kN <= s.n);
     }
 }
 
 // Stores a staged output block (rows [i0, i0 + rows), columns [j0, j0 + jn)) as whole rows:
-// 16 lanes x 4 fp32 columns, four rows per instruction, 16 bytes per lane at any alignment.
-template <bool TEMPORAL>
+// COLS / 4 lanes x 4 fp32 columns, 256 / COLS rows per instruction, 16 bytes per lane at any
+// alignment.
+template <bool TEMPORAL, int COLS>
 __device__ __forceinline__ void store_block_f32(float* c, const Shape& s, int64_t bidx, int i0, int rows,
                                             int j0, int jn, int lane, const float* lc) {
-    const int col = (lane & 15) * 4;
-    const int rq = lane >> 4;
-    // one 64-bit base per lane, advanced by 4 output rows per instruction
+    constexpr int kRowsAtOnce = 256 / COLS;
+    constexpr int kLdc = COLS + 4;
+    const int col = (lane % (COLS / 4)) * 4;
+    const int rq = lane / (COLS / 4);
+    // one 64-bit base per lane, advanced by the rows of an instruction
     const int64_t off0 = bidx * s.c_batch + static_cast<int64_t>(i0 + rq) * s.n + j0 + col;
-    const int64_t step = 4 * static_cast<int64_t>(s.n);
+    const int64_t step = kRowsAtOnce * static_cast<int64_t>(s.n);
     const bool col_ok = col < jn;
     const bool whole = col + 3 < jn;
 #pragma unroll
-    for (int r0 = 0; r0 < kTileM; r0 += 4) {
+    for (int r0 = 0; r0 < kTileM; r0 += kRowsAtOnce) {
         const int r = r0 + rq;
         if (r < rows && col_ok) {
             const f32x4 v = *reinterpret_cast<const f32x4*>(lc + r * kLdc + col);
-            float* cp = c + off0 + (r0 / 4) * step;
+            float* cp = c + off0 + (r0 / kRowsAtOnce) * step;
             if (whole) {
                 if constexpr (TEMPORAL)
                     *reinterpret_cast<f32x4_any*>(cp) = v;
@@ -364,46 +391,55 @@ __device__ __forceinline__ float half_pair(float v, int lane, F op) {
 // columns; the two lanes of a row exchange their maxima per block and add their sums at the
 // end).  The second pass recomputes the products and writes 2^(y - M) / sum.  Recomputing costs
 // matrix-core time, which these products have to spare; storing S would cost its bytes twice.
-template <int LAYOUT, bool BF16OUT, bool VEC, bool AREG, bool TEMPORAL, bool SOFTMAX = false>
+template <int LAYOUT, bool BF16OUT, bool VEC, int FORM, bool TEMPORAL, bool SOFTMAX = false>
 __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b, void* c,
                                            const Shape& s, int64_t bidx, int i0, int rows,
                                            int wave, int lane, uint16_t* lw, uint16_t* lbs,
                                            int done_rows, int round_rows_n, int total_rows) {
+    using G = Geo<LAYOUT, FORM>;
+    constexpr bool AREG = G::kAReg;
     const int li = lane & 31;
     const int h = lane >> 5;
     uint16_t* const la = lw;
     const int64_t a_row = rows > 0 ? bidx * s.a_batch + static_cast<int64_t>(i0) * s.k : 0;
     const int64_t b_row = bidx * s.b_batch;
-    const int nk = (s.k + kChunkK - 1) / kChunkK;  // k > 0 here
-    const int nj = (s.n + kBlockN - 1) / kBlockN;
+    const int nk = AREG ? 1 : (s.k + kChunkK - 1) / kChunkK;  // k > 0 here
+    const int nj = (s.n + G::kN - 1) / G::kN;
     const int nsteps = nk * nj;
     const int nall = (SOFTMAX ? 2 : 1) * nsteps;  // both passes' steps, in one stream
     // Accumulators are zero at every column block's start: set here and again after each
     // block's output (AREG, one step per block: the block's first MFMA takes a zero addend
     // instead), not selected at every step.
-    f32x16 acc[kBlockTiles];
+    f32x16 acc[G::kTiles];
 #pragma unroll
-    for (int t = 0; t < kBlockTiles; ++t) acc[t] = f32x16{};
-    Pieces<!AREG> p[kDepth];
-    u16x8 a_reg[AREG ? kChunkK / kTileK : 1];
+    for (int t = 0; t < G::kTiles; ++t) acc[t] = f32x16{};
+    Pieces<G> p[kDepth];
+    u16x8 a_reg[AREG ? G::kStepK / kTileK : 1];
     if constexpr (AREG) {  // A once, through the wave's LDS into its MFMA layout
-        u16x8 pa[kAPieces];
-        load_a<VEC>(a, a_row, s, rows, 0, lane, !TEMPORAL, pa);  // read once
-        write_a<VEC>(pa, a_row, s, rows, 0, lane, la);
-        wave_lds_sync();
+        constexpr int kSlices = G::kStepK / kChunkK;
+        u16x8 pa[kSlices][kAPieces];
 #pragma unroll
-        for (int q = 0; q < kChunkK / kTileK; ++q)
-            a_reg[q] = *reinterpret_cast<const u16x8*>(la + li * kLdk + q * kTileK + 8 * h);
-        wave_lds_sync();
+        for (int sl = 0; sl < kSlices; ++sl)
+            load_a<VEC>(a, a_row, s, rows, sl * kChunkK, lane, !TEMPORAL, pa[sl]);  // read once
+#pragma unroll
+        for (int sl = 0; sl < kSlices; ++sl) {
+            write_a<VEC>(pa[sl], a_row, s, rows, sl * kChunkK, lane, la);
+            wave_lds_sync();
+#pragma unroll
+            for (int q = 0; q < kChunkK / kTileK; ++q)
+                a_reg[sl * (kChunkK / kTileK) + q] =
+                    *reinterpret_cast<const u16x8*>(la + li * kLdk + q * kTileK + 8 * h);
+            wave_lds_sync();
+        }
     }
     // The steps' (column block, reduction slice) pairs are counted up as the steps go, not
     // divided out of the step index: on this path every scalar instruction counts, twelve
     // waves per CU share the scalar unit.  The load stream runs kDepth steps ahead and stays
     // on the last step once it gets there (its loads are then issued again, unused).
     int ld_st = 0, ld_j = 0, ld_k = 0;
-    auto load = [&](Pieces<!AREG>& pp) {
-        load_step<LAYOUT, VEC, !AREG>(a, a_row, b, b_row, s, rows, ld_j * kBlockN, ld_k * kChunkK, wave, lane,
-                                      !TEMPORAL && nj == 1, pp);  // A read once when one column block
+    auto load = [&](Pieces<G>& pp) {
+        load_step<LAYOUT, VEC, G>(a, a_row, b, b_row, s, rows, ld_j * G::kN, ld_k * kChunkK, wave, lane,
+                                  !TEMPORAL && nj == 1, pp);  // A read once when one column block
         if (ld_st + 1 < nall) {
             ++ld_st;
             if (++ld_k == nk) {
@@ -439,7 +475,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
     // block's end, its output.
     // PASS (a compile-time tag): 0 without SOFTMAX, else 1 (row statistics) or 2 (output), so
     // that each pass's step is compiled on its own.
-    auto step = [&](auto pass, int st, Pieces<!AREG>& pp, uint16_t* lb) {
+    auto step = [&](auto pass, int st, Pieces<G>& pp, uint16_t* lb) {
         constexpr int PASS = decltype(pass)::value;
         if constexpr (!AREG)
             set_prio(3 - (st >= prio_step[0]) - (st >= prio_step[1]) - (st >= prio_step[2]));
@@ -448,28 +484,28 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
             cur_k = 0;
             if (++cur_j == nj) cur_j = 0;
         }
-        const int j0 = jb * kBlockN;
+        const int j0 = jb * G::kN;
         // lb (buffer st % 2) was last read at step st - 2; every wave finished that step
         // before the barrier of step st - 1, so one barrier per step orders both uses.
-        write_step<LAYOUT, VEC, !AREG>(pp, a_row, b_row, s, rows, j0, kb * kChunkK, wave, lane, la, lb);
+        write_step<LAYOUT, VEC, G>(pp, a_row, b_row, s, rows, j0, kb * kChunkK, wave, lane, la, lb);
         __syncthreads();
         // issued on every step (past the last step: the last step's operands again, cache
         // hits, unused), so that every path has the same loads in flight
         load(pp);
         if (rows > 0) {  // wave-uniform
 #pragma unroll
-            for (int kk = 0; kk < kChunkK; kk += kTileK) {
+            for (int kk = 0; kk < G::kStepK; kk += kTileK) {
                 const bf16x8 av = __builtin_bit_cast(
                     bf16x8, AREG ? a_reg[AREG ? kk / kTileK : 0]
                                  : *reinterpret_cast<const u16x8*>(la + li * kLdk + kk + 8 * h));
 #pragma unroll
-                for (int t = 0; t < kBlockTiles; ++t) {  // a tile past n multiplies zeros
+                for (int t = 0; t < G::kTiles; ++t) {  // a tile past n multiplies zeros
                     bf16x8 bv;
                     if constexpr (LAYOUT == kNT)
                         bv = __builtin_bit_cast(
-                            bf16x8, *reinterpret_cast<const u16x8*>(lb + (t * kTileN + li) * kLdk + kk + 8 * h));
+                            bf16x8, *reinterpret_cast<const u16x8*>(lb + (t * kTileN + li) * G::kLdb + kk + 8 * h));
                     else
-                        bv = nn_row_operand(lb, t, kk, lane);
+                        bv = nn_row_operand<G::kLdb>(lb, t, kk, lane);
                     acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
                         bv, av, (AREG && kk == 0) ? f32x16{} : acc[t], 0, 0, 0);
                 }
@@ -479,7 +515,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
         if (kb + 1 < nk || rows == 0) return;
         // column block done: tile t, lane (li, h) holds output row li, columns
         // j0 + 32 t + 8 g + 4 h + 0..3
-        const int jn = s.n - j0 < kBlockN ? s.n - j0 : kBlockN;
+        const int jn = s.n - j0 < G::kN ? s.n - j0 : G::kN;
         float scale = s.alpha;
         if constexpr (SOFTMAX) {
             // Logits in base-2 units, y = acc * c with c = alpha log2 e, never formed on their
@@ -487,6 +523,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
             // 2^(y - M) takes one fma and one v_exp_f32.  Columns past n (a partial last block)
             // count as -inf.
             const float c2 = s.alpha * kLog2eF;
+            static_assert(G::kTiles == kBlockTiles, "two tiles per softmax block");
             const bool full = jn == kBlockN;  // wave-uniform: only a partial last block masks
             auto col_ok = [&](int t, int i) { return t * kTileN + 8 * (i / 4) + 4 * h + (i % 4) < jn; };
             if constexpr (PASS == 1) {  // first pass: fold this block into the row's maximum and sum
@@ -510,8 +547,10 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
                 float bm = c2 >= 0.0f
                                ? extreme([](float u, float v) { return __builtin_elementwise_maximum(u, v); }, kNegInfF)
                                : extreme([](float u, float v) { return __builtin_elementwise_minimum(u, v); }, -kNegInfF);
-                bm = c2 == 0.0f ? 0.0f : c2 * bm;  // the block's largest y (alpha = 0: all y are 0)
-                bm = half_pair(bm, lane, [](float u, float v) { return __builtin_elementwise_maximum(u, v); });
+                // the largest y of the lane's half of the block (alpha = 0: all y are 0); the two
+                // lanes of a row keep statistics of their own columns and meet once, at the end
+                // of the row, so that no step waits for an exchange between lanes
+                bm = c2 == 0.0f ? 0.0f : c2 * bm;
                 const float mx = __builtin_elementwise_maximum(sm_max, bm);
                 const float ms = mx == kNegInfF ? 0.0f : mx;
 #pragma unroll
@@ -532,12 +571,14 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
                     for (int w = 8; w >= 1; w /= 2)
 #pragma unroll
                         for (int i = 0; i < w; ++i) acc[t][i] = acc[t][2 * i] + acc[t][2 * i + 1];
-                static_assert(kBlockTiles == 2, "two tiles per block");
                 const float bs = acc[0][0] + acc[1][0];
                 sm_sum = sm_sum * __builtin_amdgcn_exp2f(sm_max - ms) + bs;
                 sm_max = mx;
-                if (jb + 1 == nj) {  // the row's last block: both lanes' sums, and 1 / sum
-                    const float tot = half_pair(sm_sum, lane, [](float u, float v) { return u + v; });
+                if (jb + 1 == nj) {  // the row's last block: both lanes' maxima and sums, and 1 / sum
+                    const float all = half_pair(sm_max, lane, [](float u, float v) { return __builtin_elementwise_maximum(u, v); });
+                    const float mine = sm_max == kNegInfF ? 0.0f : sm_sum * __builtin_amdgcn_exp2f(sm_max - all);
+                    const float tot = half_pair(mine, lane, [](float u, float v) { return u + v; });
+                    sm_max = all;
                     sm_inv = tot == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(tot);
                 }
                 if constexpr (!AREG) {
@@ -558,32 +599,46 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
         if constexpr (BF16OUT) {  // rounded to bf16 (nearest even) on the way into LDS
             uint16_t* const lh = lw;
 #pragma unroll
-            for (int t = 0; t < kBlockTiles; ++t) {
+            for (int t0 = 0; t0 < G::kTiles; t0 += kBlockTiles) {
+                if (t0 > 0 && t0 * kTileN >= jn) break;  // wave-uniform
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    *reinterpret_cast<u32x2*>(lh + li * kLdh + t * kTileN + 8 * g + 4 * h) =
-                        u32x2{pack_bf16(scale * acc[t][4 * g], scale * acc[t][4 * g + 1]),
-                              pack_bf16(scale * acc[t][4 * g + 2], scale * acc[t][4 * g + 3])};
+                for (int t = 0; t < kBlockTiles; ++t) {
+                    const f32x16& v = acc[t0 + t];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        *reinterpret_cast<u32x2*>(lh + li * kLdh + t * kTileN + 8 * g + 4 * h) =
+                            u32x2{pack_bf16(scale * v[4 * g], scale * v[4 * g + 1]),
+                                  pack_bf16(scale * v[4 * g + 2], scale * v[4 * g + 3])};
+                }
+                wave_lds_sync();
+                store_block_bf16<TEMPORAL>(static_cast<uint16_t*>(c), s, bidx, i0, rows, j0 + t0 * kTileN,
+                                           jn - t0 * kTileN, lane, lh);
+                wave_lds_sync();  // the next part, or the next step, rewrites the region
             }
-            wave_lds_sync();
-            store_block_bf16<TEMPORAL>(static_cast<uint16_t*>(c), s, bidx, i0, rows, j0, jn, lane, lh);
         } else {
             float* const lc = reinterpret_cast<float*>(lw);
+            constexpr int kAtOnce = G::kStageF / kTileN;
 #pragma unroll
-            for (int t = 0; t < kBlockTiles; ++t) {
+            for (int t0 = 0; t0 < G::kTiles; t0 += kAtOnce) {
+                if (t0 > 0 && t0 * kTileN >= jn) break;  // wave-uniform
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    *reinterpret_cast<f32x4*>(lc + li * kLdc + t * kTileN + 8 * g + 4 * h) =
-                        f32x4{scale * acc[t][4 * g], scale * acc[t][4 * g + 1],
-                              scale * acc[t][4 * g + 2], scale * acc[t][4 * g + 3]};
+                for (int t = 0; t < kAtOnce; ++t) {
+                    const f32x16& v = acc[t0 + t];
+#pragma unroll
+                    for (int g = 0; g < 4; ++g)
+                        *reinterpret_cast<f32x4*>(lc + li * G::kLdc + t * kTileN + 8 * g + 4 * h) =
+                            f32x4{scale * v[4 * g], scale * v[4 * g + 1], scale * v[4 * g + 2],
+                                  scale * v[4 * g + 3]};
+                }
+                wave_lds_sync();
+                store_block_f32<TEMPORAL, G::kStageF>(static_cast<float*>(c), s, bidx, i0, rows, j0 + t0 * kTileN,
+                                                      jn - t0 * kTileN, lane, lc);
+                wave_lds_sync();
             }
-            wave_lds_sync();
-            store_block_f32<TEMPORAL>(static_cast<float*>(c), s, bidx, i0, rows, j0, jn, lane, lc);
         }
-        wave_lds_sync();  // the next step rewrites the region
         if constexpr (!AREG) {
 #pragma unroll
-            for (int t = 0; t < kBlockTiles; ++t) acc[t] = f32x16{};
+            for (int t = 0; t < G::kTiles; ++t) acc[t] = f32x16{};
         }
     };
     // Two steps per iteration and the odd one after the loop, so that every path around the
@@ -603,15 +658,15 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
         if (!odd_start) {
             for (; st + 1 < end; st += 2) {
                 step(pass, st, p[0], lbs);
-                step(pass, st + 1, p[1], lbs + kBBufElems);
+                step(pass, st + 1, p[1], lbs + G::kBBuf);
             }
             if (st < end) step(pass, st++, p[0], lbs);
         } else {
             for (; st + 1 < end; st += 2) {
-                step(pass, st, p[1], lbs + kBBufElems);
+                step(pass, st, p[1], lbs + G::kBBuf);
                 step(pass, st + 1, p[0], lbs);
             }
-            if (st < end) step(pass, st++, p[1], lbs + kBBufElems);
+            if (st < end) step(pass, st++, p[1], lbs + G::kBBuf);
         }
     };
     if constexpr (!SOFTMAX) {
@@ -658,7 +713,8 @@ constexpr int kS1WavesPerSimd = 2;
 // kLdA) and each 128-column step takes two 64-deep chunks of B through the shared buffers.
 constexpr int kLdA = 2 * kChunkK + 8;
 constexpr int s1_wave_bytes(bool bf16_out, bool deep) {
-    return deep && kTileM * kLdA * 2 > wave_lds_bytes(bf16_out) ? kTileM * kLdA * 2 : wave_lds_bytes(bf16_out);
+    const int base = wave_bytes<kNT, kFormA1>(bf16_out);
+    return deep && kTileM * kLdA * 2 > base ? kTileM * kLdA * 2 : base;
 }
 constexpr int s1_lds_bytes(bool bf16_out, bool deep = false) {
     return kWaves * s1_wave_bytes(bf16_out, deep) + kDepth * kS1BBufElems * 2 + 2 * kWaves * kTileM * 4;
@@ -712,16 +768,17 @@ __device__ __forceinline__ void s1_store_block(const f32x16 (&v)[kBlockTiles], f
         wave_lds_sync();
         store_block_bf16<TEMPORAL>(static_cast<uint16_t*>(c), s, bidx, i0, rows, j0, jn, lane, lw);
     } else {
+        using G = Geo<kNT, kFormA1>;
         float* const lc = reinterpret_cast<float*>(lw);
 #pragma unroll
         for (int t = 0; t < kBlockTiles; ++t)
 #pragma unroll
             for (int g = 0; g < 4; ++g)
-                *reinterpret_cast<f32x4*>(lc + li * kLdc + t * kTileN + 8 * g + 4 * h) =
+                *reinterpret_cast<f32x4*>(lc + li * G::kLdc + t * kTileN + 8 * g + 4 * h) =
                     f32x4{scale * v[t][4 * g], scale * v[t][4 * g + 1], scale * v[t][4 * g + 2],
                           scale * v[t][4 * g + 3]};
         wave_lds_sync();
-        store_block_f32<TEMPORAL>(static_cast<float*>(c), s, bidx, i0, rows, j0, jn, lane, lc);
+        store_block_f32<TEMPORAL, G::kStageF>(static_cast<float*>(c), s, bidx, i0, rows, j0, jn, lane, lc);
     }
     wave_lds_sync();  // the next block rewrites the region
 }
@@ -919,7 +976,7 @@ constexpr int kWavesPerSimd = 3;
 // Worker loop: workgroup w runs its items; an item's rows are taken up to 128 at a time (cut
 // where a batch ends), 32 per wave (single-pass softmax: 64 at a time, 32 per wave pair).  Every bound of these loops is the same for the four
 // waves, so they meet the same barriers.
-template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, bool AREG>
+template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, int FORM>
 __device__ __forceinline__ void gemm_worker(const uint16_t* a, const uint16_t* b, void* c,
                                             const Shape& s, const int32_t* __restrict__ worker_ptr,
                                             const bsm_item* __restrict__ items,
@@ -928,15 +985,14 @@ __device__ __forceinline__ void gemm_worker(const uint16_t* a, const uint16_t* b
     constexpr bool kSoftmax = MODE == kModeNtSoftmax;
     constexpr bool kS1 = MODE == kModeNtSoftmax1;
     static_assert(!kS1 || VEC, "the single-pass form is a 16-byte instance");
-    // The single-pass instances take their last template flag as the deep form (64 < k <= 128,
-    // A kept in LDS), not as A in registers, which their k <= 64 form always does.
-    constexpr bool kDeep = kS1 && AREG;
+    // single-pass instances: kFormA2 is the deep form (64 < k <= 128, A kept in LDS)
+    constexpr bool kDeep = kS1 && FORM == kFormA2;
     constexpr int kRoundRows = kS1 ? kS1Rows : kWaves * kTileM;
     const int w = blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int lane = static_cast<int>(threadIdx.x) & 63;
     const uint64_t t0 = trace ? __builtin_amdgcn_s_memrealtime() : 0;
-    constexpr int kWaveBytes = kS1 ? s1_wave_bytes(BF16OUT, kDeep) : wave_lds_bytes(BF16OUT);
+    constexpr int kWaveBytes = kS1 ? s1_wave_bytes(BF16OUT, kDeep) : wave_bytes<kLayout, FORM>(BF16OUT);
     uint16_t* const lw = lds_base + wave * (kWaveBytes / 2);
     uint16_t* const lbs = lds_base + kWaves * (kWaveBytes / 2);
     float* const lstat = reinterpret_cast<float*>(lbs + kDepth * kS1BBufElems);  // kS1 only
@@ -970,7 +1026,7 @@ __device__ __forceinline__ void gemm_worker(const uint16_t* a, const uint16_t* b
                     if (s.k == 0)
                         zero_rows<BF16OUT, kSoftmax>(c, s, bidx, i + row0, mine, lane);
                     else
-                        round_rows<kLayout, BF16OUT, VEC, AREG, TEMPORAL, kSoftmax>(
+                        round_rows<kLayout, BF16OUT, VEC, FORM, TEMPORAL, kSoftmax>(
                             a, b, c, s, bidx, i + row0, mine, wave, lane, lw, lbs, wg_done, seg, total_rows);
                 }
                 wg_done += seg;
@@ -993,27 +1049,40 @@ __device__ __forceinline__ void gemm_worker(const uint16_t* a, const uint16_t* b
     }
 }
 
-extern __shared__ uint16_t bsm_gemm_lds[];  // wg_lds_bytes() per workgroup
+extern __shared__ uint16_t bsm_gemm_lds[];  // the form's LDS bytes per workgroup
 
 constexpr int kGemmThreads = 64 * kWaves;
 
-// Compiled for two waves per SIMD: the single-pass softmax, whose held products take 128
-// registers, and the two-pass softmax with A staged through LDS (k > 64): capped at three waves
-// it spilled 149 registers and took 157 us at 192 x 512 x 512 x 128, against 83 us at two.
 // TEMPORAL: ordinary stores of C and loads of A (a consumer finds C in the Infinity Cache)
 // instead of nontemporal ones; a compile-time choice, so the default instance carries no
-// branch for it.  AREG (A's operands held in registers, k <= 64 < n, 16-byte form only): a
-// separate instance too, so that neither form's registers are allocated for the other's.
-constexpr bool use_areg(bool vec, int n, int k) { return vec && k <= kChunkK && n > kBlockN; }
-template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, bool AREG>
-__global__ void __launch_bounds__(kGemmThreads,
-                                  (MODE == kModeNtSoftmax1 || (MODE == kModeNtSoftmax && !AREG))
-                                      ? kS1WavesPerSimd : kWavesPerSimd)
+// branch for it.
+//
+// The form of a launch.  A in registers takes aligned whole pieces (VEC) and pays from the
+// second column block on; forms with a 128-wide B block need `wide`, that the plan's workgroups
+// per CU leave room for their LDS.
+constexpr int form_of(int mode, bool vec, bool wide, int n, int k) {
+    if (vec && n > kBlockN && k <= kChunkK) return kFormA1;
+    if (wide && mode == kModeNn && n > kBlockN) return kFormWide;
+    if (wide && mode != kModeNn && vec && n > kBlockN && k <= 2 * kChunkK) return kFormA2;
+    return kFormStep;
+}
+
+// Compiled for two waves per SIMD: the single-pass softmax, whose held products take 128
+// registers, and the two-pass softmax with A staged through LDS: capped at three waves it
+// spilled 149 registers and took 157 us at 192 x 512 x 512 x 128, against 83 us at two.  The
+// forms with a 128-wide B block too (three waves spill 88 and 45 registers), except the plain
+// product with A in registers, which fits.  Plans of these default to two workgroups per CU:
+// three, one of them waiting, take 191 against 147 us and 116 against 76 us at the shapes above.
+constexpr int waves_per_simd(int mode, int form) {
+    return mode == kModeNtSoftmax1 || (mode == kModeNtSoftmax && form != kFormA1) || form == kFormWide
+               ? kS1WavesPerSimd : kWavesPerSimd;
+}
+template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, int FORM>
+__global__ void __launch_bounds__(kGemmThreads, waves_per_simd(MODE, FORM))
 bsm_gemm_kernel(const uint16_t* a, const uint16_t* b, void* c, Shape s,
                 const int32_t* __restrict__ worker_ptr, const bsm_item* __restrict__ items,
                 bsm_trace_rec* __restrict__ trace) {
-    static_assert(VEC || !AREG, "registers hold A in the 16-byte form only");
-    gemm_worker<MODE, BF16OUT, VEC, TEMPORAL, AREG>(a, b, c, s, worker_ptr, items, trace, bsm_gemm_lds);
+    gemm_worker<MODE, BF16OUT, VEC, TEMPORAL, FORM>(a, b, c, s, worker_ptr, items, trace, bsm_gemm_lds);
 }
 
 }  // namespace bsm_mm

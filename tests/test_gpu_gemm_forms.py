@@ -1,0 +1,67 @@
+"""GPU parity of the matrix products' forms at the edges of their dispatch, against the fp64
+oracle and, bit for bit, between launches that cut the rows differently: operands whose rows are
+not whole 16-byte pieces (any element boundary, the operand's last piece, operands shorter than
+one piece), A held in registers for 64 < k <= 128, and NN in 128-column blocks."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2002_07062_amd as bsm
+from gpu_util import bits_to_f64, to_host_bits
+from test_gpu_gemm import _check as check_product
+from test_gpu_gemm import _dev_bf16, _operands
+from test_gpu_gemm_softmax import _check as check_softmax
+
+pytestmark = pytest.mark.gpu
+
+
+def _product(shape, layout, out, a_d, b_d, alpha, topology=None, schedule="balanced", pad=5):
+    batch, m, n, k = shape
+    c = torch.full((batch * m * n + pad,), float("nan"), device="cuda",
+                   dtype=torch.float32 if out == "f32" else torch.bfloat16)
+    p = bsm.bsm_gemm_plan_create(batch, m, n, k, layout, out, schedule, topology=topology, device=0)
+    bsm.bsm_gemm_execute(p, a_d, b_d, c, alpha)
+    torch.cuda.synchronize()
+    p.destroy()
+    bits = to_host_bits(c)
+    assert np.all(np.isnan(bits_to_f64(bits[batch * m * n:]))), "written past C"
+    return bits[: batch * m * n]
+
+
+# n and k just inside and outside each form (blocks of 64 and 128 columns, reductions of 64 and
+# 128), odd lengths whose rows start at every element boundary, and operands of 1..9 elements
+SHAPES = [(2, 130, 65, 72), (1, 33, 129, 128), (3, 31, 200, 120), (2, 129, 64, 136), (2, 64, 66, 65),
+          (3, 37, 96, 333), (1, 128, 128, 200), (2, 50, 130, 64), (1, 70, 81, 77), (1, 1, 7, 1),
+          (1, 1, 1, 9), (1, 3, 3, 3), (3, 5, 511, 127)]
+
+
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+@pytest.mark.parametrize("layout", ["nt", "nn", "nt_softmax"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_forms_against_the_oracle_and_each_other(shape, layout, out):
+    batch, m, n, k = shape
+    print(f"[forms {layout} {shape} {out}]", flush=True)
+    a, b = _operands(batch, m, n, k, seed=300 + m + n)
+    a_d, b_d = _dev_bf16(a), _dev_bf16(b)
+    alpha = 1.0 / np.sqrt(k)
+    got = _product(shape, layout, out, a_d, b_d, alpha)
+    if layout == "nt_softmax":
+        check_softmax(got, a, b, batch, m, n, k, alpha, out)
+    else:
+        check_product(got, a, b, batch, m, n, k, layout, out, alpha)
+    assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha, schedule="rr"), got)
+    if layout != "nt_softmax" and out == "bf16":
+        # four workgroups per CU leave no room for the 128-wide forms: the same bits without them
+        assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha, topology={"wg_per_cu": 4}), got)
+
+
+@pytest.mark.parametrize("n,k", [(520, 128), (700, 72), (513, 64)])
+def test_two_pass_softmax_forms_past_512_columns(n, k):
+    batch, m = 2, 70
+    a, b = _operands(batch, m, n, k, seed=400 + n)
+    a_d, b_d = _dev_bf16(a), _dev_bf16(b)
+    for alpha in (0.125, -0.125):
+        got = _product((batch, m, n, k), "nt_softmax", "f32", a_d, b_d, alpha)
+        check_softmax(got, a, b, batch, m, n, k, alpha, "f32")
+        assert np.array_equal(_product((batch, m, n, k), "nt_softmax", "f32", a_d, b_d, alpha, schedule="xcd"), got)
