@@ -155,9 +155,8 @@ typedef struct bsm_plan_stats {
     int32_t n_overlap;         /* XCD: slices straddling two or more virtual banks */
     int32_t max_cols;          /* longest row */
     int32_t kernel_class;      /* which kernel instance the plan launches (internal) */
-    int32_t lds_bytes_per_wave; /* LDS each wave may stage a row in (rows beyond the register
-                                   tile whose start or length is not 16-byte aligned, and
-                                   backward rows of 257..512 16-byte vectors; 0: none) */
+    int32_t lds_bytes_per_wave; /* LDS each wave may stage a row in; 0: none (rows are held in
+                                   registers, or read twice) */
     int32_t flags;             /* the BSM_FLAG_* bits the plan runs with */
     double max_worker_cost;    /* planner cost of the most loaded worker */
     double mean_worker_cost;   /* total planner cost / n_workers */
@@ -205,10 +204,7 @@ typedef struct bsm_plan_s* bsm_plan;
  *                  and slice s starts at element s*R*C.  Otherwise [batch] element offsets:
  *                  slice s occupies elements [slice_offsets[s], slice_offsets[s] + R_s*C_s).
  *                  Slices may sit in any order with gaps between them, but must not overlap;
- *                  gaps are never written.  A row that starts or ends inside a 16-byte
- *                  vector (buffers 16-byte aligned) is read as the aligned vectors that
- *                  cover it: up to 15 bytes before and after it are read and ignored (a
- *                  16-byte vector never crosses a page, so this cannot fault).
+ *                  gaps are never read or written, and rows may start and end anywhere.
  *   rows, cols     [batch] (or [1] when uniform), each >= 0; an empty slice is skipped
  *   schedule       see bsm_schedule
  *   stream         hipStream_t as void*

@@ -40,7 +40,6 @@ struct bsm_plan_s {
     bool gemm_single = false;  // layout 2 in one pass (products held in registers)
     bool gemm_wide = false;    // the CU's LDS holds its workgroups' 128-wide B blocks
     int64_t gemm_batch = 0;
-    int lds_floats_per_wave = 0;  // one-wave long-row staging (kernel classes 4, 5 on a device)
     int32_t flags = 0;            // BSM_FLAG_* bits
     void* d_table = nullptr;  // device copy: worker_ptr, then items (256-byte aligned)
     const int32_t* d_worker_ptr = nullptr;
@@ -105,21 +104,6 @@ int default_waves_per_cu(bsm_dtype d, int kclass) {
     return d == BSM_BF16 ? 16 : 8;
 }
 
-// Smallest LDS region worth staging a row in (shorter rows never reach the long-row path).
-constexpr int64_t kMinStageBytes = 8192;
-
-// LDS per wave for long-row staging: the CU's LDS split over its resident workgroups, capped
-// by the per-workgroup limit, less the kernels' own static LDS (`static_bytes` per workgroup),
-// split over the waves and rounded down to 64 bytes.
-int64_t lds_bytes_per_wave(const hipDeviceProp_t& prop, const bsm::Topology& t,
-                           int64_t static_bytes) {
-    const int64_t per_cu = static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor);
-    const int64_t per_wg = std::min<int64_t>(per_cu / std::max(1, t.wg_per_cu),
-                                             static_cast<int64_t>(prop.sharedMemPerBlock)) -
-                           static_bytes;
-    const int64_t per_wave = (per_wg / t.waves_per_wg()) & ~static_cast<int64_t>(63);
-    return per_wave >= kMinStageBytes ? per_wave : 0;
-}
 constexpr int kDefaultPieceBytes = 8192;
 constexpr float kDefaultItemCost = 1024.0f;
 constexpr float kDefaultRowCost = 64.0f;
@@ -197,21 +181,8 @@ bsm_status resolve_topology(const bsm_topology* user, int device, bsm_dtype dtyp
             int n = 0;
             DeviceGuard g;
             hipError_t e = g.enter(device);
-            hipDeviceProp_t prop;
-            if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
-            size_t lds = 0;
-            if (e == hipSuccess && kclass >= kLongRowClass) {
-                bsm::Topology probe;
-                probe.wg_per_cu = want;
-                probe.wg_threads = t.wg_threads;
-                int static_bytes = 0;
-                e = bsm::static_lds_bytes(dtype, kclass, shifted, &static_bytes);
-                if (e == hipSuccess)
-                    lds = static_cast<size_t>(lds_bytes_per_wave(prop, probe, static_bytes)) *
-                          (t.wg_threads / 64);
-            }
             if (e == hipSuccess)
-                e = bsm::resident_wgs_per_cu(dtype, kclass, shifted, t.wg_threads, lds, &n);
+                e = bsm::resident_wgs_per_cu(dtype, kclass, shifted, t.wg_threads, &n);
             if (e != hipSuccess) return hip_fail(e, "occupancy query");
             t.wg_per_cu = std::max(1, std::min(want, n));
         }
@@ -316,7 +287,7 @@ bsm_status create_plan(bsm_plan* out_plan, const int64_t* offs, const int32_t* r
         std::string err = bsm::make_geometry(offs, rows, cols, batch, elem_bytes_of(dtype), &p->geo);
         if (!err.empty()) return fail(BSM_ERR_INVALID_ARG, "geometry: %s", err.c_str());
         p->shifted = any_shifted(p->geo);
-        p->kernel_class = bsm::kernel_class_for(p->geo.max_cols, elem_bytes_of(dtype), p->shifted);
+        p->kernel_class = bsm::kernel_class_for(p->geo.max_cols, elem_bytes_of(dtype));
         // Rows beyond the register tile are worked by whole workgroups (team_threads of the
         // class), one row at a time: such plans run that workgroup size whatever the topology
         // asks (a row's bits depend on it), and every worker of their table is a workgroup.
@@ -370,17 +341,6 @@ bsm_status create_plan(bsm_plan* out_plan, const int64_t* offs, const int32_t* r
         DeviceGuard g;
         hipError_t e = g.enter(device);
         if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
-        if (p->kernel_class >= kLongRowClass) {
-            hipDeviceProp_t prop;
-            e = hipGetDeviceProperties(&prop, device);
-            if (e != hipSuccess) return hip_fail(e, "hipGetDeviceProperties");
-            int static_bytes = 0;
-            e = bsm::static_lds_bytes(dtype, p->kernel_class, p->shifted, &static_bytes);
-            if (e != hipSuccess) return hip_fail(e, "hipFuncGetAttributes");
-            const int64_t b = lds_bytes_per_wave(prop, p->topo, static_bytes);
-            p->lds_floats_per_wave = static_cast<int>(b / static_cast<int64_t>(sizeof(float)));
-            p->table.stats.lds_bytes_per_wave = static_cast<int32_t>(b);
-        }
         if (!upload) {
             *out_plan = p.release();
             return BSM_OK;
@@ -445,11 +405,11 @@ bsm_status execute_plan(bsm_plan p, bool backward, const void* a, const void* b,
         e = bsm::launch_softmax_backward(p->dtype, p->kernel_class, p->shifted, temporal, a, b, out,
                                          p->d_worker_ptr, p->d_items, p->topo.n_wg(),
                                          p->topo.wg_threads, p->table.per_wave ? 1 : 0,
-                                         p->lds_floats_per_wave, trace, s);
+                                         trace, s);
     else
         e = bsm::launch_softmax(p->dtype, p->kernel_class, p->shifted, temporal, a, out, p->d_worker_ptr,
                                 p->d_items, p->topo.n_wg(), p->topo.wg_threads,
-                                p->table.per_wave ? 1 : 0, p->lds_floats_per_wave, trace, s);
+                                p->table.per_wave ? 1 : 0, trace, s);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");
     p->used = true;
     return BSM_OK;

@@ -21,9 +21,9 @@
 // wave covers 64/G rows at a time, with four 16-byte loads per lane in flight.  Rows longer
 // than the largest register tile (512 vectors) are held in the registers of a whole workgroup
 // (up to 32 values per lane in kernel class 4, 64 in classes 5 and 6, whose workgroups have 256
-// and 512 threads) and read once, or, longer still, read twice with an online max/sum.  Rows whose start or length is not 16-byte aligned use
-// element loads with the same lane layout, or one wave per row (staged in the wave's LDS
-// region, else two passes).  This is bandwidth-bound work: no MFMA.
+// and 512 threads) and read once, or, longer still, read twice with an online max/sum.  Rows whose
+// start or length is not 16-byte aligned take the same paths with 16-byte accesses at element
+// boundaries.  This is bandwidth-bound work: no MFMA.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -44,6 +44,9 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+// 16-byte accesses at element boundaries (the same instructions as the aligned ones)
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x4 u32x4_any __attribute__((aligned(2)));
 
 constexpr float kLog2e = 1.44269504088896340736f;
 constexpr float kNegInf = -__builtin_huge_valf();
@@ -143,11 +146,19 @@ struct F32 {
     static constexpr int kEPV = 4;  // elements per 16-byte vector
     using R = f32x4;  // one 16-byte vector as loaded
     __device__ __forceinline__ static R load_raw(const T* p) { return load16<NT>(reinterpret_cast<const R*>(p)); }
+    __device__ __forceinline__ static R load_any(const T* p) {
+        if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(p));
+        return *reinterpret_cast<const f32x4_any*>(p);
+    }
+    __device__ __forceinline__ static void store_any(T* p, const float* y) {
+        const f32x4 v{y[0], y[1], y[2], y[3]};
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any*>(p));
+        else *reinterpret_cast<f32x4_any*>(p) = v;
+    }
     __device__ __forceinline__ static R raw_fill(float f) { return R{f, f, f, f}; }
     __device__ __forceinline__ static void unpack(R v, float* x) {
         x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
     }
-    __device__ __forceinline__ static void load_vec(const T* p, float* x) { unpack(load_raw(p), x); }
     __device__ __forceinline__ static void store_vec(T* p, const float* y) {
         store16<NT>(reinterpret_cast<f32x4*>(p), f32x4{y[0], y[1], y[2], y[3]});
     }
@@ -162,6 +173,15 @@ struct BF16 {
     static constexpr int kEPV = 8;
     using R = u32x4;  // one 16-byte vector as loaded: eight bf16 bit patterns
     __device__ __forceinline__ static R load_raw(const T* p) { return load16<NT>(reinterpret_cast<const R*>(p)); }
+    __device__ __forceinline__ static R load_any(const T* p) {
+        if constexpr (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any*>(p));
+        return *reinterpret_cast<const u32x4_any*>(p);
+    }
+    __device__ __forceinline__ static void store_any(T* p, const float* y) {
+        const u32x4 v{pack(y[0], y[1]), pack(y[2], y[3]), pack(y[4], y[5]), pack(y[6], y[7])};
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any*>(p));
+        else *reinterpret_cast<u32x4_any*>(p) = v;
+    }
     // f's bf16 pattern twice per dword (exact for the fills used: -inf and 0)
     __device__ __forceinline__ static R raw_fill(float f) {
         const unsigned h = f_bits(f) >> 16;
@@ -174,7 +194,6 @@ struct BF16 {
             x[2 * i + 1] = bits_f(v[i] & 0xFFFF0000u);
         }
     }
-    __device__ __forceinline__ static void load_vec(const T* p, float* x) { unpack(load_raw(p), x); }
     __device__ __forceinline__ static unsigned pack(float a, float b) {
         // round to nearest even, NaN stays NaN (v_cvt_pk_bf16_f32)
         return __builtin_bit_cast(unsigned, __builtin_convertvector(f32x2{a, b}, bf16x2));
@@ -191,62 +210,133 @@ struct BF16 {
     }
 };
 
-// Softmax of U rows per group, all loads first (U rows x V vectors in flight per lane).
-//   row r of the item starts at element base + r * cols; rows r0, r0 + step, ...
-// The 16-byte vectors of one row.  An aligned row (SHIFT false: its start and length whole
-// vectors) holds cols / EPV of them from its start.  A shifted row -- start or length not a
-// whole number of vectors, the buffers themselves 16-byte aligned -- is covered by the aligned
-// vectors from the one holding its first element: the first `ph` elements of vector 0 precede
-// the row and the last vector may run past its end.  Those outside elements are read with the
-// vector (a 16-byte vector never crosses a page, so it is mapped wherever one of its elements
-// is) and replaced by `pad`, and never written: the row's first and last vectors are stored
-// element by element, every other one as a whole.
-template <class E, bool SHIFT>
+// The 16-byte vectors of one row of `cols` elements, dealt to STRIDE lanes: lane i holds vectors
+// i, i + STRIDE, .. (slots 0, 1, ..; V of them at most, V > 1 only for rows of more than one
+// slot).  An aligned row (SHIFT false: its start and length whole vectors) holds cols / EPV
+// vectors from its start.  A shifted row (at least EPV elements, from any element boundary) has
+// nv = ceil(cols / EPV): slot 0 from its start, the other slots up to its end, that is, moved
+// back by the `sh` elements that the last vector would run past it.  Lane 0's vector of slot 1
+// then starts with `sh` elements that the last vector of slot 0 holds as well.  (One slot: only
+// the last vector moves.)  No access leaves the row, and nothing is loaded or stored element by
+// element: both lanes that hold a duplicate compute the same value from it and store the same
+// bits, and only one counts it in the row's sums (row_sum, row_dot; `mask` where a whole pass
+// leaves duplicates out).  Which slot holds them is known when the code is compiled, and the
+// slots past it lie at constant distances, so shifted rows need few registers that aligned ones
+// do not (moving the last slot instead, known only for each row, spilled up to 53 registers;
+// moving only the last vector 124).  Before, shifted rows were read as the aligned vectors around them, with
+// the outside elements masked and the first and last vectors stored element by element (GB/s,
+// 30-400 MB, before -> now): forward bf16 77 2370 -> 3900, 333 3490 -> 4140, 4105 5170 -> 5210, 8193
+// 2730 -> 4870; fp32 77 2380 -> 2750, 333 4470 -> 5440, 1001 5440 -> 5730, 4097 3820 -> 4940;
+// backward fp32 77 4430 -> 5250, 1001 5570 -> 5770, 16383 3270 -> 4740, bf16 333 4520 -> 4560.
+template <class E, bool SHIFT, int STRIDE, int V>
 struct RowVecs {
     static constexpr int EPV = E::kEPV;
-    int64_t start;  // element offset of vector 0
-    int ph;         // elements of vector 0 before the row
+    int64_t start;  // element offset of the row
     int cols;
-    int nv;         // vectors covering the row
-    __device__ __forceinline__ RowVecs(int64_t row_start, int c) : cols(c) {
-        ph = SHIFT ? static_cast<int>(row_start & (EPV - 1)) : 0;
-        start = row_start - ph;
-        nv = SHIFT ? (ph + c + EPV - 1) / EPV : c / EPV;
+    int nv;         // vectors of the row
+    __device__ __forceinline__ RowVecs(int64_t row_start, int c) : start(row_start), cols(c) {
+        nv = SHIFT ? (c + EPV - 1) / EPV : c / EPV;
     }
-    // Elements [lo, hi) of vector vi belong to the row.
-    __device__ __forceinline__ int lo(int vi) const { return ph - vi * EPV; }
-    __device__ __forceinline__ int hi(int vi) const { return cols + ph - vi * EPV; }
-    __device__ __forceinline__ void mask(int vi, float* x, float pad) const {
-        if constexpr (SHIFT) {
-            const int l = lo(vi), h = hi(vi);
-            if (l > 0 || h < EPV) {
+    __device__ __forceinline__ bool in(int i, int s) const { return i + s * STRIDE < nv; }
+    __device__ __forceinline__ int sh() const { return nv * EPV - cols; }
+    // Elements that lane i's vector of slot s holds twice.
+    __device__ __forceinline__ int dup(int i, int s) const {
+        return SHIFT && (V > 1 ? s == 1 && i == 0 : i == nv - 1) ? sh() : 0;
+    }
+    __device__ __forceinline__ int64_t at(int i, int s) const {
+        if constexpr (!SHIFT) return start + (i + s * STRIDE) * EPV;
+        if constexpr (V == 1) return start + (i * EPV < cols - EPV ? i * EPV : cols - EPV);
+        return (s > 0 ? start - sh() : start) + (i + s * STRIDE) * EPV;
+    }
+    __device__ __forceinline__ typename E::R load(const typename E::T* in, int i, int s) const {
+        if constexpr (SHIFT) return E::load_any(in + at(i, s));
+        return E::load_raw(in + at(i, s));
+    }
+    __device__ __forceinline__ void store(typename E::T* out, int i, int s, const float* y) const {
+        if constexpr (SHIFT) E::store_any(out + at(i, s), y);
+        else E::store_vec(out + at(i, s), y);
+    }
+    // Duplicates as `pad`, and a store without them, for passes that read the row again while
+    // other lanes write it (in place, a duplicate may already hold its result).
+    __device__ __forceinline__ void mask(int i, int s, float* x, float pad) const {
+        if (SHIFT && (V == 1 || s == 1)) {
+            const int d = dup(i, s);
 #pragma unroll
-                for (int e = 0; e < EPV; ++e)
-                    if (e < l || e >= h) x[e] = pad;
-            }
+            for (int e = 0; e < EPV; ++e) x[e] = e < d ? pad : x[e];
         }
     }
-    __device__ __forceinline__ void store(typename E::T* out, int vi, const float* y) const {
-        typename E::T* p = out + start + vi * EPV;
+    __device__ __forceinline__ void store_own(typename E::T* out, int i, int s, const float* y) const {
         if constexpr (SHIFT) {
-            const int l = lo(vi), h = hi(vi);
-            if (l > 0 || h < EPV) {
+            const int d = dup(i, s);
+            if (d > 0) {
 #pragma unroll
                 for (int e = 0; e < EPV; ++e)
-                    if (e >= l && e < h) E::store1(p + e, y[e]);
+                    if (e >= d) E::store1(out + at(i, s) + e, y[e]);
                 return;
             }
         }
-        E::store_vec(p, y);
+        store(out, i, s, y);
     }
 };
 
-// Vectors a row of `cols` elements may span: one more than its length in vectors when shifted.
-template <class E, bool SHIFT>
-__device__ __forceinline__ int span_vecs(int cols) {
-    return (cols + E::kEPV - 1) / E::kEPV + (SHIFT ? 1 : 0);
+// Sum of a lane's V vectors, each element of the row counted once: the tree of
+// lane_reduce<V * EPV>, a vector at a time, with the duplicates left out.
+template <class E, int V, bool SHIFT, int STRIDE>
+__device__ __forceinline__ float row_sum(const RowVecs<E, SHIFT, STRIDE, V>& rv, int i, const float* x) {
+    constexpr int EPV = E::kEPV;
+    if constexpr (!SHIFT) {
+        return lane_reduce<V * EPV, OpAdd>(x);
+    } else {
+        float sv[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            if (v == (V > 1 ? 1 : 0)) {
+                const int d = rv.dup(i, v);
+                float z[EPV];
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) z[e] = e < d ? 0.0f : x[v * EPV + e];
+                sv[v] = lane_reduce<EPV, OpAdd>(z);
+            } else {
+                sv[v] = lane_reduce<EPV, OpAdd>(x + v * EPV);
+            }
+        }
+        return lane_reduce<V, OpAdd>(sv);
+    }
 }
 
+// The same for the products a g (lane_dot's tree).
+template <class E, int V, bool SHIFT, int STRIDE>
+__device__ __forceinline__ float row_dot(const RowVecs<E, SHIFT, STRIDE, V>& rv, int i, const float* a, const float* g) {
+    constexpr int EPV = E::kEPV;
+    if constexpr (!SHIFT) {
+        return lane_dot<V * EPV>(a, g);
+    } else {
+        float sv[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            if (v == (V > 1 ? 1 : 0)) {
+                const int d = rv.dup(i, v);
+                float z[EPV];
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) z[e] = e < d ? 0.0f : g[v * EPV + e];
+                sv[v] = lane_dot<EPV>(a + v * EPV, z);
+            } else {
+                sv[v] = lane_dot<EPV>(a + v * EPV, g + v * EPV);
+            }
+        }
+        return lane_reduce<V, OpAdd>(sv);
+    }
+}
+
+// Vectors of a row of `cols` elements (the last one partial, or shifted back).
+template <class E>
+__device__ __forceinline__ int span_vecs(int cols) {
+    return (cols + E::kEPV - 1) / E::kEPV;
+}
+
+// Softmax of U rows per group, all loads first (U rows x V vectors in flight per lane).
+//   row r of the item starts at element base + r * cols; rows r0, r0 + step, ...
+// VEC false: element by element, for rows shorter than a vector (V = 1).
 template <class E, int G, int V, int U, bool VEC, bool SHIFT = false>
 __device__ __forceinline__ void rows_u(const typename E::T* in, typename E::T* out, int64_t base,
                                        int cols, int nrows, int r0, int step, int lane) {
@@ -263,15 +353,10 @@ __device__ __forceinline__ void rows_u(const typename E::T* in, typename E::T* o
         if constexpr (VEC) {
             // the vectors as loaded (a lane's loads all issued before any use; unpacking
             // inside each conditional load would make every load wait for the previous one)
-            const RowVecs<E, SHIFT> rv(o, cols);
+            const RowVecs<E, SHIFT, G, V> rv(o, cols);
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const int vi = lane + v * G;
-                if (act[u] && vi < rv.nv)
-                    raw[u][v] = E::load_raw(in + rv.start + vi * EPV);
-                else
-                    raw[u][v] = E::raw_fill(kNegInf);
-            }
+            for (int v = 0; v < V; ++v)
+                raw[u][v] = act[u] && rv.in(lane, v) ? rv.load(in, lane, v) : E::raw_fill(kNegInf);
         } else {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -283,12 +368,8 @@ __device__ __forceinline__ void rows_u(const typename E::T* in, typename E::T* o
     if constexpr (VEC) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const RowVecs<E, SHIFT> rv(base + static_cast<int64_t>(r0 + u * step) * cols, cols);
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                E::unpack(raw[u][v], &x[u][v * EPV]);
-                rv.mask(lane + v * G, &x[u][v * EPV], kNegInf);
-            }
+            for (int v = 0; v < V; ++v) E::unpack(raw[u][v], &x[u][v * EPV]);
         }
     }
 #pragma unroll
@@ -297,19 +378,17 @@ __device__ __forceinline__ void rows_u(const typename E::T* in, typename E::T* o
         const float ms = (m == kNegInf) ? 0.0f : m;  // fully masked row: every e is 0
 #pragma unroll
         for (int k = 0; k < K; ++k) x[u][k] = __builtin_amdgcn_exp2f((x[u][k] - ms) * kLog2e);
-        const float s = group_reduce<G, OpAdd>(lane_reduce<K, OpAdd>(x[u]));
+        const int r = r0 + u * step;
+        const int64_t o = base + static_cast<int64_t>(r) * cols;
+        const RowVecs<E, SHIFT, G, V> rv(o, cols);
+        const float s = group_reduce<G, OpAdd>(row_sum<E, V>(rv, lane, x[u]));
         const float inv = (s == 0.0f) ? 0.0f : __builtin_amdgcn_rcpf(s);
 #pragma unroll
         for (int k = 0; k < K; ++k) x[u][k] *= inv;
-        const int r = r0 + u * step;
-        const int64_t o = base + static_cast<int64_t>(r) * cols;
         if constexpr (VEC) {
-            const RowVecs<E, SHIFT> rv(o, cols);
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const int vi = lane + v * G;
-                if (act[u] && vi < rv.nv) rv.store(out, vi, &x[u][v * EPV]);
-            }
+            for (int v = 0; v < V; ++v)
+                if (act[u] && rv.in(lane, v)) rv.store(out, lane, v, &x[u][v * EPV]);
         } else {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -459,191 +538,6 @@ __device__ __forceinline__ uint32_t run_item(const typename E::T* in, typename E
     return done;
 }
 
-// One wave per row, for rows that neither a register tile nor the workgroup path takes: rows
-// whose start or length is not 16-byte aligned, beyond 64 vectors (element-wise, in chunks of
-// 8 elements, whose per-element addresses cost registers), and in the backward pass aligned
-// rows of 257..512 vectors (chunks of CH 16-byte vectors per lane, VALS values: 32 for one
-// input stream, 16 for two, so each lane keeps CH loads in flight).
-//
-// When the row fits the wave's LDS region (`cap` floats, given to plans with long rows), it is
-// read from HBM once: pass 1 keeps a per-lane max while staging the values in LDS, pass 2
-// turns the staged values into e = 2^((x - M) log2 e) in place and sums them, pass 3 writes
-// e * (1/S).  Every lane re-reads only what it wrote itself, so no barrier is needed.
-//
-// Otherwise two passes over HBM: pass 1 keeps a per-lane running max and a sum rescaled
-// whenever a chunk raises the max, the lanes' pairs are merged, pass 2 re-reads the row and
-// writes e * (1/S) (1.5x the bytes of the staged path).
-template <class E, bool VEC, int VALS = 32>
-struct LongRow {
-    using T = typename E::T;
-    static constexpr int EPV = E::kEPV;
-    static constexpr int CH = VALS / EPV;      // vectors per lane per chunk (aligned rows)
-    static constexpr int K = VEC ? CH * EPV : 8;  // values per lane per chunk
-
-    // Loads chunk c0 (vector index of the lane's first vector, stride 64) into x; vectors past
-    // the row are -inf.  Element-wise variant: elements j0 + 64 k.
-    __device__ __forceinline__ static void load(const T* src, int cols, int first, float* x,
-                                                float pad = kNegInf) {
-        if constexpr (VEC) {
-            // every load of the chunk issued before any is unpacked (as in rows_u)
-            const int nvec = cols / EPV;
-            typename E::R raw[CH];
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int vi = first + c * 64;
-                if (vi < nvec)
-                    raw[c] = E::load_raw(src + vi * EPV);
-                else
-                    raw[c] = E::raw_fill(pad);
-            }
-#pragma unroll
-            for (int c = 0; c < CH; ++c) E::unpack(raw[c], x + c * EPV);
-        } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int j = first + k * 64;
-                x[k] = j < cols ? E::load1(src + j) : pad;
-            }
-        }
-    }
-    // The lane's values of a chunk to / from LDS at their element index (each lane touches
-    // only what it wrote itself).
-    __device__ __forceinline__ static void to_lds(float* lds, int cols, int first, const float* x) {
-        if constexpr (VEC) {
-            const int nvec = cols / EPV;
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int vi = first + c * 64;
-                if (vi < nvec) {
-#pragma unroll
-                    for (int i = 0; i < EPV; i += 4)
-                        *reinterpret_cast<f32x4*>(lds + vi * EPV + i) =
-                            f32x4{x[c * EPV + i], x[c * EPV + i + 1], x[c * EPV + i + 2], x[c * EPV + i + 3]};
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int j = first + k * 64;
-                if (j < cols) lds[j] = x[k];
-            }
-        }
-    }
-    __device__ __forceinline__ static void from_lds(const float* lds, int cols, int first, float* x,
-                                                    float pad) {
-        if constexpr (VEC) {
-            const int nvec = cols / EPV;
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int vi = first + c * 64;
-#pragma unroll
-                for (int i = 0; i < EPV; i += 4) {
-                    f32x4 v = f32x4{pad, pad, pad, pad};
-                    if (vi < nvec) v = *reinterpret_cast<const f32x4*>(lds + vi * EPV + i);
-                    x[c * EPV + i] = v.x;
-                    x[c * EPV + i + 1] = v.y;
-                    x[c * EPV + i + 2] = v.z;
-                    x[c * EPV + i + 3] = v.w;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int j = first + k * 64;
-                x[k] = j < cols ? lds[j] : pad;
-            }
-        }
-    }
-    __device__ __forceinline__ static void store(T* dst, int cols, int first, const float* y) {
-        if constexpr (VEC) {
-            const int nvec = cols / EPV;
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int vi = first + c * 64;
-                if (vi < nvec) E::store_vec(dst + vi * EPV, y + c * EPV);
-            }
-        } else {
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int j = first + k * 64;
-                if (j < cols) E::store1(dst + j, y[k]);
-            }
-        }
-    }
-    static constexpr int kStep = VEC ? CH * 64 : K * 64;
-    __device__ __forceinline__ static int extent(int cols) { return VEC ? cols / EPV : cols; }
-};
-
-// Forward one-wave path: element by element (rows in buffers that are not 16-byte aligned;
-// aligned buffers take the register tiles, shifted vectors or the workgroup path).
-template <class E, bool STAGE>
-__device__ __forceinline__ void long_row(const typename E::T* src, typename E::T* dst, int cols,
-                                         int lane, float* lds, int cap) {
-    using L = LongRow<E, false>;
-    constexpr int K = L::K;
-    const int step = L::kStep;
-    if (STAGE && cols <= cap) {
-        // LDS holds the row as floats at their element index
-        float m = kNegInf;
-        for (int first = lane; first < cols; first += step) {
-            float x[K];
-            L::load(src, cols, first, x);
-            m = OpMax::f(m, lane_reduce<K, OpMax>(x));
-            L::to_lds(lds, cols, first, x);
-        }
-        const float M = group_reduce<64, OpMax>(m);
-        const float Ms = (M == kNegInf) ? 0.0f : M;
-        float s = 0.0f;
-        for (int first = lane; first < cols; first += step) {
-            float e[K];
-#pragma unroll
-            for (int k = 0; k < K; ++k) {
-                const int j = first + k * 64;
-                e[k] = j < cols ? __builtin_amdgcn_exp2f((lds[j] - Ms) * kLog2e) : 0.0f;
-                if (j < cols) lds[j] = e[k];
-            }
-            s += lane_reduce<K, OpAdd>(e);
-        }
-        const float S = group_reduce<64, OpAdd>(s);
-        const float inv = (S == 0.0f) ? 0.0f : __builtin_amdgcn_rcpf(S);
-        for (int first = lane; first < cols; first += step) {
-            float y[K];
-            L::from_lds(lds, cols, first, y, 0.0f);
-#pragma unroll
-            for (int k = 0; k < K; ++k) y[k] *= inv;
-            L::store(dst, cols, first, y);
-        }
-        return;
-    }
-    float m = kNegInf, s = 0.0f;
-    for (int first = lane; first < cols; first += step) {
-        float x[K];
-        L::load(src, cols, first, x);
-        const float cm = lane_reduce<K, OpMax>(x);
-        if (cm > m) {
-            s *= __builtin_amdgcn_exp2f((m - cm) * kLog2e);
-            m = cm;
-        }
-        if (m != kNegInf) {
-#pragma unroll
-            for (int k = 0; k < K; ++k) x[k] = __builtin_amdgcn_exp2f((x[k] - m) * kLog2e);
-            s += lane_reduce<K, OpAdd>(x);
-        }
-    }
-    const float M = group_reduce<64, OpMax>(m);
-    const float Ms = (M == kNegInf) ? 0.0f : M;
-    const float scale = (m == kNegInf) ? 0.0f : __builtin_amdgcn_exp2f((m - Ms) * kLog2e);
-    const float S = group_reduce<64, OpAdd>(s * scale);
-    const float inv = (S == 0.0f) ? 0.0f : __builtin_amdgcn_rcpf(S);
-    for (int first = lane; first < cols; first += step) {
-        float x[K];
-        L::load(src, cols, first, x);
-#pragma unroll
-        for (int k = 0; k < K; ++k) x[k] = __builtin_amdgcn_exp2f((x[k] - Ms) * kLog2e) * inv;
-        L::store(dst, cols, first, x);
-    }
-}
-
 // ------------------------------------------------------------------------ workgroup rows
 // Aligned rows beyond the register tile, one row at a time per workgroup: all of its
 // nt = 64 * nwaves lanes share the row, lane t holding vectors t, t + nt, ..., t + (L-1) nt (so
@@ -674,56 +568,60 @@ __device__ __forceinline__ void team_combine(float (&v)[U], int which, int wave,
     }
 }
 
-// Lane t's vectors t + c nt, c < L, of row rv; vectors past the row (or of an inactive row)
-// read as `pad`, and so do a shifted row's outside elements (after team_unpack).
-template <class E, int L, bool SHIFT>
-__device__ __forceinline__ void team_load(const typename E::T* in, const RowVecs<E, SHIFT>& rv,
-                                          int first, int nt, bool act, typename E::R* raw,
+// Lane t's vectors of slots s0 + c, c < L, of row rv (NT lanes to a slot); vectors past the row
+// (or of an inactive row) read as `pad`.
+template <class E, int L, bool SHIFT, int NT>
+using TeamVecs = RowVecs<E, SHIFT, NT, (L > 1 ? L : 2)>;
+
+template <class E, int L, bool SHIFT, int NT>
+__device__ __forceinline__ void team_load(const typename E::T* in, const TeamVecs<E, L, SHIFT, NT>& rv,
+                                          int t, int s0, bool act, typename E::R* raw,
                                           float pad = kNegInf) {
-    constexpr int EPV = E::kEPV;
 #pragma unroll
-    for (int c = 0; c < L; ++c) {
-        const int vi = first + c * nt;
-        raw[c] = (act && vi < rv.nv) ? E::load_raw(in + rv.start + vi * EPV) : E::raw_fill(pad);
-    }
+    for (int c = 0; c < L; ++c)
+        raw[c] = (act && rv.in(t, s0 + c)) ? rv.load(in, t, s0 + c) : E::raw_fill(pad);
 }
 
-template <class E, int L, bool SHIFT>
-__device__ __forceinline__ void team_unpack(const RowVecs<E, SHIFT>& rv, int first, int nt,
-                                            const typename E::R* raw, float* x,
-                                            float pad = kNegInf) {
+template <class E, int L>
+__device__ __forceinline__ void team_unpack(const typename E::R* raw, float* x) {
 #pragma unroll
-    for (int c = 0; c < L; ++c) {
-        E::unpack(raw[c], x + c * E::kEPV);
-        rv.mask(first + c * nt, x + c * E::kEPV, pad);
-    }
+    for (int c = 0; c < L; ++c) E::unpack(raw[c], x + c * E::kEPV);
 }
 
-template <class E, int L, bool SHIFT>
-__device__ __forceinline__ void team_store(typename E::T* out, const RowVecs<E, SHIFT>& rv,
-                                           int first, int nt, bool act, const float* y) {
+// Duplicates of a shifted row as `pad` (passes over a row that is read twice).
+template <class E, int L, bool SHIFT, int NT>
+__device__ __forceinline__ void team_mask(const TeamVecs<E, L, SHIFT, NT>& rv, int t, int s0, float* x, float pad) {
+#pragma unroll
+    for (int c = 0; c < L; ++c) rv.mask(t, s0 + c, x + c * E::kEPV, pad);
+}
+
+template <class E, int L, bool SHIFT, int NT, bool OWN = false>
+__device__ __forceinline__ void team_store(typename E::T* out, const TeamVecs<E, L, SHIFT, NT>& rv,
+                                           int t, int s0, bool act, const float* y) {
 #pragma unroll
     for (int c = 0; c < L; ++c) {
-        const int vi = first + c * nt;
-        if (act && vi < rv.nv) rv.store(out, vi, y + c * E::kEPV);
+        if (act && rv.in(t, s0 + c)) {
+            if constexpr (OWN) rv.store_own(out, t, s0 + c, y + c * E::kEPV);
+            else rv.store(out, t, s0 + c, y + c * E::kEPV);
+        }
     }
 }
 
 // Up to U rows (those with act[u], starting at elements off[u]) held in registers: L vectors
-// per lane cover nt * L vectors of a row.  A row's arithmetic does not depend on U.
-template <class E, int L, int U, bool SHIFT>
+// per lane cover NT * L vectors of a row.  A row's arithmetic does not depend on U.
+template <class E, int L, int U, bool SHIFT, int NT>
 __device__ __forceinline__ void team_rows(const typename E::T* in, typename E::T* out,
                                           const int64_t (&off)[U], const bool (&act)[U], int cols,
-                                          int t, int nt, int wave, int nwaves, int lane) {
+                                          int t, int wave, int nwaves, int lane) {
+    using RV = TeamVecs<E, L, SHIFT, NT>;
     constexpr int K = L * E::kEPV;
     float x[U][K];
     typename E::R raw[U][L];
 #pragma unroll
     for (int u = 0; u < U; ++u)
-        team_load<E, L, SHIFT>(in, RowVecs<E, SHIFT>(off[u], cols), t, nt, act[u], raw[u]);
+        team_load<E, L, SHIFT, NT>(in, RV(off[u], cols), t, 0, act[u], raw[u]);
 #pragma unroll
-    for (int u = 0; u < U; ++u)
-        team_unpack<E, L, SHIFT>(RowVecs<E, SHIFT>(off[u], cols), t, nt, raw[u], x[u]);
+    for (int u = 0; u < U; ++u) team_unpack<E, L>(raw[u], x[u]);
     float m[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) m[u] = group_reduce<64, OpMax>(lane_reduce<K, OpMax>(x[u]));
@@ -734,7 +632,7 @@ __device__ __forceinline__ void team_rows(const typename E::T* in, typename E::T
         const float ms = (m[u] == kNegInf) ? 0.0f : m[u];
 #pragma unroll
         for (int k = 0; k < K; ++k) x[u][k] = __builtin_amdgcn_exp2f((x[u][k] - ms) * kLog2e);
-        s[u] = group_reduce<64, OpAdd>(lane_reduce<K, OpAdd>(x[u]));
+        s[u] = group_reduce<64, OpAdd>(row_sum<E, L>(RV(off[u], cols), t, x[u]));
     }
     team_combine<OpAdd, U>(s, 1, wave, nwaves, lane);
 #pragma unroll
@@ -742,7 +640,7 @@ __device__ __forceinline__ void team_rows(const typename E::T* in, typename E::T
         const float inv = (s[u] == 0.0f) ? 0.0f : __builtin_amdgcn_rcpf(s[u]);
 #pragma unroll
         for (int k = 0; k < K; ++k) x[u][k] *= inv;
-        team_store<E, L, SHIFT>(out, RowVecs<E, SHIFT>(off[u], cols), t, nt, act[u], x[u]);
+        team_store<E, L, SHIFT, NT>(out, RV(off[u], cols), t, 0, act[u], x[u]);
     }
 }
 
@@ -775,19 +673,20 @@ struct RowWalk {
     }
 };
 
-// A row longer than nt * L vectors: chunks of nt * L vectors, read twice.
-template <class E, int L, bool SHIFT>
+// A row longer than NT * L vectors: chunks of L slots, read twice.
+template <class E, int L, bool SHIFT, int NT>
 __device__ __forceinline__ void team_row_two_pass(const typename E::T* in, typename E::T* out,
-                                                  int64_t off, int cols, int t, int nt, int wave,
+                                                  int64_t off, int cols, int t, int wave,
                                                   int nwaves, int lane) {
     constexpr int K = L * E::kEPV;
-    const RowVecs<E, SHIFT> rv(off, cols);
+    const TeamVecs<E, L, SHIFT, NT> rv(off, cols);
     float m = kNegInf, s = 0.0f;
-    for (int first = t; first - t < rv.nv; first += nt * L) {
+    for (int s0 = 0; s0 * NT < rv.nv; s0 += L) {
         float x[K];
         typename E::R raw[L];
-        team_load<E, L, SHIFT>(in, rv, first, nt, true, raw);
-        team_unpack<E, L, SHIFT>(rv, first, nt, raw, x);
+        team_load<E, L, SHIFT, NT>(in, rv, t, s0, true, raw);
+        team_unpack<E, L>(raw, x);
+        team_mask<E, L, SHIFT, NT>(rv, t, s0, x, kNegInf);
         const float cm = lane_reduce<K, OpMax>(x);
         if (cm > m) {
             s *= __builtin_amdgcn_exp2f((m - cm) * kLog2e);
@@ -806,14 +705,14 @@ __device__ __forceinline__ void team_row_two_pass(const typename E::T* in, typen
     float S[1] = {group_reduce<64, OpAdd>(s * scale)};
     team_combine<OpAdd, 1>(S, 1, wave, nwaves, lane);
     const float inv = (S[0] == 0.0f) ? 0.0f : __builtin_amdgcn_rcpf(S[0]);
-    for (int first = t; first - t < rv.nv; first += nt * L) {
+    for (int s0 = 0; s0 * NT < rv.nv; s0 += L) {
         float x[K];
         typename E::R raw[L];
-        team_load<E, L, SHIFT>(in, rv, first, nt, true, raw);
-        team_unpack<E, L, SHIFT>(rv, first, nt, raw, x);
+        team_load<E, L, SHIFT, NT>(in, rv, t, s0, true, raw);
+        team_unpack<E, L>(raw, x);
 #pragma unroll
         for (int k = 0; k < K; ++k) x[k] = __builtin_amdgcn_exp2f((x[k] - Ms) * kLog2e) * inv;
-        team_store<E, L, SHIFT>(out, rv, first, nt, true, x);
+        team_store<E, L, SHIFT, NT, true>(out, rv, t, s0, true, x);
     }
 }
 
@@ -828,9 +727,9 @@ template <class E, int KCLASS, bool SHIFT>
 __device__ __forceinline__ uint32_t team_item(const typename E::T* in, typename E::T* out,
                                               int64_t base, int cols, int nrows, int reps,
                                               int64_t stride, int wave, int nwaves, int lane) {
-    const int nt = nwaves * 64;
+    constexpr int nt = bsm::team_threads(KCLASS);  // the workgroup: such plans run no other size
     const int t = wave * 64 + lane;
-    const int per_lane = (span_vecs<E, SHIFT>(cols) + nt - 1) / nt;
+    const int per_lane = (span_vecs<E>(cols) + nt - 1) / nt;
     constexpr int kMaxL = kTeamMaxL<E, KCLASS>;  // 4 or 8 (class 4), 8 or 16 (class 5)
     if (per_lane <= 3) {
         // the shortest rows (at most 3 of the 4 vectors per lane): two in flight, so that a lane
@@ -841,7 +740,7 @@ __device__ __forceinline__ uint32_t team_item(const typename E::T* in, typename 
             int64_t off[2];
             bool act[2];
             w.next(off, act);
-            team_rows<E, 4, 2, SHIFT>(in, out, off, act, cols, t, nt, wave, nwaves, lane);
+            team_rows<E, 4, 2, SHIFT, nt>(in, out, off, act, cols, t, wave, nwaves, lane);
         }
     } else if (E::kBytes == 2 && kMaxL >= 6 && per_lane <= 6) {
         // bf16 rows of 5 or 6 vectors per lane (e.g. 8200 elements): two rows in flight, as for
@@ -855,10 +754,10 @@ __device__ __forceinline__ uint32_t team_item(const typename E::T* in, typename 
             bool act[2];
             w.next(off, act);
             if (per_lane <= 5)
-                team_rows<E, (kMaxL >= 6 ? 5 : 4), 2, SHIFT>(in, out, off, act, cols, t, nt, wave,
+                team_rows<E, (kMaxL >= 6 ? 5 : 4), 2, SHIFT, nt>(in, out, off, act, cols, t, wave,
                                                              nwaves, lane);
             else
-                team_rows<E, (kMaxL >= 6 ? 6 : 4), 2, SHIFT>(in, out, off, act, cols, t, nt, wave,
+                team_rows<E, (kMaxL >= 6 ? 6 : 4), 2, SHIFT, nt>(in, out, off, act, cols, t, wave,
                                                              nwaves, lane);
         }
     } else if (per_lane <= kMaxL) {
@@ -868,12 +767,12 @@ __device__ __forceinline__ uint32_t team_item(const typename E::T* in, typename 
             bool act[1];
             w.next(off, act);
             if (per_lane <= 4)
-                team_rows<E, 4, 1, SHIFT>(in, out, off, act, cols, t, nt, wave, nwaves, lane);
+                team_rows<E, 4, 1, SHIFT, nt>(in, out, off, act, cols, t, wave, nwaves, lane);
             else if (kMaxL > 8 && per_lane <= 8)
-                team_rows<E, (kMaxL > 8 ? 8 : kMaxL), 1, SHIFT>(in, out, off, act, cols, t, nt,
+                team_rows<E, (kMaxL > 8 ? 8 : kMaxL), 1, SHIFT, nt>(in, out, off, act, cols, t,
                                                                 wave, nwaves, lane);
             else
-                team_rows<E, kMaxL, 1, SHIFT>(in, out, off, act, cols, t, nt, wave, nwaves, lane);
+                team_rows<E, kMaxL, 1, SHIFT, nt>(in, out, off, act, cols, t, wave, nwaves, lane);
         }
     } else {
         RowWalk<1> w(base, cols, nrows, reps, stride);
@@ -881,25 +780,19 @@ __device__ __forceinline__ uint32_t team_item(const typename E::T* in, typename 
             int64_t off[1];
             bool act[1];
             w.next(off, act);
-            team_row_two_pass<E, kMaxL, SHIFT>(in, out, off[0], cols, t, nt, wave, nwaves, lane);
+            team_row_two_pass<E, kMaxL, SHIFT, nt>(in, out, off[0], cols, t, wave, nwaves, lane);
         }
     }
     return team_rows_of_wave(nrows, reps, wave, nwaves);
 }
 
-// Vectors the largest register tile of a kernel class covers (classes 4 and 5: any row).
-template <int KCLASS>
-constexpr int kClassMaxVecs = KCLASS == 0 ? 64 : KCLASS == 1 ? 128 : KCLASS == 2 ? 256
-                              : KCLASS == 3 ? 512 : 0x7FFFFFFF;
-
-// Register-tile choice per item (wave-uniform branch); the thresholds are bsm::tile_for's.  A
-// shifted item's tile covers the vectors its rows may span (one more than their length).
+// Register-tile choice per item (wave-uniform branch); the thresholds are bsm::tile_for's.
 template <class E, int KCLASS, bool VEC, bool SHIFT>
 __device__ __forceinline__ uint32_t dispatch_item(const typename E::T* in, typename E::T* out,
                                                   int64_t base, int cols, int nrows, int reps,
                                                   int64_t stride, int wave, int nwaves,
-                                                  int lane64, float* lds, int cap, bool team) {
-    const int nvec = VEC ? span_vecs<E, SHIFT>(cols) : (cols + E::kEPV - 1) / E::kEPV;
+                                                  int lane64, bool team) {
+    const int nvec = span_vecs<E>(cols);
 #define BSM_RUN(G, V, U) run_item<E, G, V, U, VEC, SHIFT>(in, out, base, cols, nrows, reps, stride, wave, nwaves, lane64)
     if constexpr (VEC) {
         // the tile of bsm::tile_for: one wave-uniform branch per (G, V, U) the class can pick
@@ -938,11 +831,7 @@ __device__ __forceinline__ uint32_t dispatch_item(const typename E::T* in, typen
         }
 #undef BSM_TILE
     } else {
-        // element-wise rows (buffers not 16-byte aligned), one row per group in flight: the
-        // per-element addresses cost registers; longer rows take the one-wave path
-        if (nvec <= 16) return BSM_RUN(16, 1, 1);
-        if (nvec <= 32) return BSM_RUN(32, 1, 1);
-        if (nvec <= 64) return BSM_RUN(64, 1, 1);
+        return BSM_RUN(16, 1, 1);  // rows shorter than a vector
     }
 #undef BSM_RUN
     if constexpr (VEC && KCLASS >= 4) {
@@ -951,21 +840,7 @@ __device__ __forceinline__ uint32_t dispatch_item(const typename E::T* in, typen
             return team_item<E, KCLASS, SHIFT>(in, out, base, cols, nrows, reps, stride, wave,
                                                nwaves, lane64);
     }
-    if constexpr (!VEC || KCLASS >= 4) {
-        uint32_t done = 0;
-        for (int k = 0; k < reps; ++k) {
-            for (int r = wave; r < nrows; r += nwaves) {
-                const int64_t o = base + k * stride + static_cast<int64_t>(r) * cols;
-                // element by element (an aligned item gets here only in a per-wave table of a
-                // long-row class, which the host never builds); only the long-row classes are
-                // launched with LDS to stage rows in
-                long_row<E, (KCLASS >= 4)>(in + o, out + o, cols, lane64, lds, cap);
-                ++done;
-            }
-        }
-        return done;
-    }
-    return 0;  // unreachable: the item's access path is chosen so that its class covers it
+    return 0;  // unreachable: the plan's class covers its longest row
 }
 
 // ------------------------------------------------------------------------------- backward
@@ -982,6 +857,48 @@ __device__ __forceinline__ void rows_u_bwd(const typename E::T* y, const typenam
                                            int r0, int step, int lane) {
     constexpr int EPV = E::kEPV;
     constexpr int K = V * EPV;
+    if constexpr (E::kBytes == 2 && V == 8) {
+        // bf16 rows of 257..512 vectors: y and dy stay packed as they were loaded (64 registers)
+        // and are unpacked a vector at a time, once for d and once for dx; unpacked together
+        // they take 128 registers.  Against two reads of the row (5/3 of the bytes): 64 slices of
+        // 500 x 3328 179 -> 121 us, 500 x 3333 188 -> 128 us, 500 x 2056 118 -> 78 us.
+        static_assert(U == 1, "one row per wave");
+        const bool act = r0 < nrows;
+        const RowVecs<E, SHIFT, G, V> rv(base + static_cast<int64_t>(r0) * cols, cols);
+        typename E::R ra[V], rg[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const bool in = act && rv.in(lane, v);
+            ra[v] = in ? rv.load(y, lane, v) : E::raw_fill(0.0f);
+            rg[v] = in ? rv.load(dy, lane, v) : E::raw_fill(0.0f);
+        }
+        float sv[V];
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            float a[EPV], g[EPV];
+            E::unpack(ra[v], a);
+            E::unpack(rg[v], g);
+            if (SHIFT && v == 1) {
+                const int d = rv.dup(lane, v);
+#pragma unroll
+                for (int e = 0; e < EPV; ++e) g[e] = e < d ? 0.0f : g[e];
+            }
+            sv[v] = lane_dot<EPV>(a, g);
+        }
+        const float d = group_reduce<G, OpAdd>(lane_reduce<V, OpAdd>(sv));
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            // opaque to the compiler, which would otherwise keep the values unpacked above
+            asm volatile("" : "+v"(ra[v]), "+v"(rg[v]));
+            float a[EPV], g[EPV];
+            E::unpack(ra[v], a);
+            E::unpack(rg[v], g);
+#pragma unroll
+            for (int e = 0; e < EPV; ++e) a[e] = a[e] * (g[e] - d);
+            if (act && rv.in(lane, v)) rv.store(dx, lane, v, a);
+        }
+        return;
+    }
     float a[U][K], g[U][K];
     typename E::R ra[U][V], rg[U][V];
     bool act[U];
@@ -991,13 +908,12 @@ __device__ __forceinline__ void rows_u_bwd(const typename E::T* y, const typenam
         act[u] = r < nrows;
         const int64_t o = base + static_cast<int64_t>(r) * cols;
         if constexpr (VEC) {
-            const RowVecs<E, SHIFT> rv(o, cols);
+            const RowVecs<E, SHIFT, G, V> rv(o, cols);
 #pragma unroll
             for (int v = 0; v < V; ++v) {
-                const int vi = lane + v * G;
-                if (act[u] && vi < rv.nv) {
-                    ra[u][v] = E::load_raw(y + rv.start + vi * EPV);
-                    rg[u][v] = E::load_raw(dy + rv.start + vi * EPV);
+                if (act[u] && rv.in(lane, v)) {
+                    ra[u][v] = rv.load(y, lane, v);
+                    rg[u][v] = rv.load(dy, lane, v);
                 } else {
                     ra[u][v] = rg[u][v] = E::raw_fill(0.0f);
                 }
@@ -1012,33 +928,28 @@ __device__ __forceinline__ void rows_u_bwd(const typename E::T* y, const typenam
             }
         }
     }
-    if constexpr (VEC) {  // unpacked after every load is issued; outside elements are 0
+    if constexpr (VEC) {  // unpacked after every load is issued; vectors past the row are 0
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            const RowVecs<E, SHIFT> rv(base + static_cast<int64_t>(r0 + u * step) * cols, cols);
 #pragma unroll
             for (int v = 0; v < V; ++v) {
                 E::unpack(ra[u][v], &a[u][v * EPV]);
                 E::unpack(rg[u][v], &g[u][v * EPV]);
-                rv.mask(lane + v * G, &a[u][v * EPV], 0.0f);
-                rv.mask(lane + v * G, &g[u][v * EPV], 0.0f);
             }
         }
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const float d = group_reduce<G, OpAdd>(lane_dot<K>(a[u], g[u]));
-#pragma unroll
-        for (int k = 0; k < K; ++k) a[u][k] = a[u][k] * (g[u][k] - d);
         const int r = r0 + u * step;
         const int64_t o = base + static_cast<int64_t>(r) * cols;
-        if constexpr (VEC) {
-            const RowVecs<E, SHIFT> rv(o, cols);
+        const RowVecs<E, SHIFT, G, V> rv(o, cols);
+        const float d = group_reduce<G, OpAdd>(row_dot<E, V>(rv, lane, a[u], g[u]));
 #pragma unroll
-            for (int v = 0; v < V; ++v) {
-                const int vi = lane + v * G;
-                if (act[u] && vi < rv.nv) rv.store(dx, vi, &a[u][v * EPV]);
-            }
+        for (int k = 0; k < K; ++k) a[u][k] = a[u][k] * (g[u][k] - d);
+        if constexpr (VEC) {
+#pragma unroll
+            for (int v = 0; v < V; ++v)
+                if (act[u] && rv.in(lane, v)) rv.store(dx, lane, v, &a[u][v * EPV]);
         } else {
 #pragma unroll
             for (int k = 0; k < K; ++k) {
@@ -1152,115 +1063,75 @@ __device__ __forceinline__ uint32_t run_item_bwd(const typename E::T* y, const t
     return done;
 }
 
-// One row beyond the tile, one wave: pass 1 streams y and dy once, keeping the lane's partial
-// sum of products (each chunk's products by the in-lane tree, chunks in order) and, when both
-// fit the wave's LDS region (2 cols <= cap), staging them there; pass 2 forms dx from LDS or,
-// otherwise, from a second read of y and dy.  Both variants add in the same order.
-template <class E, bool VEC, bool STAGE>
-__device__ __forceinline__ void long_row_bwd(const typename E::T* y, const typename E::T* dy,
-                                             typename E::T* dx, int cols, int lane, float* lds,
-                                             int cap) {
-    using L = LongRow<E, VEC, 16>;  // two streams: half the values per lane per chunk
-    constexpr int K = L::K;
-    const int n = L::extent(cols);
-    const int step = L::kStep;
-    const bool stage = STAGE && 2 * cols <= cap;
-    float s = 0.0f;
-    for (int first = lane; first < n; first += step) {
-        float a[K], g[K];
-        L::load(y, cols, first, a, 0.0f);
-        L::load(dy, cols, first, g, 0.0f);
-        if (stage) {
-            L::to_lds(lds, cols, first, a);
-            L::to_lds(lds + cols, cols, first, g);
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) g[k] *= a[k];
-        s += lane_reduce<K, OpAdd>(g);
-    }
-    const float d = group_reduce<64, OpAdd>(s);
-    for (int first = lane; first < n; first += step) {
-        float a[K], g[K];
-        if (stage) {
-            L::from_lds(lds, cols, first, a, 0.0f);
-            L::from_lds(lds + cols, cols, first, g, 0.0f);
-        } else {
-            L::load(y, cols, first, a, 0.0f);
-            L::load(dy, cols, first, g, 0.0f);
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) a[k] = a[k] * (g[k] - d);
-        L::store(dx, cols, first, a);
-    }
-}
-
 // Backward rows beyond the register tile, one (or two) at a time per workgroup, laid out as
 // in team_rows: y and dy held in registers, d = sum dy * y formed by the in-lane tree, the
 // wave's butterfly and the waves' values in wave order; one barrier per rows, alternating the
 // slot set (`which`), so a set is rewritten only after every wave has passed the next barrier.
-template <class E, int L, int U, bool SHIFT>
+template <class E, int L, int U, bool SHIFT, int NT>
 __device__ __forceinline__ void team_rows_bwd(const typename E::T* y, const typename E::T* dy,
                                               typename E::T* dx, const int64_t (&off)[U],
-                                              const bool (&act)[U], int cols, int t, int nt,
+                                              const bool (&act)[U], int cols, int t,
                                               int wave, int nwaves, int lane, int which) {
+    using RV = TeamVecs<E, L, SHIFT, NT>;
     constexpr int K = L * E::kEPV;
     float a[U][K], g[U][K];
     typename E::R ra[U][L], rg[U][L];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const RowVecs<E, SHIFT> rv(off[u], cols);
-        team_load<E, L, SHIFT>(y, rv, t, nt, act[u], ra[u], 0.0f);  // padding: products 0
-        team_load<E, L, SHIFT>(dy, rv, t, nt, act[u], rg[u], 0.0f);
+        const RV rv(off[u], cols);
+        team_load<E, L, SHIFT, NT>(y, rv, t, 0, act[u], ra[u], 0.0f);  // padding: products 0
+        team_load<E, L, SHIFT, NT>(dy, rv, t, 0, act[u], rg[u], 0.0f);
     }
     float d[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-        const RowVecs<E, SHIFT> rv(off[u], cols);
-        team_unpack<E, L, SHIFT>(rv, t, nt, ra[u], a[u], 0.0f);
-        team_unpack<E, L, SHIFT>(rv, t, nt, rg[u], g[u], 0.0f);
-        d[u] = group_reduce<64, OpAdd>(lane_dot<K>(a[u], g[u]));
+        const RV rv(off[u], cols);
+        team_unpack<E, L>(ra[u], a[u]);
+        team_unpack<E, L>(rg[u], g[u]);
+        d[u] = group_reduce<64, OpAdd>(row_dot<E, L>(rv, t, a[u], g[u]));
     }
     team_combine<OpAdd, U>(d, which, wave, nwaves, lane);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
         for (int k = 0; k < K; ++k) a[u][k] = a[u][k] * (g[u][k] - d[u]);
-        team_store<E, L, SHIFT>(dx, RowVecs<E, SHIFT>(off[u], cols), t, nt, act[u], a[u]);
+        team_store<E, L, SHIFT, NT>(dx, RV(off[u], cols), t, 0, act[u], a[u]);
     }
 }
 
-// A backward row longer than nt * L vectors: d over chunks, then y and dy read again.
-template <class E, int L, bool SHIFT>
+// A backward row longer than NT * L vectors: d over chunks, then y and dy read again.
+template <class E, int L, bool SHIFT, int NT>
 __device__ __forceinline__ void team_row_bwd_two_pass(const typename E::T* y,
                                                       const typename E::T* dy, typename E::T* dx,
-                                                      int64_t off, int cols, int t, int nt,
+                                                      int64_t off, int cols, int t,
                                                       int wave, int nwaves, int lane, int which) {
     constexpr int K = L * E::kEPV;
-    const RowVecs<E, SHIFT> rv(off, cols);
+    const TeamVecs<E, L, SHIFT, NT> rv(off, cols);
     float s = 0.0f;
-    for (int first = t; first - t < rv.nv; first += nt * L) {
+    for (int s0 = 0; s0 * NT < rv.nv; s0 += L) {
         float a[K], g[K];
         typename E::R ra[L], rg[L];
-        team_load<E, L, SHIFT>(y, rv, first, nt, true, ra, 0.0f);
-        team_load<E, L, SHIFT>(dy, rv, first, nt, true, rg, 0.0f);
-        team_unpack<E, L, SHIFT>(rv, first, nt, ra, a, 0.0f);
-        team_unpack<E, L, SHIFT>(rv, first, nt, rg, g, 0.0f);
+        team_load<E, L, SHIFT, NT>(y, rv, t, s0, true, ra, 0.0f);
+        team_load<E, L, SHIFT, NT>(dy, rv, t, s0, true, rg, 0.0f);
+        team_unpack<E, L>(ra, a);
+        team_unpack<E, L>(rg, g);
+        team_mask<E, L, SHIFT, NT>(rv, t, s0, g, 0.0f);
 #pragma unroll
         for (int k = 0; k < K; ++k) g[k] *= a[k];
         s += lane_reduce<K, OpAdd>(g);
     }
     float d[1] = {group_reduce<64, OpAdd>(s)};
     team_combine<OpAdd, 1>(d, which, wave, nwaves, lane);
-    for (int first = t; first - t < rv.nv; first += nt * L) {
+    for (int s0 = 0; s0 * NT < rv.nv; s0 += L) {
         float a[K], g[K];
         typename E::R ra[L], rg[L];
-        team_load<E, L, SHIFT>(y, rv, first, nt, true, ra, 0.0f);
-        team_load<E, L, SHIFT>(dy, rv, first, nt, true, rg, 0.0f);
-        team_unpack<E, L, SHIFT>(rv, first, nt, ra, a, 0.0f);
-        team_unpack<E, L, SHIFT>(rv, first, nt, rg, g, 0.0f);
+        team_load<E, L, SHIFT, NT>(y, rv, t, s0, true, ra, 0.0f);
+        team_load<E, L, SHIFT, NT>(dy, rv, t, s0, true, rg, 0.0f);
+        team_unpack<E, L>(ra, a);
+        team_unpack<E, L>(rg, g);
 #pragma unroll
         for (int k = 0; k < K; ++k) a[k] = a[k] * (g[k] - d[0]);
-        team_store<E, L, SHIFT>(dx, rv, first, nt, true, a);
+        team_store<E, L, SHIFT, NT, true>(dx, rv, t, s0, true, a);
     }
 }
 
@@ -1269,9 +1140,9 @@ __device__ __forceinline__ uint32_t team_item_bwd(const typename E::T* y, const 
                                                   typename E::T* dx, int64_t base, int cols,
                                                   int nrows, int reps, int64_t stride, int wave,
                                                   int nwaves, int lane) {
-    const int nt = nwaves * 64;
+    constexpr int nt = bsm::team_threads(KCLASS);
     const int t = wave * 64 + lane;
-    const int per_lane = (span_vecs<E, SHIFT>(cols) + nt - 1) / nt;
+    const int per_lane = (span_vecs<E>(cols) + nt - 1) / nt;
     constexpr int kMaxL = kTeamMaxL<E, KCLASS>;  // vectors per lane and stream
     constexpr bool kPair = 2 * 4 * E::kEPV <= bsm::kTeamValues;  // as in team_item
     int which = 0;
@@ -1281,7 +1152,7 @@ __device__ __forceinline__ uint32_t team_item_bwd(const typename E::T* y, const 
             int64_t off[2];
             bool act[2];
             w.next(off, act);
-            team_rows_bwd<E, 4, 2, SHIFT>(y, dy, dx, off, act, cols, t, nt, wave, nwaves, lane,
+            team_rows_bwd<E, 4, 2, SHIFT, nt>(y, dy, dx, off, act, cols, t, wave, nwaves, lane,
                                           which);
             which ^= 1;
         }
@@ -1291,7 +1162,7 @@ __device__ __forceinline__ uint32_t team_item_bwd(const typename E::T* y, const 
             int64_t off[1];
             bool act[1];
             w.next(off, act);
-            team_rows_bwd<E, kMaxL, 1, SHIFT>(y, dy, dx, off, act, cols, t, nt, wave, nwaves,
+            team_rows_bwd<E, kMaxL, 1, SHIFT, nt>(y, dy, dx, off, act, cols, t, wave, nwaves,
                                               lane, which);
             which ^= 1;
         }
@@ -1301,7 +1172,7 @@ __device__ __forceinline__ uint32_t team_item_bwd(const typename E::T* y, const 
             int64_t off[1];
             bool act[1];
             w.next(off, act);
-            team_row_bwd_two_pass<E, kMaxL, SHIFT>(y, dy, dx, off[0], cols, t, nt, wave, nwaves,
+            team_row_bwd_two_pass<E, kMaxL, SHIFT, nt>(y, dy, dx, off[0], cols, t, wave, nwaves,
                                                    lane, which);
             which ^= 1;
         }
@@ -1312,102 +1183,13 @@ __device__ __forceinline__ uint32_t team_item_bwd(const typename E::T* y, const 
     return team_rows_of_wave(nrows, reps, wave, nwaves);
 }
 
-// long_row_bwd for a shifted row: the same two passes over the vectors that cover it (outside
-// elements read as 0, never written), staged when both streams' vectors fit the wave's LDS
-// region.
-template <class E, bool STAGE>
-__device__ __forceinline__ void long_row_bwd_shift(const typename E::T* y, const typename E::T* dy,
-                                                   typename E::T* dx, int64_t o, int cols,
-                                                   int lane, float* lds, int cap) {
-    constexpr int EPV = E::kEPV;
-    constexpr int CH = 16 / EPV;  // vectors per lane and stream per chunk (16 values)
-    constexpr int K = CH * EPV;
-    const RowVecs<E, true> rv(o, cols);
-    const int n = rv.nv;
-    const int span = n * EPV;  // floats of one stream staged
-    const bool stage = STAGE && 2 * span <= cap;
-    float s = 0.0f;
-    for (int first = lane; first < n; first += CH * 64) {
-        float a[K], g[K];
-        typename E::R ra[CH], rg[CH];
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int vi = first + c * 64;
-            ra[c] = vi < n ? E::load_raw(y + rv.start + vi * EPV) : E::raw_fill(0.0f);
-            rg[c] = vi < n ? E::load_raw(dy + rv.start + vi * EPV) : E::raw_fill(0.0f);
-        }
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int vi = first + c * 64;
-            E::unpack(ra[c], a + c * EPV);
-            E::unpack(rg[c], g + c * EPV);
-            rv.mask(vi, a + c * EPV, 0.0f);
-            rv.mask(vi, g + c * EPV, 0.0f);
-            if (stage && vi < n) {
-#pragma unroll
-                for (int i = 0; i < EPV; i += 4) {
-                    *reinterpret_cast<f32x4*>(lds + vi * EPV + i) =
-                        f32x4{a[c * EPV + i], a[c * EPV + i + 1], a[c * EPV + i + 2], a[c * EPV + i + 3]};
-                    *reinterpret_cast<f32x4*>(lds + span + vi * EPV + i) =
-                        f32x4{g[c * EPV + i], g[c * EPV + i + 1], g[c * EPV + i + 2], g[c * EPV + i + 3]};
-                }
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) g[k] *= a[k];
-        s += lane_reduce<K, OpAdd>(g);
-    }
-    const float d = group_reduce<64, OpAdd>(s);
-    for (int first = lane; first < n; first += CH * 64) {
-        float a[K], g[K];
-        if (stage) {
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int vi = first + c * 64;
-#pragma unroll
-                for (int i = 0; i < EPV; i += 4) {
-                    f32x4 va = f32x4{0.0f, 0.0f, 0.0f, 0.0f}, vg = va;
-                    if (vi < n) {
-                        va = *reinterpret_cast<const f32x4*>(lds + vi * EPV + i);
-                        vg = *reinterpret_cast<const f32x4*>(lds + span + vi * EPV + i);
-                    }
-                    a[c * EPV + i] = va.x; a[c * EPV + i + 1] = va.y;
-                    a[c * EPV + i + 2] = va.z; a[c * EPV + i + 3] = va.w;
-                    g[c * EPV + i] = vg.x; g[c * EPV + i + 1] = vg.y;
-                    g[c * EPV + i + 2] = vg.z; g[c * EPV + i + 3] = vg.w;
-                }
-            }
-        } else {
-            typename E::R ra[CH], rg[CH];
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                const int vi = first + c * 64;
-                ra[c] = vi < n ? E::load_raw(y + rv.start + vi * EPV) : E::raw_fill(0.0f);
-                rg[c] = vi < n ? E::load_raw(dy + rv.start + vi * EPV) : E::raw_fill(0.0f);
-            }
-#pragma unroll
-            for (int c = 0; c < CH; ++c) {
-                E::unpack(ra[c], a + c * EPV);
-                E::unpack(rg[c], g + c * EPV);
-            }
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) a[k] = a[k] * (g[k] - d);
-#pragma unroll
-        for (int c = 0; c < CH; ++c) {
-            const int vi = first + c * 64;
-            if (vi < n) rv.store(dx, vi, a + c * EPV);
-        }
-    }
-}
-
 template <class E, int KCLASS, bool VEC, bool SHIFT>
 __device__ __forceinline__ uint32_t dispatch_item_bwd(const typename E::T* y,
                                                       const typename E::T* dy, typename E::T* dx,
                                                       int64_t base, int cols, int nrows, int reps,
                                                       int64_t stride, int wave, int nwaves,
-                                                      int lane64, float* lds, int cap, bool team) {
-    const int nvec = VEC ? span_vecs<E, SHIFT>(cols) : (cols + E::kEPV - 1) / E::kEPV;
+                                                      int lane64, bool team) {
+    const int nvec = span_vecs<E>(cols);
     if constexpr (VEC && KCLASS >= 4) {
         // rows beyond the forward register tile: the workgroup's waves share each row
         if (team && nvec > 512)
@@ -1440,30 +1222,13 @@ __device__ __forceinline__ uint32_t dispatch_item_bwd(const typename E::T* y,
             BSM_TILE(64, 2, 1);
         }
         if constexpr (KCLASS >= 2) BSM_TILE(64, 4, 1);
-        if constexpr (F && KCLASS >= 3) BSM_TILE(64, 8, 1);
+        if constexpr (KCLASS >= 3) BSM_TILE(64, 8, 1);
 #undef BSM_TILE
     } else {
-        if (nvec <= 16) return BSM_RUN_BWD(16, 1, 1);
-        if (nvec <= 32) return BSM_RUN_BWD(32, 1, 1);
-        if (nvec <= 64) return BSM_RUN_BWD(64, 1, 1);
+        return BSM_RUN_BWD(16, 1, 1);  // rows shorter than a vector
     }
 #undef BSM_RUN_BWD
-    if constexpr (!VEC || KCLASS >= 3) {
-        uint32_t done = 0;
-        for (int k = 0; k < reps; ++k) {
-            for (int r = wave; r < nrows; r += nwaves) {
-                const int64_t o = base + k * stride + static_cast<int64_t>(r) * cols;
-                if constexpr (VEC && SHIFT)
-                    long_row_bwd_shift<E, (KCLASS >= 4)>(y, dy, dx, o, cols, lane64, lds, cap);
-                else
-                    long_row_bwd<E, VEC, (KCLASS >= 4)>(y + o, dy + o, dx + o, cols, lane64, lds,
-                                                        cap);
-                ++done;
-            }
-        }
-        return done;
-    }
-    return 0;  // unreachable: the item's access path is chosen so that its class covers it
+    return 0;  // unreachable: the plan's class covers its longest row
 }
 
 // Worker w of the table is workgroup w (all its waves share each item) or, when per_wave is
@@ -1473,8 +1238,7 @@ template <class E, int KCLASS, bool BWD, bool SHIFTED>
 __device__ __forceinline__ void worker_loop(const typename E::T* a, const typename E::T* b,
                                             typename E::T* out, const int32_t* __restrict__ worker_ptr,
                                             const bsm_item* __restrict__ items, int base_aligned,
-                                            int per_wave, int lds_floats_per_wave,
-                                            bsm_trace_rec* __restrict__ trace, float* lds_base) {
+                                            int per_wave, bsm_trace_rec* __restrict__ trace) {
     const int w = blockIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
     const int nwaves = static_cast<int>(blockDim.x) >> 6;
@@ -1483,7 +1247,6 @@ __device__ __forceinline__ void worker_loop(const typename E::T* a, const typena
     const int worker = per_wave ? w * nwaves + wave : w;
     const int my_wave = per_wave ? 0 : wave;
     const int my_nwaves = per_wave ? 1 : nwaves;
-    float* const lds = lds_base + wave * lds_floats_per_wave;
     uint32_t rows = 0;
     const int i0 = worker_ptr[worker];
     const int i1 = worker_ptr[worker + 1];
@@ -1493,32 +1256,29 @@ __device__ __forceinline__ void worker_loop(const typename E::T* a, const typena
         const int nrows = items[i].nrows;
         const int reps = items[i].reps;
         const int64_t stride = static_cast<int64_t>(items[i].rep_stride) * cols;
-        // Access path: whole 16-byte vectors when every row of the item starts and ends on
-        // one; shifted vectors when the buffers are aligned but the rows are not (in the
-        // instances for plans with such slices, SHIFTED, and as long as the kernel class has a
-        // tile or path for the extra vector); else element by element.
-        const bool rows_whole = ((base | static_cast<int64_t>(cols)) & (E::kEPV - 1)) == 0;
-        const int span = span_vecs<E, true>(cols);
-        const bool shift_fits = SHIFTED && (BWD ? (KCLASS >= 3 || span <= kClassMaxVecs<KCLASS>)
-                                                : span <= kClassMaxVecs<KCLASS>);
-        const int path = !base_aligned ? 0 : rows_whole ? 1 : shift_fits ? 2 : 0;
-#define BSM_ARGS_TAIL cols, nrows, reps, stride, my_wave, my_nwaves, lane64, lds, lds_floats_per_wave, !per_wave
+        // Access path: whole aligned 16-byte vectors when every row of the item starts and ends
+        // on one; in the instances for plans with other rows, or launches on buffers that are
+        // not 16-byte aligned (SHIFTED), vectors at element boundaries, and element by element
+        // rows shorter than a vector.
+        const bool whole = !SHIFTED ||
+            (base_aligned && ((base | static_cast<int64_t>(cols)) & (E::kEPV - 1)) == 0);
+#define BSM_ARGS cols, nrows, reps, stride, my_wave, my_nwaves, lane64
         if constexpr (BWD) {
-            if (path == 1)
-                rows += dispatch_item_bwd<E, KCLASS, true, false>(a, b, out, base, BSM_ARGS_TAIL);
-            else if (SHIFTED && path == 2)
-                rows += dispatch_item_bwd<E, KCLASS, true, SHIFTED>(a, b, out, base, BSM_ARGS_TAIL);
-            else
-                rows += dispatch_item_bwd<E, KCLASS, false, false>(a, b, out, base, BSM_ARGS_TAIL);
+            if (whole)
+                rows += dispatch_item_bwd<E, KCLASS, true, false>(a, b, out, base, BSM_ARGS, !per_wave);
+            else if (SHIFTED && cols >= E::kEPV)
+                rows += dispatch_item_bwd<E, KCLASS, true, SHIFTED>(a, b, out, base, BSM_ARGS, !per_wave);
+            else if constexpr (SHIFTED)
+                rows += dispatch_item_bwd<E, KCLASS, false, false>(a, b, out, base, BSM_ARGS, !per_wave);
         } else {
-            if (path == 1)
-                rows += dispatch_item<E, KCLASS, true, false>(a, out, base, BSM_ARGS_TAIL);
-            else if (SHIFTED && path == 2)
-                rows += dispatch_item<E, KCLASS, true, SHIFTED>(a, out, base, BSM_ARGS_TAIL);
-            else
-                rows += dispatch_item<E, KCLASS, false, false>(a, out, base, BSM_ARGS_TAIL);
+            if (whole)
+                rows += dispatch_item<E, KCLASS, true, false>(a, out, base, BSM_ARGS, !per_wave);
+            else if (SHIFTED && cols >= E::kEPV)
+                rows += dispatch_item<E, KCLASS, true, SHIFTED>(a, out, base, BSM_ARGS, !per_wave);
+            else if constexpr (SHIFTED)
+                rows += dispatch_item<E, KCLASS, false, false>(a, out, base, BSM_ARGS, !per_wave);
         }
-#undef BSM_ARGS_TAIL
+#undef BSM_ARGS
     }
     if (trace && lane64 == 0) {
         bsm_trace_rec rec;
@@ -1533,8 +1293,6 @@ __device__ __forceinline__ void worker_loop(const typename E::T* a, const typena
     }
 }
 
-extern __shared__ float bsm_lds[];  // lds_floats_per_wave floats per wave (long rows only)
-
 // Launch bounds: any workgroup size up to 1024 threads (128 VGPRs per lane); long-row plans run
 // workgroups of bsm::team_threads(class) threads (classes 4 and 5: 256, two or more per CU;
 // class 6: 512, one per CU), so their rows may hold up to 256 VGPRs per lane.  bf16 plans of
@@ -1548,14 +1306,15 @@ template <class E, int KCLASS>
 constexpr int kMinWavesPerSimd = (KCLASS >= 4 || (E::kBytes == 2 && KCLASS == 3)) ? 2 : 1;
 
 // SHIFTED: the instance for plans with slices whose rows do not start and end on 16-byte
-// vectors (kept apart so that the other plans' instances carry none of its registers).
+// vectors, and for buffers that are not 16-byte aligned (kept apart so that the other launches'
+// instances carry none of its registers).
 template <class E, int KCLASS, bool SHIFTED>
 __global__ void __launch_bounds__((kMaxThreads<E, KCLASS>), (kMinWavesPerSimd<E, KCLASS>))
 bsm_softmax_kernel(const typename E::T* in, typename E::T* out, const int32_t* __restrict__ worker_ptr,
                    const bsm_item* __restrict__ items, int base_aligned, int per_wave,
-                   int lds_floats_per_wave, bsm_trace_rec* __restrict__ trace) {
+                   bsm_trace_rec* __restrict__ trace) {
     worker_loop<E, KCLASS, false, SHIFTED>(in, nullptr, out, worker_ptr, items, base_aligned,
-                                           per_wave, lds_floats_per_wave, trace, bsm_lds);
+                                           per_wave, trace);
 }
 
 // dx = softmax backward of (y, dy) under the same work table.
@@ -1563,10 +1322,8 @@ template <class E, int KCLASS, bool SHIFTED>
 __global__ void __launch_bounds__((kMaxThreads<E, KCLASS>), (kMinWavesPerSimd<E, KCLASS>))
 bsm_softmax_bwd_kernel(const typename E::T* y, const typename E::T* dy, typename E::T* dx,
                        const int32_t* __restrict__ worker_ptr, const bsm_item* __restrict__ items,
-                       int base_aligned, int per_wave, int lds_floats_per_wave,
-                       bsm_trace_rec* __restrict__ trace) {
-    worker_loop<E, KCLASS, true, SHIFTED>(y, dy, dx, worker_ptr, items, base_aligned, per_wave,
-                                          lds_floats_per_wave, trace, bsm_lds);
+                       int base_aligned, int per_wave, bsm_trace_rec* __restrict__ trace) {
+    worker_loop<E, KCLASS, true, SHIFTED>(y, dy, dx, worker_ptr, items, base_aligned, per_wave, trace);
 }
 
 }  // namespace bsm_dev

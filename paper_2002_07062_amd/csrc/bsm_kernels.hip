@@ -31,16 +31,15 @@ __global__ void __launch_bounds__(256) bsm_copy_bytes_kernel(const unsigned char
         dst[i] = src[i];
 }
 
-// Both ops take (a, [b,] out, worker_ptr, items, aligned, per_wave, lds_floats, trace); the
+// Both ops take (a, [b,] out, worker_ptr, items, aligned, per_wave, trace); the
 // forward op has no b.
 hipError_t launch_fn(const void* fn, bool bwd, const void* a, const void* b, void* out,
                      const int32_t* worker_ptr, const bsm_item* items, int n_wg, int wg_threads,
-                     int aligned, int per_wave, int lds_floats, void* trace, hipStream_t stream) {
-    const size_t lds_bytes = static_cast<size_t>(lds_floats) * sizeof(float) * (wg_threads / 64);
-    void* args_fwd[] = {&a, &out, &worker_ptr, &items, &aligned, &per_wave, &lds_floats, &trace};
-    void* args_bwd[] = {&a, &b, &out, &worker_ptr, &items, &aligned, &per_wave, &lds_floats, &trace};
+                     int aligned, int per_wave, void* trace, hipStream_t stream) {
+    void* args_fwd[] = {&a, &out, &worker_ptr, &items, &aligned, &per_wave, &trace};
+    void* args_bwd[] = {&a, &b, &out, &worker_ptr, &items, &aligned, &per_wave, &trace};
     // hipLaunchKernel reports a failed launch itself, without touching the thread's last error
-    return hipLaunchKernel(fn, dim3(n_wg), dim3(wg_threads), bwd ? args_bwd : args_fwd, lds_bytes,
+    return hipLaunchKernel(fn, dim3(n_wg), dim3(wg_threads), bwd ? args_bwd : args_fwd, 0,
                            stream);
 }
 
@@ -57,9 +56,8 @@ const void* fn_for(bsm_dtype dtype, bool temporal, int kclass, bool shifted, boo
 
 namespace bsm {
 
-int kernel_class_for(int32_t max_cols, int elem_bytes, bool shifted) {
-    const int64_t nvec = (static_cast<int64_t>(max_cols) * elem_bytes + kVecBytes - 1) / kVecBytes +
-                         (shifted ? 1 : 0);
+int kernel_class_for(int32_t max_cols, int elem_bytes) {
+    const int64_t nvec = (static_cast<int64_t>(max_cols) * elem_bytes + kVecBytes - 1) / kVecBytes;
     if (nvec <= 32) return 0;
     if (nvec <= 128) return 1;  // rows of 33..64 vectors run 32 lanes x 2 vectors
     if (nvec <= 256) return 2;
@@ -73,44 +71,29 @@ int kernel_class_for(int32_t max_cols, int elem_bytes, bool shifted) {
 hipError_t launch_softmax(bsm_dtype dtype, int kernel_class, bool shifted, bool temporal,
                           const void* in, void* out, const int32_t* d_worker_ptr,
                           const bsm_item* d_items, int n_wg, int wg_threads, int per_wave,
-                          int lds_floats_per_wave, void* trace, hipStream_t stream) {
+                          void* trace, hipStream_t stream) {
     const int aligned = ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-    return launch_fn(fn_for(dtype, temporal, kernel_class, shifted, false), false, in, nullptr, out,
+    return launch_fn(fn_for(dtype, temporal, kernel_class, shifted || !aligned, false), false, in, nullptr, out,
                      d_worker_ptr, d_items, n_wg, wg_threads, aligned, per_wave,
-                     lds_floats_per_wave, trace, stream);
+                     trace, stream);
 }
 
 hipError_t launch_softmax_backward(bsm_dtype dtype, int kernel_class, bool shifted, bool temporal,
                                    const void* y, const void* dy, void* dx,
                                    const int32_t* d_worker_ptr, const bsm_item* d_items, int n_wg,
-                                   int wg_threads, int per_wave, int lds_floats_per_wave,
-                                   void* trace, hipStream_t stream) {
+                                   int wg_threads, int per_wave, void* trace, hipStream_t stream) {
     const int aligned = ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(dy) |
                           reinterpret_cast<uintptr_t>(dx)) & 15) == 0;
-    return launch_fn(fn_for(dtype, temporal, kernel_class, shifted, true), true, y, dy, dx,
+    return launch_fn(fn_for(dtype, temporal, kernel_class, shifted || !aligned, true), true, y, dy, dx,
                      d_worker_ptr, d_items, n_wg, wg_threads, aligned, per_wave,
-                     lds_floats_per_wave, trace, stream);
-}
-
-// Largest static LDS of the plan's instances (forward and backward, both cache policies).
-hipError_t static_lds_bytes(bsm_dtype dtype, int kernel_class, bool shifted, int* bytes) {
-    *bytes = 0;
-    for (int temporal = 0; temporal < 2; ++temporal)
-        for (int bwd = 0; bwd < 2; ++bwd) {
-            hipFuncAttributes a;
-            const hipError_t e =
-                hipFuncGetAttributes(&a, fn_for(dtype, temporal != 0, kernel_class, shifted, bwd != 0));
-            if (e != hipSuccess) return e;
-            if (static_cast<int>(a.sharedSizeBytes) > *bytes) *bytes = static_cast<int>(a.sharedSizeBytes);
-        }
-    return hipSuccess;
+                     trace, stream);
 }
 
 // Resident workgroups per CU of the plan's forward instance.
 hipError_t resident_wgs_per_cu(bsm_dtype dtype, int kernel_class, bool shifted, int wg_threads,
-                               size_t dyn_lds_bytes, int* n) {
+                               int* n) {
     return hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        n, fn_for(dtype, false, kernel_class, shifted, false), wg_threads, dyn_lds_bytes);
+        n, fn_for(dtype, false, kernel_class, shifted, false), wg_threads, 0);
 }
 
 hipError_t launch_copy(const void* src, void* dst, int64_t bytes, int n_cu, hipStream_t stream) {

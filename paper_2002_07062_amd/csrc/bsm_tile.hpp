@@ -76,11 +76,10 @@ constexpr Tile tile_for(int64_t nvec, int kclass, int elem_bytes, bool packed = 
 }
 
 // Register tile of the backward pass (two input streams, y and dy) for an aligned row of
-// `nvec` vectors; V = 0: the one-wave or workgroup paths.  bf16 rows keep half the forward
+// `nvec` vectors; V = 0: the workgroup path.  bf16 rows keep half the forward
 // pass's rows in flight.  fp32 rows, like the forward pass, keep about 4-5 KiB of both streams
-// per wave in flight where a power-of-two tile is partly empty, and rows of 257-512 vectors
-// keep a 64 x 8 register tile (the one-wave path, staging y and dy in LDS, ran them at
-// 3.7 TB/s).
+// per wave in flight where a power-of-two tile is partly empty.  Rows of 257-512 vectors keep a
+// 64 x 8 register tile (fp32 at 3.7 TB/s with y and dy staged in LDS by one wave instead).
 constexpr Tile tile_for_bwd(int64_t nvec, int kclass, int elem_bytes, bool packed = true) {
     const bool f = elem_bytes == 4;
     // plans of kernel class 0: rows of 5-7 vectors (fp32 also 9-10 and 17-21) in packed
@@ -100,7 +99,7 @@ constexpr Tile tile_for_bwd(int64_t nvec, int kclass, int elem_bytes, bool packe
         if (nvec <= 128) return Tile{64, 2, 1};
     }
     if (kclass >= 2 && nvec <= 256) return Tile{64, 4, 1};
-    if (f && kclass >= 3 && nvec <= 512) return Tile{64, 8, 1};
+    if (kclass >= 3 && nvec <= 512) return Tile{64, 8, 1};
     return Tile{64, 0, 1};
 }
 
