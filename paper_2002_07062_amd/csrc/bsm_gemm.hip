@@ -12,7 +12,7 @@ namespace {
 
 using bsm_mm::Shape;
 
-template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, int FORM>
+template <int MODE, bool BF16OUT, int OPS, bool TEMPORAL, int FORM>
 hipError_t launch_g(const void* a, const void* b, void* c, const Shape& s, const int32_t* worker_ptr,
                     const bsm_item* items, int n_wg, void* trace, hipStream_t stream) {
     const uint16_t* a_a = static_cast<const uint16_t*>(a);
@@ -25,7 +25,7 @@ hipError_t launch_g(const void* a, const void* b, void* c, const Shape& s, const
     const size_t lds = static_cast<size_t>(MODE == bsm_mm::kModeNtSoftmax1
                                                ? bsm_mm::s1_lds_bytes(BF16OUT, FORM == bsm_mm::kFormA2)
                                                : bsm_mm::wg_bytes<layout, FORM>(BF16OUT));
-    return hipLaunchKernel(reinterpret_cast<const void*>(&bsm_mm::bsm_gemm_kernel<MODE, BF16OUT, VEC, TEMPORAL, FORM>),
+    return hipLaunchKernel(reinterpret_cast<const void*>(&bsm_mm::bsm_gemm_kernel<MODE, BF16OUT, OPS, TEMPORAL, FORM>),
                            dim3(n_wg), dim3(bsm_mm::kGemmThreads), args, lds, stream);
 }
 
@@ -86,28 +86,37 @@ hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pas
     // the one-pass softmax takes alpha != 0 only (with alpha = 0 every logit is 0, which the
     // two-pass form handles)
     if (layout == kModeNtSoftmax && single_pass && vec && alpha != 0.0f && single_pass_shape(n, k)) {
-        if (k > kChunkK) BSM_G(kModeNtSoftmax1, true, kFormA2)
-        BSM_G(kModeNtSoftmax1, true, kFormA1)
+        if (k > kChunkK) BSM_G(kModeNtSoftmax1, kVec, kFormA2)
+        BSM_G(kModeNtSoftmax1, kVec, kFormA1)
+    }
+    if (s.k > 0 && (s.a_total < 8 || s.b_total < 8)) {
+#define BSM_GT(M)                                                                                              \
+    return bf16_out ? launch_g<M, true, kTiny, false, kFormStep>(a, b, c, s, d_worker_ptr, d_items, n_wg, trace, stream) \
+                    : launch_g<M, false, kTiny, false, kFormStep>(a, b, c, s, d_worker_ptr, d_items, n_wg, trace, stream)
+        if (layout == kNN) BSM_GT(kModeNn);
+        if (layout == kModeNtSoftmax) BSM_GT(kModeNtSoftmax);
+        BSM_GT(kModeNt);
+#undef BSM_GT
     }
     if (layout == kNN) {
-        if (form == kFormA1) BSM_G(kModeNn, true, kFormA1)
+        if (form == kFormA1) BSM_G(kModeNn, kVec, kFormA1)
         if (form == kFormWide) {
-            if (vec) BSM_G(kModeNn, true, kFormWide)
-            BSM_G(kModeNn, false, kFormWide)
+            if (vec) BSM_G(kModeNn, kVec, kFormWide)
+            BSM_G(kModeNn, kAny, kFormWide)
         }
-        if (vec) BSM_G(kModeNn, true, kFormStep)
-        BSM_G(kModeNn, false, kFormStep)
+        if (vec) BSM_G(kModeNn, kVec, kFormStep)
+        BSM_G(kModeNn, kAny, kFormStep)
     }
     if (layout == kModeNtSoftmax) {
-        if (form == kFormA1) BSM_G(kModeNtSoftmax, true, kFormA1)
-        if (form == kFormA2) BSM_G(kModeNtSoftmax, true, kFormA2)
-        if (vec) BSM_G(kModeNtSoftmax, true, kFormStep)
-        BSM_G(kModeNtSoftmax, false, kFormStep)
+        if (form == kFormA1) BSM_G(kModeNtSoftmax, kVec, kFormA1)
+        if (form == kFormA2) BSM_G(kModeNtSoftmax, kVec, kFormA2)
+        if (vec) BSM_G(kModeNtSoftmax, kVec, kFormStep)
+        BSM_G(kModeNtSoftmax, kAny, kFormStep)
     }
-    if (form == kFormA1) BSM_G(kModeNt, true, kFormA1)
-    if (form == kFormA2) BSM_G(kModeNt, true, kFormA2)
-    if (vec) BSM_G(kModeNt, true, kFormStep)
-    BSM_G(kModeNt, false, kFormStep)
+    if (form == kFormA1) BSM_G(kModeNt, kVec, kFormA1)
+    if (form == kFormA2) BSM_G(kModeNt, kVec, kFormA2)
+    if (vec) BSM_G(kModeNt, kVec, kFormStep)
+    BSM_G(kModeNt, kAny, kFormStep)
 #undef BSM_G
 }
 

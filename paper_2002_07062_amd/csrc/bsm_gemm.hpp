@@ -121,30 +121,32 @@ __device__ __forceinline__ unsigned pack_bf16(float a, float b) {
 
 // Eight consecutive bf16 of a row-major operand of `total` elements, from column c of the row
 // that starts at element `row` (rows of `len` elements).
-// VEC (len % 8 == 0, 16-byte aligned operands): one unconditional 16-byte load, from the row's
+// kVec (len % 8 == 0, 16-byte aligned operands): one unconditional 16-byte load, from the row's
 // last whole piece when c is past the row (the caller zeroes such pieces when it writes them to
 // LDS), so that no branch or select on the loaded data sits between a step's loads and the wait
 // before their use.
-// Otherwise (any len, any element-aligned operand): the same single load at its element
-// boundary.  It may run on into the following rows; the operand's last piece is loaded so that
-// it ends with the operand instead, and keep8 moves it into place.  Element loads, eight per
-// piece, took 105 us for the context product of 192 x (333 x 333)(333 x 64).  An operand of
-// fewer than eight elements is loaded element by element.
+// kAny (any len, any element-aligned operand of at least eight elements): the same single load
+// at its element boundary.  It may run on into the following rows; the operand's last piece is
+// loaded so that it ends with the operand instead, and keep8 moves it into place.  Element
+// loads, eight per piece, took 105 us for the context product of 192 x (333 x 333)(333 x 64).
+// kTiny (an operand has fewer than eight elements): element by element, in an instance of its
+// own: inside the others it made most of their code, and the product above took 32.6 us, now 24.3.
 // Ordinary (cache-resident) loads where the data is read again (B by every row round of its
 // batch, A by every column block), nontemporal (STREAM) where it is read once.
-template <bool VEC, bool STREAM = false>
+enum { kAny = 0, kVec = 1, kTiny = 2 };
+template <int OPS, bool STREAM = false>
 __device__ __forceinline__ u16x8 load8(const uint16_t* base, int64_t row, int c, int len, int64_t total) {
-    if constexpr (VEC) {
+    if constexpr (OPS == kVec) {
         const u16x8* p = reinterpret_cast<const u16x8*>(base + row + (c < len ? c : len - 8));
+        if constexpr (STREAM) return __builtin_nontemporal_load(p);
+        return *p;
+    } else if constexpr (OPS == kAny) {
+        const int64_t i = row + c;
+        const u16x8_any* p = reinterpret_cast<const u16x8_any*>(base + (i < total - 8 ? i : total - 8));
         if constexpr (STREAM) return __builtin_nontemporal_load(p);
         return *p;
     } else {
         const int64_t i = row + c;
-        if (total >= 8) {  // the same for every lane of the launch
-            const u16x8_any* p = reinterpret_cast<const u16x8_any*>(base + (i < total - 8 ? i : total - 8));
-            if constexpr (STREAM) return __builtin_nontemporal_load(p);
-            return *p;
-        }
         u16x8 v;
 #pragma unroll
         for (int e = 0; e < 8; ++e) v[e] = base[i + e < total ? i + e : total - 1];
@@ -153,21 +155,21 @@ __device__ __forceinline__ u16x8 load8(const uint16_t* base, int64_t row, int c,
 }
 
 // Zeroes the elements of a piece loaded by load8 that lie past `len`, or all of them when !ok.
-// VEC: the piece is wholly in or wholly out, four 32-bit selects.  Otherwise the piece may hold
+// kVec: the piece is wholly in or wholly out, four 32-bit selects.  Otherwise the piece may hold
 // any number of the row's elements (`whole`, the same for the wave: the step's columns all lie
 // inside the rows, so that only !ok is left), and the operand's last piece is first moved down
 // by the elements it was loaded early.
-template <bool VEC>
+template <int OPS>
 __device__ __forceinline__ u16x8 keep8(u16x8 v, int64_t row, int c, int len, int64_t total, bool ok, bool whole) {
     u32x4 w = __builtin_bit_cast(u32x4, v);
-    if (VEC || whole) {
+    if (OPS == kVec || whole) {
         const bool in = ok && (whole || c < len);
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = in ? w[e] : 0u;
         return __builtin_bit_cast(u16x8, w);
     }
     const int left = ok ? len - c : 0;  // the row's elements from the piece's first one on
-    const int64_t early = total >= 8 ? row + c - (total - 8) : 0;
+    const int64_t early = OPS == kAny ? row + c - (total - 8) : 0;
     if (early > 0 && left > 0) {  // early <= 7 here: the row has an element in the piece
         if (early & 4) w = u32x4{w[2], w[3], 0u, 0u};
         if (early & 2) w = u32x4{w[1], w[2], w[3], 0u};
@@ -222,7 +224,7 @@ __device__ __forceinline__ bf16x8 nn_row_operand(const uint16_t* lb, int t, int 
 
 // A's pieces of the reduction slice [k0, k0 + 64) of the wave's rows (a_row: element of the
 // first), and their LDS writes (rows past `rows` and columns past k zeroed).
-template <bool VEC>
+template <int OPS>
 __device__ __forceinline__ void load_a(const uint16_t* a, int64_t a_row, const Shape& s, int rows, int k0,
                                        int lane, bool stream, u16x8 (&pa)[kAPieces]) {
 #pragma unroll
@@ -230,59 +232,59 @@ __device__ __forceinline__ void load_a(const uint16_t* a, int64_t a_row, const S
         const int r = piece_row(lane, q);
         const int64_t row = a_row + static_cast<int64_t>(r < rows ? r : (rows > 0 ? rows - 1 : 0)) * s.k;
         const int c = k0 + piece_col(lane, q);
-        pa[q] = stream ? load8<VEC, true>(a, row, c, s.k, s.a_total) : load8<VEC, false>(a, row, c, s.k, s.a_total);
+        pa[q] = stream ? load8<OPS, true>(a, row, c, s.k, s.a_total) : load8<OPS, false>(a, row, c, s.k, s.a_total);
     }
 }
 
-template <bool VEC>
+template <int OPS>
 __device__ __forceinline__ void write_a(const u16x8 (&pa)[kAPieces], int64_t a_row, const Shape& s, int rows,
                                         int k0, int lane, uint16_t* la) {
 #pragma unroll
     for (int q = 0; q < kAPieces; ++q) {
         const int r = piece_row(lane, q), c = piece_col(lane, q);
         *reinterpret_cast<u16x8*>(la + r * kLdk + c) =
-            keep8<VEC>(pa[q], a_row + static_cast<int64_t>(r) * s.k, k0 + c, s.k, s.a_total, r < rows,
+            keep8<OPS>(pa[q], a_row + static_cast<int64_t>(r) * s.k, k0 + c, s.k, s.a_total, r < rows,
                        k0 + kChunkK <= s.k);
     }
 }
 
 // The wave's quarter of the B block of step (j0, k0): pieces q = kBPieces * wave + 0, 1, .. of
 // the block (B's rows j0.. for NT, B's rows k0.. for NN).  b_row: element of the batch's first.
-template <int LAYOUT, bool VEC, class G>
+template <int LAYOUT, int OPS, class G>
 __device__ __forceinline__ void load_step(const uint16_t* a, int64_t a_row, const uint16_t* b, int64_t b_row,
                                           const Shape& s, int rows, int j0, int k0, int wave,
                                           int lane, bool stream_a, Pieces<G>& p) {
-    if constexpr (!G::kAReg) load_a<VEC>(a, a_row, s, rows, k0, lane, stream_a, p.a);
+    if constexpr (!G::kAReg) load_a<OPS>(a, a_row, s, rows, k0, lane, stream_a, p.a);
 #pragma unroll
     for (int q = 0; q < G::kBPieces; ++q) {
         const int r = piece_row<G::kBCols>(lane, G::kBPieces * wave + q);
         const int c = piece_col<G::kBCols>(lane, G::kBPieces * wave + q);
         if constexpr (LAYOUT == kNT) {
             const int j = j0 + r;
-            p.b[q] = load8<VEC>(b, b_row + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k, k0 + c, s.k, s.b_total);
+            p.b[q] = load8<OPS>(b, b_row + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k, k0 + c, s.k, s.b_total);
         } else {
             const int kr = k0 + r;
-            p.b[q] = load8<VEC>(b, b_row + static_cast<int64_t>(kr < s.k ? kr : s.k - 1) * s.n, j0 + c, s.n, s.b_total);
+            p.b[q] = load8<OPS>(b, b_row + static_cast<int64_t>(kr < s.k ? kr : s.k - 1) * s.n, j0 + c, s.n, s.b_total);
         }
     }
 }
 
-template <int LAYOUT, bool VEC, class G>
+template <int LAYOUT, int OPS, class G>
 __device__ __forceinline__ void write_step(const Pieces<G>& p, int64_t a_row, int64_t b_row, const Shape& s,
                                            int rows, int j0, int k0, int wave, int lane, uint16_t* la,
                                            uint16_t* lb) {
-    if constexpr (!G::kAReg) write_a<VEC>(p.a, a_row, s, rows, k0, lane, la);
+    if constexpr (!G::kAReg) write_a<OPS>(p.a, a_row, s, rows, k0, lane, la);
 #pragma unroll
     for (int q = 0; q < G::kBPieces; ++q) {
         const int r = piece_row<G::kBCols>(lane, G::kBPieces * wave + q);
         const int c = piece_col<G::kBCols>(lane, G::kBPieces * wave + q);
         if constexpr (LAYOUT == kNT)
             *reinterpret_cast<u16x8*>(lb + r * G::kLdb + c) =
-                keep8<VEC>(p.b[q], b_row + static_cast<int64_t>(j0 + r) * s.k, k0 + c, s.k, s.b_total,
+                keep8<OPS>(p.b[q], b_row + static_cast<int64_t>(j0 + r) * s.k, k0 + c, s.k, s.b_total,
                            j0 + r < s.n, k0 + G::kStepK <= s.k);
         else
             *reinterpret_cast<u16x8*>(lb + r * G::kLdb + c) =
-                keep8<VEC>(p.b[q], b_row + static_cast<int64_t>(k0 + r) * s.n, j0 + c, s.n, s.b_total,
+                keep8<OPS>(p.b[q], b_row + static_cast<int64_t>(k0 + r) * s.n, j0 + c, s.n, s.b_total,
                            k0 + r < s.k, j0 + G::kN <= s.n);
     }
 }
@@ -391,7 +393,7 @@ __device__ __forceinline__ float half_pair(float v, int lane, F op) {
 // columns; the two lanes of a row exchange their maxima per block and add their sums at the
 // end).  The second pass recomputes the products and writes 2^(y - M) / sum.  Recomputing costs
 // matrix-core time, which these products have to spare; storing S would cost its bytes twice.
-template <int LAYOUT, bool BF16OUT, bool VEC, int FORM, bool TEMPORAL, bool SOFTMAX = false>
+template <int LAYOUT, bool BF16OUT, int OPS, int FORM, bool TEMPORAL, bool SOFTMAX = false>
 __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b, void* c,
                                            const Shape& s, int64_t bidx, int i0, int rows,
                                            int wave, int lane, uint16_t* lw, uint16_t* lbs,
@@ -420,10 +422,10 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
         u16x8 pa[kSlices][kAPieces];
 #pragma unroll
         for (int sl = 0; sl < kSlices; ++sl)
-            load_a<VEC>(a, a_row, s, rows, sl * kChunkK, lane, !TEMPORAL, pa[sl]);  // read once
+            load_a<OPS>(a, a_row, s, rows, sl * kChunkK, lane, !TEMPORAL, pa[sl]);  // read once
 #pragma unroll
         for (int sl = 0; sl < kSlices; ++sl) {
-            write_a<VEC>(pa[sl], a_row, s, rows, sl * kChunkK, lane, la);
+            write_a<OPS>(pa[sl], a_row, s, rows, sl * kChunkK, lane, la);
             wave_lds_sync();
 #pragma unroll
             for (int q = 0; q < kChunkK / kTileK; ++q)
@@ -438,7 +440,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
     // on the last step once it gets there (its loads are then issued again, unused).
     int ld_st = 0, ld_j = 0, ld_k = 0;
     auto load = [&](Pieces<G>& pp) {
-        load_step<LAYOUT, VEC, G>(a, a_row, b, b_row, s, rows, ld_j * G::kN, ld_k * kChunkK, wave, lane,
+        load_step<LAYOUT, OPS, G>(a, a_row, b, b_row, s, rows, ld_j * G::kN, ld_k * kChunkK, wave, lane,
                                   !TEMPORAL && nj == 1, pp);  // A read once when one column block
         if (ld_st + 1 < nall) {
             ++ld_st;
@@ -487,7 +489,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
         const int j0 = jb * G::kN;
         // lb (buffer st % 2) was last read at step st - 2; every wave finished that step
         // before the barrier of step st - 1, so one barrier per step orders both uses.
-        write_step<LAYOUT, VEC, G>(pp, a_row, b_row, s, rows, j0, kb * kChunkK, wave, lane, la, lb);
+        write_step<LAYOUT, OPS, G>(pp, a_row, b_row, s, rows, j0, kb * kChunkK, wave, lane, la, lb);
         __syncthreads();
         // issued on every step (past the last step: the last step's operands again, cache
         // hits, unused), so that every path has the same loads in flight
@@ -735,7 +737,7 @@ __device__ __forceinline__ void s1_load(const uint16_t* b, int64_t b_row, const 
     for (int q = 0; q < kS1BPieces; ++q) {
         const int qg = kS1BPieces * wave + q;
         const int j = j0 + piece_row(lane, qg);
-        p.b[q] = load8<true>(b, b_row + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k,
+        p.b[q] = load8<kVec>(b, b_row + static_cast<int64_t>(j < s.n ? j : s.n - 1) * s.k,
                              k0 + piece_col(lane, qg), s.k, s.b_total);
     }
 }
@@ -746,7 +748,7 @@ __device__ __forceinline__ void s1_write(const S1Pieces& p, const Shape& s, int 
     for (int q = 0; q < kS1BPieces; ++q) {
         const int qg = kS1BPieces * wave + q;
         const int r = piece_row(lane, qg), c = piece_col(lane, qg);
-        *reinterpret_cast<u16x8*>(lb + r * kLdk + c) = keep8<true>(p.b[q], 0, k0 + c, s.k, s.b_total, j0 + r < s.n, false);
+        *reinterpret_cast<u16x8*>(lb + r * kLdk + c) = keep8<kVec>(p.b[q], 0, k0 + c, s.k, s.b_total, j0 + r < s.n, false);
     }
 }
 
@@ -807,7 +809,7 @@ __device__ __forceinline__ void round_rows_s1(const uint16_t* a, const uint16_t*
     // ordinary loads, so that the second finds them in cache.
     u16x8 pa[NK][kAPieces];
 #pragma unroll
-    for (int kc = 0; kc < NK; ++kc) load_a<true>(a, a_row, s, rows, kc * kChunkK, lane, false, pa[kc]);
+    for (int kc = 0; kc < NK; ++kc) load_a<kVec>(a, a_row, s, rows, kc * kChunkK, lane, false, pa[kc]);
     S1Pieces p[kDepth];
     s1_load(b, b_row, s, sub_j0(0), sub_k0(0), wave, lane, p[0]);
     s1_load(b, b_row, s, sub_j0(nu > 1 ? 1 : 0), sub_k0(nu > 1 ? 1 : 0), wave, lane, p[1]);
@@ -820,7 +822,7 @@ __device__ __forceinline__ void round_rows_s1(const uint16_t* a, const uint16_t*
         for (int qq = 0; qq < kAPieces; ++qq) {
             const int r = piece_row(lane, qq), cc = piece_col(lane, qq);
             *reinterpret_cast<u16x8*>(lw + r * LDA + kc * kChunkK + cc) =
-                keep8<true>(pa[kc][qq], 0, kc * kChunkK + cc, s.k, s.a_total, r < rows, false);
+                keep8<kVec>(pa[kc][qq], 0, kc * kChunkK + cc, s.k, s.a_total, r < rows, false);
         }
     }
     wave_lds_sync();
@@ -976,7 +978,7 @@ constexpr int kWavesPerSimd = 3;
 // Worker loop: workgroup w runs its items; an item's rows are taken up to 128 at a time (cut
 // where a batch ends), 32 per wave (single-pass softmax: 64 at a time, 32 per wave pair).  Every bound of these loops is the same for the four
 // waves, so they meet the same barriers.
-template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, int FORM>
+template <int MODE, bool BF16OUT, int OPS, bool TEMPORAL, int FORM>
 __device__ __forceinline__ void gemm_worker(const uint16_t* a, const uint16_t* b, void* c,
                                             const Shape& s, const int32_t* __restrict__ worker_ptr,
                                             const bsm_item* __restrict__ items,
@@ -984,7 +986,7 @@ __device__ __forceinline__ void gemm_worker(const uint16_t* a, const uint16_t* b
     constexpr int kLayout = MODE == kModeNn ? kNN : kNT;
     constexpr bool kSoftmax = MODE == kModeNtSoftmax;
     constexpr bool kS1 = MODE == kModeNtSoftmax1;
-    static_assert(!kS1 || VEC, "the single-pass form is a 16-byte instance");
+    static_assert(!kS1 || OPS == kVec, "the single-pass form is a 16-byte instance");
     // single-pass instances: kFormA2 is the deep form (64 < k <= 128, A kept in LDS)
     constexpr bool kDeep = kS1 && FORM == kFormA2;
     constexpr int kRoundRows = kS1 ? kS1Rows : kWaves * kTileM;
@@ -1026,7 +1028,7 @@ __device__ __forceinline__ void gemm_worker(const uint16_t* a, const uint16_t* b
                     if (s.k == 0)
                         zero_rows<BF16OUT, kSoftmax>(c, s, bidx, i + row0, mine, lane);
                     else
-                        round_rows<kLayout, BF16OUT, VEC, FORM, TEMPORAL, kSoftmax>(
+                        round_rows<kLayout, BF16OUT, OPS, FORM, TEMPORAL, kSoftmax>(
                             a, b, c, s, bidx, i + row0, mine, wave, lane, lw, lbs, wg_done, seg, total_rows);
                 }
                 wg_done += seg;
@@ -1057,7 +1059,7 @@ constexpr int kGemmThreads = 64 * kWaves;
 // instead of nontemporal ones; a compile-time choice, so the default instance carries no
 // branch for it.
 //
-// The form of a launch.  A in registers takes aligned whole pieces (VEC) and pays from the
+// The form of a launch.  A in registers takes aligned whole pieces (kVec) and pays from the
 // second column block on; forms with a 128-wide B block need `wide`, that the plan's workgroups
 // per CU leave room for their LDS.
 constexpr int form_of(int mode, bool vec, bool wide, int n, int k) {
@@ -1077,12 +1079,12 @@ constexpr int waves_per_simd(int mode, int form) {
     return mode == kModeNtSoftmax1 || (mode == kModeNtSoftmax && form != kFormA1) || form == kFormWide
                ? kS1WavesPerSimd : kWavesPerSimd;
 }
-template <int MODE, bool BF16OUT, bool VEC, bool TEMPORAL, int FORM>
+template <int MODE, bool BF16OUT, int OPS, bool TEMPORAL, int FORM>
 __global__ void __launch_bounds__(kGemmThreads, waves_per_simd(MODE, FORM))
 bsm_gemm_kernel(const uint16_t* a, const uint16_t* b, void* c, Shape s,
                 const int32_t* __restrict__ worker_ptr, const bsm_item* __restrict__ items,
                 bsm_trace_rec* __restrict__ trace) {
-    gemm_worker<MODE, BF16OUT, VEC, TEMPORAL, FORM>(a, b, c, s, worker_ptr, items, trace, bsm_gemm_lds);
+    gemm_worker<MODE, BF16OUT, OPS, TEMPORAL, FORM>(a, b, c, s, worker_ptr, items, trace, bsm_gemm_lds);
 }
 
 }  // namespace bsm_mm

@@ -44,12 +44,13 @@ int64_t row_cost_of(const Topology& t, int elem_bytes, int32_t cols) {
 }
 
 // Appends a span, merging it into the previous one when it continues it in memory with the
-// same row length (adjacent slices of equal C form one longer run of rows).
-void push_span(std::vector<Span>* v, Span s) {
+// same row length (adjacent slices of equal C form one longer run of rows; with slice_elems > 0
+// only rows of one slice do).
+void push_span(std::vector<Span>* v, Span s, int64_t slice_elems = 0) {
     if (s.nrows <= 0) return;
     if (!v->empty()) {
         Span& b = v->back();
-        if (b.cols == s.cols && b.off + static_cast<int64_t>(b.nrows) * b.cols == s.off &&
+        if ((slice_elems == 0 || b.off / slice_elems == s.off / slice_elems) && b.cols == s.cols && b.off + static_cast<int64_t>(b.nrows) * b.cols == s.off &&
             static_cast<int64_t>(b.nrows) + s.nrows <= std::numeric_limits<int32_t>::max()) {
             b.nrows += s.nrows;
             return;
@@ -348,7 +349,7 @@ std::vector<std::vector<Span>> xcd_streams(const Geometry& g, const Topology& t,
         return Span{g.off[p.slice] + static_cast<int64_t>(p.row_begin) * g.C[p.slice], g.C[p.slice], p.nrows};
     };
     for (int x = 0; x < n; ++x)
-        for (const Piece& p : kept[x]) push_span(&stream[x], to_span(p));
+        for (const Piece& p : kept[x]) push_span(&stream[x], to_span(p), t.slice_elems);
     if (!pool.empty()) {
         std::vector<int64_t> deficit(static_cast<size_t>(n), 0);
         bool any = false;
@@ -375,7 +376,7 @@ std::vector<std::vector<Span>> xcd_streams(const Geometry& g, const Topology& t,
         std::vector<std::vector<Span>> recv;
         cut_stream(segments_of(pool_spans, t, es, 0, false), deficit, n, &recv);
         for (int x = 0; x < n; ++x)
-            for (const Span& s : recv[x]) push_span(&stream[x], s);
+            for (const Span& s : recv[x]) push_span(&stream[x], s, t.slice_elems);
         tab->stats.moved_cost = moved_cost;
         tab->stats.moved_bytes = moved_bytes;
         // Each XCD takes its rows in memory order, received ones included, so that the eight
@@ -384,7 +385,7 @@ std::vector<std::vector<Span>> xcd_streams(const Geometry& g, const Topology& t,
             std::vector<Span> v = std::move(stream[x]);
             std::sort(v.begin(), v.end(), [](const Span& a, const Span& b) { return a.off < b.off; });
             stream[x].clear();
-            for (const Span& sp : v) push_span(&stream[x], sp);
+            for (const Span& sp : v) push_span(&stream[x], sp, t.slice_elems);
         }
     }
     return stream;
@@ -581,7 +582,7 @@ std::string build_table(const Geometry& g, bsm_schedule schedule, const Topology
             per_worker.assign(static_cast<size_t>(P) * nw, {});
             std::vector<Span> stream;
             for (int64_t s = 0; s < g.batch; ++s)
-                if (g.R[s] > 0 && g.C[s] > 0) push_span(&stream, Span{g.off[s], g.C[s], g.R[s]});
+                if (g.R[s] > 0 && g.C[s] > 0) push_span(&stream, Span{g.off[s], g.C[s], g.R[s]}, t.slice_elems);
             // Order of the workers within a round, chosen by measurement on MI355X: for rows
             // in a register tile, XCD-major (each XCD takes one contiguous part of every round:
             // +7% on 16384 x 128 x 128, equal elsewhere); for long rows, workgroup order

@@ -36,6 +36,9 @@ struct Topology {
     // Rows per cutting unit (0: the softmax register-tile step for the row's length).  The
     // matrix-product kernels take rows 32 at a time.
     int32_t row_unit = 0;
+    // > 0: slices of this many elements, one after the other, whose units start over in every
+    // slice (0: units of the row stream, which may run on from one slice into the next).
+    int64_t slice_elems = 0;
     // XCD schedule: virtual banks as n_xcd equal contiguous ranges instead of interleaved chunks
     bool contiguous_banks = false;
     int32_t n_wg() const { return n_cu * wg_per_cu; }

@@ -473,3 +473,24 @@ def test_random_geometries_every_row_exactly_once(seed):
         assert d["n_wg"] == topo["n_cu"] * topo["wg_per_cu"]
         if schedule == "xcd":
             assert sum(d["xcd_bytes"][: topo["n_xcd"]]) == d["algorithmic_bytes"]
+
+
+@pytest.mark.parametrize("schedule", ["balanced", "xcd"])
+@pytest.mark.parametrize("layout,shape", [("nn", (50, 333, 64, 333)), ("nt_softmax", (40, 333, 200, 64)),
+                                          ("nn", (900, 5, 16, 40)), ("nt_softmax", (7, 129, 600, 128))])
+def test_rounds_of_nn_and_score_softmax_start_over_in_every_batch_index(layout, shape, schedule):
+    """Plans of the products whose rounds read all of B cut units within each batch index: every
+    row is covered once, and under BALANCED every piece starts at a batch's first row or at a
+    multiple of the rows a workgroup takes per round."""
+    batch, m, n, k = shape
+    topo = dict(n_cu=256, n_xcd=8, wg_per_cu=2, wg_threads=256)
+    p = bsm.bsm_gemm_plan_create(batch, m, n, k, layout, "bf16", schedule, topology=topo, device=-1)
+    ptr, items, _, _ = bsm.bsm_plan_export(p)
+    p.destroy()
+    offs = np.arange(batch, dtype=np.int64) * m * n
+    assert pc.check_exactly_once(ptr, items, offs, [m] * batch, [n] * batch) == []
+    if schedule == "balanced":
+        unit = 64 if layout == "nt_softmax" and 64 < n <= 512 else 128
+        for it in items:
+            starts = it["elem_offset"] // n + np.arange(it["reps"]) * it["rep_stride"]
+            assert np.all(starts % m % unit == 0)
