@@ -314,7 +314,10 @@ typedef enum {
      * of 1/n.  For 0 < k <= 128 and 64 < n <= 512 (16-byte rows and operands, alpha != 0) each
      * product is formed once and held in registers until its row's sum is known; such plans
      * default to 2 workgroups per CU and take rounds of 64 rows (a topology asking for 3 or
-     * more workgroups per CU keeps the two-pass form, whose rounds are 128 rows).  Otherwise
+     * more workgroups per CU keeps the two-pass form, whose rounds are 128 rows).  So it is for
+     * k <= 128 and 512 < n <= 2048, any operands, in rounds of 32 rows: plans default to 2
+     * workgroups per CU of 256 threads, for n > 1024 to one of 512 (a topology that names
+     * wg_threads, or asks for more workgroups per CU, keeps the two-pass form).  Otherwise
      * each round forms its products twice (row maximum and sum, then the probabilities). */
     BSM_GEMM_NT_SOFTMAX = 2,
     BSM_GEMM_LAYOUT_MAX_ENUM = 0x7FFFFFFF
@@ -322,7 +325,7 @@ typedef enum {
 
 /* Build a matrix-product plan (out_dtype is C's type; home_xcd, topology and device as for
  * bsm_plan_create; topology->wg_threads must be 0 or 256, wg_per_cu defaults to 3, or to
- * 2 for the one-pass form of BSM_GEMM_NT_SOFTMAX, for its two-pass form with 64 < k <= 128
+ * what BSM_GEMM_NT_SOFTMAX says for its one-pass forms, or to 2 for its two-pass form with 64 < k <= 128
  * (k % 8 == 0, n > 64) and for BSM_GEMM_NN with n > 64 and k > 64 or odd).  A plan
  * made here runs only with bsm_gemm_execute.  Its stats report per_wave 0 (worker =
  * workgroup). */

@@ -43,7 +43,7 @@ def _flags() -> list[str]:
 def build(verbose: bool = False) -> str:
     hipcc = _hipcc()
     sources = ["bsm_kernels.hip", "bsm_kernels_f32.hip", "bsm_kernels_f32_shifted.hip",
-               "bsm_kernels_bf16.hip", "bsm_kernels_bf16_shifted.hip", "bsm_gemm.hip",
+               "bsm_kernels_bf16.hip", "bsm_kernels_bf16_shifted.hip", "bsm_gemm.hip", "bsm_gemm_row.hip",
                "bsm_noalloc.hip", "bsm_api.cpp", "bsm_plan.cpp"]
     with tempfile.TemporaryDirectory(prefix="bsm_build_") as tmp:
         def compile_one(src: str) -> str:

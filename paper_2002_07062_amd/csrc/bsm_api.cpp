@@ -38,6 +38,7 @@ struct bsm_plan_s {
     bool gemm = false;
     int gemm_m = 0, gemm_n = 0, gemm_k = 0, gemm_layout = 0;
     bool gemm_single = false;  // layout 2 in one pass (products held in registers)
+    int gemm_row = 0;          // layout 2 by row-tile workgroups of this many waves
     bool gemm_wide = false;    // the CU's LDS holds its workgroups' 128-wide B blocks
     int64_t gemm_batch = 0;
     int32_t flags = 0;            // BSM_FLAG_* bits
@@ -436,10 +437,23 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     // (its LDS does not fit three), unless the topology asks for more.
     bsm_topology t{};
     if (topology) t = *topology;
-    const int wg_threads = bsm::gemm_wg_threads();
+    int wg_threads = bsm::gemm_wg_threads();
     if (t.wg_threads != 0 && t.wg_threads != wg_threads)
         return fail(BSM_ERR_INVALID_ARG, "matrix-product plans run %d-thread workgroups (got %d)",
                     wg_threads, t.wg_threads);
+    // Rows of 512 < n <= 2048 and k <= 128 run in one pass too, by workgroups of four waves (two
+    // per CU) or eight (one per CU) that share 32 rows, unless the topology names a workgroup size
+    // or asks for more workgroups.
+    int row = 0;
+    if (layout == BSM_GEMM_NT_SOFTMAX && k > 0 && k <= 128 && n > 512 && t.wg_threads == 0 &&
+        static_cast<int64_t>(batch) * m * k >= 8) {
+        const int q = n <= bsm::gemm_row_max_cols(4) ? 4 : 8;
+        if (n <= bsm::gemm_row_max_cols(q) && t.wg_per_cu <= 8 / q) row = q;
+    }
+    if (row > 0) {
+        wg_threads = 64 * row;
+        if (t.wg_per_cu == 0) t.wg_per_cu = 8 / row;
+    }
     const bool single = layout == BSM_GEMM_NT_SOFTMAX && bsm::gemm_single_pass_shape(n, k) &&
                         (t.wg_per_cu == 0 || t.wg_per_cu <= bsm::gemm_waves_per_simd(true));
     if (t.wg_per_cu == 0) t.wg_per_cu = bsm::gemm_default_wgs_per_cu(layout, n, k, single);
@@ -451,7 +465,7 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
         hipDeviceProp_t prop;
         if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
         if (e != hipSuccess) return hip_fail(e, "hipGetDeviceProperties");
-        const int64_t per_wg = bsm::gemm_lds_bytes_per_wg(bf16_out, single);
+        const int64_t per_wg = row > 0 ? bsm::gemm_row_lds_bytes_per_wg(row) : bsm::gemm_lds_bytes_per_wg(bf16_out, single);
         if (per_wg > static_cast<int64_t>(prop.sharedMemPerBlock) ||
             per_wg * t.wg_per_cu > static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor))
             return fail(BSM_ERR_INVALID_ARG, "wg_per_cu %d: %lld bytes of LDS per workgroup do not fit",
@@ -470,7 +484,7 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     // short and keep the row stream's blocks.
     const int64_t slice_elems = layout == BSM_GEMM_NT ? 0 : static_cast<int64_t>(m) * n;
     bsm_status st = create_plan(&p, nullptr, rows, cols, m == 0 || n == 0 ? 0 : batch, out_dtype,
-                                schedule, home_xcd, nullptr, &t, device, bsm::gemm_rows_per_wg(single), true,
+                                schedule, home_xcd, nullptr, &t, device, row > 0 ? 32 : bsm::gemm_rows_per_wg(single), true,
                                 upload, slice_elems);
     if (st != BSM_OK) return st;
     p->topo.wg_threads = wg_threads;
@@ -485,6 +499,7 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     p->gemm_k = k;
     p->gemm_layout = layout;
     p->gemm_single = single;
+    p->gemm_row = row;
     p->gemm_wide = wide;
     p->gemm_batch = batch;
     p->table.stats.algorithmic_bytes =
@@ -520,7 +535,12 @@ bsm_status execute_gemm(bsm_plan p, const void* a, const void* b, void* c, float
     if (e != hipSuccess) return hip_fail(e, "hipSetDevice");
     hipStream_t s = static_cast<hipStream_t>(stream);
     // k == 0 runs the same kernel: an empty reduction stores zeros
-    e = bsm::launch_gemm(p->gemm_layout, p->dtype == BSM_BF16, (p->flags & BSM_FLAG_TEMPORAL) != 0,
+    const bool bf16_out = p->dtype == BSM_BF16, temporal = (p->flags & BSM_FLAG_TEMPORAL) != 0;
+    if (p->gemm_row > 0)
+        e = bsm::launch_gemm_row(p->gemm_row, bf16_out, temporal, a, b, c, p->gemm_batch, p->gemm_m, p->gemm_n, p->gemm_k,
+                                 alpha, p->d_worker_ptr, p->d_items, p->topo.n_wg(), trace, s);
+    else
+        e = bsm::launch_gemm(p->gemm_layout, p->dtype == BSM_BF16, (p->flags & BSM_FLAG_TEMPORAL) != 0,
                          p->gemm_single, p->gemm_wide, a, b, c, p->gemm_batch, p->gemm_m, p->gemm_n,
                          p->gemm_k, alpha, p->d_worker_ptr, p->d_items, p->topo.n_wg(), trace, s);
     if (e != hipSuccess) return hip_fail(e, "kernel launch");

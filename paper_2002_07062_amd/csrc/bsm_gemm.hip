@@ -59,20 +59,9 @@ hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pas
                        const void* b, void* c, int64_t batch, int m, int n, int k, float alpha,
                        const int32_t* d_worker_ptr, const bsm_item* d_items, int n_wg, void* trace,
                        hipStream_t stream) {
-    Shape s;
-    s.m = m;
-    s.n = n;
-    s.k = k;
-    s.a_batch = static_cast<int64_t>(m) * k;
-    s.b_batch = static_cast<int64_t>(n) * k;
-    s.c_batch = static_cast<int64_t>(m) * n;
-    s.a_total = static_cast<int64_t>(batch) * s.a_batch;
-    s.b_total = static_cast<int64_t>(batch) * s.b_batch;
-    s.alpha = alpha;
-    // operands of aligned whole 16-byte pieces: rows of A (and NT's B) of k elements, rows of
-    // NN's B of n elements, both bases 16-byte aligned (C is stored at any element boundary)
-    const uintptr_t ptrs = reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b);
-    const bool vec = (ptrs & 15) == 0 && k % 8 == 0 && (layout != bsm_mm::kNN || n % 8 == 0);
+    const Shape s = bsm_mm::product_shape(batch, m, n, k, alpha);
+    // rows of A (and NT's B) have k elements, rows of NN's B n; C is stored at any boundary
+    const bool vec = bsm_mm::aligned_pieces(a, b, k) && (layout != bsm_mm::kNN || n % 8 == 0);
     const int form = bsm_mm::form_of(layout, vec, wide, n, k);
     const int out = (bf16_out ? 1 : 0) | (temporal ? 2 : 0);
 #define BSM_G(M, V, F)                                                                                        \

@@ -57,6 +57,16 @@ struct Shape {
     float alpha;
 };
 
+inline Shape product_shape(int64_t batch, int m, int n, int k, float alpha) {
+    const int64_t a = static_cast<int64_t>(m) * k, b = static_cast<int64_t>(n) * k;
+    return Shape{m, n, k, a, b, static_cast<int64_t>(m) * n, batch * a, batch * b, alpha};
+}
+
+// Both operands start on 16 bytes, and their rows of `len` elements are whole 16-byte pieces.
+inline bool aligned_pieces(const void* a, const void* b, int len) {
+    return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b)) & 15) == 0 && len % 8 == 0;
+}
+
 // One step of a workgroup: the output column block [j0, j0 + 64) and the reduction slice
 // [k0, k0 + 64).  LDS (bf16 elements unless noted): per wave, A block [32][kLdk], reused after
 // a column block's last step for the output block, [32][kLdc] fp32 or [32][kLdh] bf16; shared,
@@ -970,6 +980,18 @@ __device__ __forceinline__ void round_rows_s1(const uint16_t* a, const uint16_t*
     }
 }
 
+// One wave's trace record.
+__device__ __forceinline__ void write_trace(bsm_trace_rec* trace, int w, int wave, int waves, uint32_t rows, uint64_t t0) {
+    bsm_trace_rec rec;
+    rec.wg = static_cast<uint32_t>(w);
+    rec.xcc_id = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & 0xF;
+    rec.hw_id = __builtin_amdgcn_s_getreg(4 | (0 << 6) | ((32 - 1) << 11));
+    rec.rows = rows;
+    rec.t_start = t0;
+    rec.t_end = __builtin_amdgcn_s_memrealtime();
+    trace[static_cast<int64_t>(w) * waves + wave] = rec;
+}
+
 // Kernel modes (one compiled instance each): NT, NN, NT with the row softmax in two passes,
 // and in one pass (single_pass_shape).
 enum { kModeNt = 0, kModeNn = 1, kModeNtSoftmax = 2, kModeNtSoftmax1 = 3 };
@@ -1039,16 +1061,7 @@ __device__ __forceinline__ void gemm_worker(const uint16_t* a, const uint16_t* b
             }
         }
     }
-    if (trace && lane == 0) {
-        bsm_trace_rec rec;
-        rec.wg = static_cast<uint32_t>(w);
-        rec.xcc_id = __builtin_amdgcn_s_getreg(20 | (0 << 6) | ((4 - 1) << 11)) & 0xF;
-        rec.hw_id = __builtin_amdgcn_s_getreg(4 | (0 << 6) | ((32 - 1) << 11));
-        rec.rows = done;
-        rec.t_start = t0;
-        rec.t_end = __builtin_amdgcn_s_memrealtime();
-        trace[static_cast<int64_t>(w) * kWaves + wave] = rec;
-    }
+    if (trace && lane == 0) write_trace(trace, w, wave, kWaves, done, t0);
 }
 
 extern __shared__ uint16_t bsm_gemm_lds[];  // the form's LDS bytes per workgroup

@@ -63,6 +63,14 @@ hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pas
                        const int32_t* d_worker_ptr, const bsm_item* d_items, int n_wg, void* trace,
                        hipStream_t stream);
 
+// The score softmax by row-tile workgroups of q = 4 or 8 waves (64 q threads, 32 rows per round):
+// 0 < k <= 128, n <= gemm_row_max_cols(q), operands of at least eight elements.
+int gemm_row_lds_bytes_per_wg(int q);
+int gemm_row_max_cols(int q);
+hipError_t launch_gemm_row(int q, bool bf16_out, bool temporal, const void* a, const void* b, void* c, int64_t batch,
+                           int m, int n, int k, float alpha, const int32_t* d_worker_ptr, const bsm_item* d_items,
+                           int n_wg, void* trace, hipStream_t stream);
+
 // Workgroups of the plan's forward instance that fit on one CU at once (registers and LDS).
 hipError_t resident_wgs_per_cu(bsm_dtype dtype, int kernel_class, bool shifted, int wg_threads,
                                int* n);

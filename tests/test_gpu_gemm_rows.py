@@ -1,0 +1,71 @@
+"""GPU parity of the score softmax by row-tile workgroups (512 < n <= 2048, k <= 128) against the
+fp64 oracle: both workgroup sizes at the edges of their columns, reductions that do and do not
+fill their slices, partial row tiles, several rounds per workgroup, operands at any element
+boundary, negative and zero scale, and infinities in columns that are not there."""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2002_07062_amd as bsm
+from gpu_util import bits_to_f64
+from test_gpu_gemm import _dev_bf16, _operands
+from test_gpu_gemm_forms import _product
+from test_gpu_gemm_softmax import _check
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(2, 33, 513, 1), (3, 31, 700, 72), (2, 65, 1024, 64), (1, 40, 1025, 128), (2, 32, 2048, 65),
+          (1, 1, 1999, 100), (1, 5, 2047, 127), (9, 200, 600, 8)]
+
+
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_row_tiles_against_the_oracle(shape, out):
+    batch, m, n, k = shape
+    print(f"[rows {shape} {out}]", flush=True)
+    a, b = _operands(batch, m, n, k, seed=500 + n)
+    a_d, b_d = _dev_bf16(a), _dev_bf16(b)
+    for alpha in (0.125, -0.125, 0.0):
+        got = _product(shape, "nt_softmax", out, a_d, b_d, alpha)
+        _check(got, a, b, batch, m, n, k, alpha, out)
+    want = _product(shape, "nt_softmax", out, a_d, b_d, 0.125)
+    for schedule in ("rr", "xcd"):
+        assert np.array_equal(_product(shape, "nt_softmax", out, a_d, b_d, 0.125, schedule=schedule), want)
+    few = {"n_cu": 3, "n_xcd": 1, "flags": bsm.BSM_FLAG_TEMPORAL}  # many rounds per workgroup
+    assert np.array_equal(_product(shape, "nt_softmax", out, a_d, b_d, 0.125, topology=few), want)
+    odd = [torch.cat([torch.zeros(3, device="cuda", dtype=torch.bfloat16), t])[3:] for t in (a_d, b_d)]
+    assert np.array_equal(_product(shape, "nt_softmax", out, *odd, 0.125), want)
+
+
+@pytest.mark.parametrize("n,k", [(520, 72), (1100, 64)])
+def test_infinite_operands(n, k):
+    """-inf, +inf and NaN in one row of B reach the row's column only as the softmax says: a
+    logit of -inf is a probability of 0, one of +inf or NaN makes its row NaN; the last row of B,
+    that stands in for rows past n, is -inf."""
+    m = 40
+    a = np.abs(_operands(1, m, n, k, seed=7)[0].astype(np.int32) & 0x7FFF).astype(np.uint16)  # positive
+    b = _operands(1, m, n, k, seed=8)[1].copy()
+    b.reshape(n, k)[[3, n - 1]] = 0xFF80
+    a_d, b_d = _dev_bf16(a), _dev_bf16(b)
+    got = bits_to_f64(_product((1, m, n, k), "nt_softmax", "f32", a_d, b_d, 0.01)).reshape(m, n)
+    assert np.all(got[:, [3, n - 1]] == 0.0) and np.allclose(got.sum(1), 1.0, atol=1e-5)
+    b.reshape(n, k)[5, 0] = 0x7F80
+    got = bits_to_f64(_product((1, m, n, k), "nt_softmax", "f32", a_d, _dev_bf16(b), 0.01))
+    assert np.all(np.isnan(got))
+
+
+def test_plan_takes_the_row_tiles():
+    """Workgroups of four waves up to 1024 columns, of eight up to 2048; a topology that names
+    a workgroup size or more workgroups, longer rows and longer reductions keep the general form."""
+    def describe(n, k, topology=None):
+        p = bsm.bsm_gemm_plan_create(8, 64, n, k, "nt_softmax", "bf16", topology=topology, device=0)
+        st = bsm.bsm_plan_describe(p)
+        p.destroy()
+        return st["wg_threads"], st["n_wg"] // torch.cuda.get_device_properties(0).multi_processor_count
+
+    assert describe(513, 64) == (256, 2) and describe(1024, 128) == (256, 2)
+    assert describe(1025, 64) == (512, 1) and describe(2048, 128) == (512, 1)
+    assert describe(2049, 128) == (256, 2) and describe(1100, 136) == (256, 3)
+    assert describe(600, 64, {"wg_threads": 256}) == (256, 3) and describe(1100, 64, {"wg_threads": 256}) == (256, 3)
+    assert describe(1100, 64, {"wg_per_cu": 2}) == (256, 2)
