@@ -299,7 +299,10 @@ bsm_status bsm_softmax_backward(const void* y, const void* dy, void* dx,
  * attention -- scores (512 x 64) x (64 x 512) and context (512 x 512) x (512 x 64), batch 384 --
  * scheduled by the same tables: the outputs C_b are the slices (m rows of n), cut by RR,
  * BALANCED or XCD as for the softmax, with one worker per workgroup (256 threads) and pieces
- * of whole 128-row blocks (the rows a workgroup takes per round, 32 per wave).
+ * of whole 128-row blocks (the rows a workgroup takes per round, 32 per wave).  Shapes that leave
+ * such rounds few or partly empty, and others where it is faster, run by row-tile workgroups
+ * instead, in rounds of 32 rows whose columns (NN: reduction) the waves split; a topology that
+ * names wg_threads keeps the 128-row rounds.
  *   BSM_GEMM_NT:  C_b = alpha * A_b * B_b^T    A_b m x k,  B_b n x k  (scores Q K^T)
  *   BSM_GEMM_NN:  C_b = alpha * A_b * B_b      A_b m x k,  B_b k x n  (context P V)
  * All operands row-major, batch after batch (A_b at b*m*k, B_b at b*n*k, C_b at b*m*n
@@ -315,7 +318,8 @@ typedef enum {
      * product is formed once and held in registers until its row's sum is known; such plans
      * default to 2 workgroups per CU and take rounds of 64 rows (a topology asking for 3 or
      * more workgroups per CU keeps the two-pass form, whose rounds are 128 rows).  So it is for
-     * k <= 128 and 512 < n <= 2048, any operands, in rounds of 32 rows: plans default to 2
+     * k <= 128 and 512 < n <= 2048, and for shapes of fewer columns with few rows, any operands,
+     * in rounds of 32 rows: plans default to 2
      * workgroups per CU of 256 threads, for n > 1024 to one of 512 (a topology that names
      * wg_threads, or asks for more workgroups per CU, keeps the two-pass form).  Otherwise
      * each round forms its products twice (row maximum and sum, then the probabilities). */
@@ -324,8 +328,9 @@ typedef enum {
 } bsm_gemm_layout;
 
 /* Build a matrix-product plan (out_dtype is C's type; home_xcd, topology and device as for
- * bsm_plan_create; topology->wg_threads must be 0 or 256, wg_per_cu defaults to 3, or to
- * what BSM_GEMM_NT_SOFTMAX says for its one-pass forms, or to 2 for its two-pass form with 64 < k <= 128
+ * bsm_plan_create; topology->wg_threads must be 0 or 256, wg_per_cu defaults to 3 (1
+ * for row tiles that number no more than 256), or to what BSM_GEMM_NT_SOFTMAX says for its
+ * one-pass forms, or to 2 for its two-pass form with 64 < k <= 128
  * (k % 8 == 0, n > 64) and for BSM_GEMM_NN with n > 64 and k > 64 or odd).  A plan
  * made here runs only with bsm_gemm_execute.  Its stats report per_wave 0 (worker =
  * workgroup). */

@@ -39,6 +39,7 @@ struct bsm_plan_s {
     int gemm_m = 0, gemm_n = 0, gemm_k = 0, gemm_layout = 0;
     bool gemm_single = false;  // layout 2 in one pass (products held in registers)
     int gemm_row = 0;          // layout 2 by row-tile workgroups of this many waves
+    int gemm_parts = 0;        // layouts 0 and 1 by row-tile workgroups, so many to a worker's rows
     bool gemm_wide = false;    // the CU's LDS holds its workgroups' 128-wide B blocks
     int64_t gemm_batch = 0;
     int32_t flags = 0;            // BSM_FLAG_* bits
@@ -441,14 +442,15 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     if (t.wg_threads != 0 && t.wg_threads != wg_threads)
         return fail(BSM_ERR_INVALID_ARG, "matrix-product plans run %d-thread workgroups (got %d)",
                     wg_threads, t.wg_threads);
-    // Rows of 512 < n <= 2048 and k <= 128 run in one pass too, by workgroups of four waves (two
-    // per CU) or eight (one per CU) that share 32 rows, unless the topology names a workgroup size
-    // or asks for more workgroups.
-    int row = 0;
-    if (layout == BSM_GEMM_NT_SOFTMAX && k > 0 && k <= 128 && n > 512 && t.wg_threads == 0 &&
-        static_cast<int64_t>(batch) * m * k >= 8) {
-        const int q = n <= bsm::gemm_row_max_cols(4) ? 4 : 8;
-        if (n <= bsm::gemm_row_max_cols(q) && t.wg_per_cu <= 8 / q) row = q;
+    // Row-tile workgroups, where they are the faster form, unless the topology names a workgroup
+    // size (or, for the score softmax, asks for more workgroups than fit).
+    int row = 0, parts = 0;
+    if (t.wg_threads == 0 && batch > 0 && m > 0 && n > 0 && k > 0) {
+        if (layout == BSM_GEMM_NT_SOFTMAX) row = bsm::gemm_row_softmax_waves(batch, m, n, k);
+        else parts = bsm::gemm_row_parts(layout, out_dtype == BSM_BF16, batch, m, n, k);
+        if (row > 0 && t.wg_per_cu > 8 / row) row = 0;
+        // one row tile per workgroup or less: no second and third workgroup per CU without any
+        if (parts > 0 && t.wg_per_cu == 0 && batch * ((m + 31) / 32) <= 256) t.wg_per_cu = 1;
     }
     if (row > 0) {
         wg_threads = 64 * row;
@@ -482,9 +484,9 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     // NN and the score softmax, which read all of B in every round, therefore cut whole batch
     // indices (192 x (333 x 333)(333 x 64): 36.6 -> 32.6 us); the plain scores' rounds are
     // short and keep the row stream's blocks.
-    const int64_t slice_elems = layout == BSM_GEMM_NT ? 0 : static_cast<int64_t>(m) * n;
+    const int64_t slice_elems = layout == BSM_GEMM_NT && parts == 0 ? 0 : static_cast<int64_t>(m) * n;
     bsm_status st = create_plan(&p, nullptr, rows, cols, m == 0 || n == 0 ? 0 : batch, out_dtype,
-                                schedule, home_xcd, nullptr, &t, device, row > 0 ? 32 : bsm::gemm_rows_per_wg(single), true,
+                                schedule, home_xcd, nullptr, &t, device, row > 0 || parts > 0 ? 32 : bsm::gemm_rows_per_wg(single), true,
                                 upload, slice_elems);
     if (st != BSM_OK) return st;
     p->topo.wg_threads = wg_threads;
@@ -500,6 +502,7 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     p->gemm_layout = layout;
     p->gemm_single = single;
     p->gemm_row = row;
+    p->gemm_parts = parts;
     p->gemm_wide = wide;
     p->gemm_batch = batch;
     p->table.stats.algorithmic_bytes =
@@ -539,6 +542,9 @@ bsm_status execute_gemm(bsm_plan p, const void* a, const void* b, void* c, float
     if (p->gemm_row > 0)
         e = bsm::launch_gemm_row(p->gemm_row, bf16_out, temporal, a, b, c, p->gemm_batch, p->gemm_m, p->gemm_n, p->gemm_k,
                                  alpha, p->d_worker_ptr, p->d_items, p->topo.n_wg(), trace, s);
+    else if (p->gemm_parts > 0)
+        e = bsm::launch_gemm_few_rows(p->gemm_layout, p->gemm_parts, bf16_out, temporal, a, b, c, p->gemm_batch, p->gemm_m,
+                                      p->gemm_n, p->gemm_k, alpha, p->d_worker_ptr, p->d_items, p->topo.n_wg(), trace, s);
     else
         e = bsm::launch_gemm(p->gemm_layout, p->dtype == BSM_BF16, (p->flags & BSM_FLAG_TEMPORAL) != 0,
                          p->gemm_single, p->gemm_wide, a, b, c, p->gemm_batch, p->gemm_m, p->gemm_n,

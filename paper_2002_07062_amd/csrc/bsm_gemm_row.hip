@@ -1,6 +1,7 @@
 // Host launch wrapper of the row-tile matrix products (device code in bsm_gemm_row.hpp).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstdint>
 
 #include "bsm.h"
@@ -46,12 +47,78 @@ hipError_t pick_ops(Launch& l, int q, bool temporal, bool vec) {
     return vec ? pick_temporal<BF16OUT, kVec>(l, q, temporal) : pick_temporal<BF16OUT, kAny>(l, q, temporal);
 }
 
+template <int LAYOUT, bool BF16OUT, int OPS, bool TEMPORAL, int NK>
+hipError_t launch_few(Launch& l, int parts) {
+    void* args[] = {&l.a, &l.b, &l.c, &l.s, &l.worker_ptr, &l.items, &l.trace};
+    return hipLaunchKernel(reinterpret_cast<const void*>(&bsm_gemm_few_rows_kernel<LAYOUT, BF16OUT, OPS, TEMPORAL, NK>),
+                           dim3(l.n_wg, parts), dim3(64 * kRowWaves), args, few_rows_lds_bytes(LAYOUT), l.stream);
+}
+template <bool BF16OUT, int OPS, bool TEMPORAL>
+hipError_t pick_layout(Launch& l, int parts, int layout) {
+    if (layout == kNN) return launch_few<kNN, BF16OUT, OPS, TEMPORAL, 1>(l, parts);
+    return l.s.k <= kChunkK ? launch_few<kNT, BF16OUT, OPS, TEMPORAL, 1>(l, parts)
+                            : launch_few<kNT, BF16OUT, OPS, TEMPORAL, 2>(l, parts);
+}
+template <bool BF16OUT>
+hipError_t pick_few(Launch& l, int parts, int layout, bool temporal, bool vec) {
+    if (vec)
+        return temporal ? pick_layout<BF16OUT, kVec, true>(l, parts, layout) : pick_layout<BF16OUT, kVec, false>(l, parts, layout);
+    return temporal ? pick_layout<BF16OUT, kAny, true>(l, parts, layout) : pick_layout<BF16OUT, kAny, false>(l, parts, layout);
+}
+
 }  // namespace
 
 namespace bsm {
 
 int gemm_row_lds_bytes_per_wg(int q) { return row_lds_bytes(q); }
-int gemm_row_max_cols(int q) { return row_max_cols(q); }
+
+// us below: the other form -> row tiles.
+int gemm_row_softmax_waves(int64_t batch, int m, int n, int k) {
+    // the 16-byte loads need eight elements per operand
+    if (k > 2 * kChunkK || n > row_max_cols(8) || batch * std::min(m, n) * k < 8) return 0;
+    const int64_t tiles = batch * ((m + kTileM - 1) / kTileM);  // of 32 rows
+    const int blocks = (n + kBlockN - 1) / kBlockN;             // of 64 columns
+    // Past 512 columns the other form takes two passes.
+    if (!single_pass_shape(n, k) && n > kBlockN) return n <= row_max_cols(4) ? 4 : 8;
+    // One column block (the other form: two passes of 128-row rounds; here one wave of four
+    // works): where the chip is not full of rounds, or they are mostly empty.  1000 x 30 x 60
+    // 23.6 -> 8.5, 40 x 500 x 60 (k = 128) 20.9 -> 9.3, 100 x 500 x 40 20.1 -> 13.9; past the line
+    // 100 x 1000 x 50 25.8 -> 28.4, 2000 x 200 x 64 58 -> 67.
+    if (n <= kBlockN) return m <= kTileM || batch * ((m + 127) / 128) <= 512 ? 4 : 0;
+    // Up to 512 columns the other form is one pass of 64-row rounds by wave pairs, which splits
+    // the columns over two waves.  Four must not leave more of them idle (1000 x 33 x 300
+    // 22.4 -> 27.5, 2000 x 128 x 128 34 -> 43), and win where the rounds do not fill the chip a few times
+    // (16 x 512 x 512 13.4 -> 8.7, 96 x 512 x 512 20.6 -> 17.1; 192 x 512 x 512 (k = 128) 40 -> 45, 384 x 512 x 512
+    // 65 -> 71) or where rows are not whole 128-byte lines, whose halves the waves then
+    // store at about the same time (1000 x 128 x 500 77 -> 61, 1000 x 64 x 200 19.0 -> 17.4).
+    const int64_t rounds = batch * ((m + kS1Rows - 1) / kS1Rows);
+    if (tiles * ((blocks + 3) / 4) > rounds * ((blocks + 1) / 2)) return 0;
+    return rounds <= 800 || m <= kTileM || n % kBlockN != 0 ? 4 : 0;
+}
+
+int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k) {
+    if (batch * std::min(m, n) * k < 8 || (layout == kNT && k > 2 * kChunkK)) return 0;
+    const int64_t tiles = batch * ((m + kTileM - 1) / kTileM);
+    const int64_t blocks = (n + kBlockN - 1) / kBlockN;
+    const int64_t rounds = batch * ((m + 127) / 128);  // of the general form
+    if (layout == kNT) {
+        // The general form keeps full rounds of bf16 rows of whole 128-byte lines, once they
+        // fill the chip (384 x 512 x 512 44 -> 54, 200 x 512 x 512 25.1 -> 27.7, 400 x 256 x 256 (k = 128)
+        // 22.4 -> 26.5; B is staged once for 128 rows).  Otherwise row tiles: fewer rounds
+        // (96 x 512 x 512 17.9 -> 11.9, 4 x 2048 x 2048 (k = 128) 48 -> 12), partly empty ones (512 x 16 x 936
+        // 142 -> 30, 800 x 65 x 500 44 -> 34), lines that two blocks share, here stored at about the
+        // same time (1000 x 128 x 300 62 -> 38, 300 x 333 x 333 57 -> 38), fp32 (384 x 512 x 512 78.7 -> 72.8).
+        if (bf16_out && n % kBlockN == 0 && rounds >= 768 && 4 * rounds * 10 <= 13 * tiles) return 0;
+    } else {
+        // NN's waves split the reduction, A is read once per 64 columns and B once per 32 rows:
+        // for few tiles.  us at tiles x blocks: 504 (4 x (2000 x 2000)(2000 x 128)) 58 -> 20, 800
+        // (200 x (128 x 500)(500 x 64)) 24.6 -> 14.9, 876 33.6 -> 29.9, 1000 16.5 -> 19.5, 1024 27 -> 31, 1512 32 -> 37.
+        if (tiles * blocks > 896) return 0;
+    }
+    // column parts until three workgroups per CU have rows, at least four blocks (NN: one) to a part
+    const int64_t most = layout == kNT ? (blocks + kRowWaves - 1) / kRowWaves : blocks;
+    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({most, 8, 768 / tiles})));
+}
 
 hipError_t launch_gemm_row(int q, bool bf16_out, bool temporal, const void* a, const void* b, void* c, int64_t batch,
                            int m, int n, int k, float alpha, const int32_t* d_worker_ptr, const bsm_item* d_items,
@@ -61,6 +128,16 @@ hipError_t launch_gemm_row(int q, bool bf16_out, bool temporal, const void* a, c
              static_cast<bsm_trace_rec*>(trace), n_wg, stream};
     const bool vec = aligned_pieces(a, b, k);
     return bf16_out ? pick_ops<true>(l, q, temporal, vec) : pick_ops<false>(l, q, temporal, vec);
+}
+
+hipError_t launch_gemm_few_rows(int layout, int parts, bool bf16_out, bool temporal, const void* a, const void* b, void* c,
+                                int64_t batch, int m, int n, int k, float alpha, const int32_t* d_worker_ptr,
+                                const bsm_item* d_items, int n_wg, void* trace, hipStream_t stream) {
+    Launch l{static_cast<const uint16_t*>(a), static_cast<const uint16_t*>(b), c,
+             product_shape(batch, m, n, k, alpha), d_worker_ptr, d_items,
+             static_cast<bsm_trace_rec*>(trace), n_wg, stream};
+    const bool vec = aligned_pieces(a, b, k) && (layout != kNN || n % 8 == 0);
+    return bf16_out ? pick_few<true>(l, parts, layout, temporal, vec) : pick_few<false>(l, parts, layout, temporal, vec);
 }
 
 }  // namespace bsm

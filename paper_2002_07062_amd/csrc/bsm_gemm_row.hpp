@@ -1,8 +1,11 @@
 // Matrix products by row-tile workgroups: the Q waves of a workgroup share one 32-row tile of
 // the output and split its columns; wave q takes the 64-column blocks q, q + Q, ..  Each wave
 // streams its own columns of B through its own LDS region (no other wave reads them, so the
-// stream meets no barrier) against the tile's rows of A, kept in LDS; k <= 128.
+// stream meets no barrier) against the tile's rows of A; k <= 128.  The 32-row tiles make four times the
+// workgroups of the general form's 128-row rounds, and the four waves work on any of them.
 //
+//   NT: each block is stored as it comes.
+//   NN: the waves split the reduction instead and add their sums at the end.
 //   NT + softmax: the products of a row stay in registers until it is done, for n <= 256 Q.
 //   The two-pass form forms every product and every exponential twice, with a barrier at every
 //   64 columns.  us, two passes -> this: 237 x (241 x 64)(64 x 920) bf16 99 -> 56, 64 x (1000 x 64)
@@ -18,6 +21,7 @@ namespace bsm_mm {
 
 constexpr int kRowMaxBlocks = 4;  // 64-column blocks a wave holds (128 registers)
 constexpr int kRowPieces = kBlockN * kChunkK / 8 / 64;  // 16-byte pieces per lane of a 64 x 64 chunk of B
+constexpr int kRowWaves = 4;      // waves of the plain products' workgroups
 // a wave's LDS: the chunk; A's and the output's staging reuse it
 constexpr int kRowWaveBytes = kBlockN * kLdk * 2;
 static_assert(kRowWaveBytes >= kTileM * Geo<kNT, kFormA1>::kLdc * 4, "fp32 output staging fits the chunk");
@@ -292,6 +296,189 @@ __device__ __forceinline__ uint32_t row_softmax_worker(const uint16_t* a, const 
     }
 }
 
+// Worker of the plain scores (NT, k <= 128): as above, each block stored as soon as its products
+// are there.  The columns may be split over `slots` waves of several workgroups: `slot` is this
+// wave's.
+template <bool BF16OUT, int OPS, bool TEMPORAL, int NK, int Q>
+__device__ __forceinline__ uint32_t row_nt_worker(const uint16_t* a, const uint16_t* b, void* c, const Shape& s,
+                                                  Rounds rounds, int wave, int lane, int slot, int slots,
+                                                  uint16_t* lw, uint16_t* la) {
+    const int li = lane & 31;
+    const int h = lane >> 5;
+    const int nj = (s.n + kBlockN - 1) / kBlockN;
+    uint32_t done = 0;
+    int64_t bidx;
+    int i0, rows;
+    while (rounds.next(s, bidx, i0, rows)) {
+        u16x8 p[kRowPieces];
+        const uint16_t* base;
+        int end;
+        auto load_b = [&](int jb, int kc) {
+            const int64_t at = bidx * s.b_batch + static_cast<int64_t>(jb * kBlockN) * s.k;
+            base = b + at;
+            const int64_t to_end = s.b_total - 8 - at;
+            end = to_end < (1 << 24) ? static_cast<int>(to_end) : (1 << 24);
+            row_load<OPS>(base, s, jb * kBlockN, kc * kChunkK, end, here(lane), p);
+        };
+        if (slot < nj) load_b(slot, 0);
+        __syncthreads();  // the previous round's A is consumed
+#pragma unroll
+        for (int q = 0; q < 8 * NK * kTileM / (64 * Q); ++q) {
+            const int e = here(lane) + 64 * wave + 64 * Q * q;
+            const int r = e / (8 * NK), col = e % (8 * NK) * 8;
+            const int64_t row = bidx * s.a_batch + static_cast<int64_t>(i0 + (r < rows ? r : rows - 1)) * s.k;
+            *reinterpret_cast<u16x8*>(la + r * kRowLda<NK> + col) =
+                keep8<OPS>(load8<OPS>(a, row, col, s.k, s.a_total), row, col, s.k, s.a_total, r < rows,
+                           false);
+        }
+        __syncthreads();
+        u16x8 a_reg[NK * (kChunkK / kTileK)];
+#pragma unroll
+        for (int q = 0; q < NK * (kChunkK / kTileK); ++q)
+            a_reg[q] = *reinterpret_cast<const u16x8*>(la + li * kRowLda<NK> + q * kTileK + 8 * h);
+        for (int jb = slot; jb < nj; jb += slots) {
+            f32x16 acc[kBlockTiles];
+#pragma unroll
+            for (int kc = 0; kc < NK; ++kc) {
+                row_write<OPS>(p, s, jb * kBlockN, kc * kChunkK, end, here(lane), lw);
+                wave_lds_sync();
+                if (kc + 1 < NK) load_b(jb, kc + 1);
+                else if (jb + slots < nj) load_b(jb + slots, 0);
+#pragma unroll
+                for (int kk = 0; kk < kChunkK; kk += kTileK) {
+                    const bf16x8 av = __builtin_bit_cast(bf16x8, a_reg[(kc * kChunkK + kk) / kTileK]);
+#pragma unroll
+                    for (int t = 0; t < kBlockTiles; ++t) {
+                        const bf16x8 bv = __builtin_bit_cast(
+                            bf16x8, *reinterpret_cast<const u16x8*>(lw + (t * kTileN + li) * kLdk + kk + 8 * h));
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                            bv, av, (kc == 0 && kk == 0) ? f32x16{} : acc[t], 0, 0, 0);
+                    }
+                }
+                wave_lds_sync();
+            }
+            const int left = s.n - jb * kBlockN;
+            s1_store_block<BF16OUT, TEMPORAL>(acc, s.alpha, c, s, bidx, i0, rows, jb * kBlockN,
+                                              left < kBlockN ? left : kBlockN, here(lane), lw);
+        }
+        if (wave == 0) done += static_cast<uint32_t>(rows);
+    }
+    return done;
+}
+
+// Worker of the context product (NN): wave q of Q takes the 64-deep slices q, q + Q, .. of the
+// reduction for all 32 rows and one 64-column block, and the Q partial sums meet in LDS.
+struct RowNnGeo {
+    static constexpr bool kAReg = false;
+    static constexpr int kStepK = kChunkK;
+    static constexpr int kN = kBlockN;
+    static constexpr int kBCols = kBlockN;
+    static constexpr int kLdb = kBlockN + 8;
+    static constexpr int kBPieces = kRowPieces;
+};
+constexpr int kRowNnA = kTileM * kLdk * 2;  // bytes of a wave's A slice
+constexpr int kRowNnWaveBytes = kRowNnA + kChunkK * RowNnGeo::kLdb * 2;
+constexpr int kRowLdc = kBlockN + 4;        // floats, the partial sums' row
+static_assert(kRowNnWaveBytes >= kTileM * kRowLdc * 4, "a wave's partial sums fit its region");
+
+constexpr int few_rows_lds_bytes(int layout) {
+    return layout == kNN ? kRowWaves * kRowNnWaveBytes : kRowWaves * kRowWaveBytes + kTileM * kRowLda<2> * 2;
+}
+
+template <bool BF16OUT, int OPS, bool TEMPORAL, int Q>
+__device__ __forceinline__ uint32_t row_nn_worker(const uint16_t* a, const uint16_t* b, void* c, const Shape& s,
+                                                  Rounds rounds, int wave, int lane, int jb0, int jbs, uint16_t* lds) {
+    const int li = lane & 31;
+    const int h = lane >> 5;
+    uint16_t* const la = lds + wave * (kRowNnWaveBytes / 2);
+    uint16_t* const lb = la + kRowNnA / 2;
+    const int nk = (s.k + kChunkK - 1) / kChunkK;
+    uint32_t done = 0;
+    int64_t bidx;
+    int i0, rows;
+    while (rounds.next(s, bidx, i0, rows)) {
+        const int64_t a_row = bidx * s.a_batch + static_cast<int64_t>(i0) * s.k;
+        const int64_t b_row = bidx * s.b_batch;
+        for (int j0 = jb0 * kBlockN; j0 < s.n; j0 += jbs * kBlockN) {
+            f32x16 acc[kBlockTiles] = {f32x16{}, f32x16{}};
+            Pieces<RowNnGeo> p;
+            auto load = [&](int kc) {
+                load_step<kNN, OPS, RowNnGeo>(a, a_row, b, b_row, s, rows, j0, kc * kChunkK, 0, here(lane), false, p);
+            };
+            if (wave < nk) load(wave);
+            for (int kc = wave; kc < nk; kc += Q) {
+                write_step<kNN, OPS, RowNnGeo>(p, a_row, b_row, s, rows, j0, kc * kChunkK, 0, here(lane), la, lb);
+                wave_lds_sync();
+                if (kc + Q < nk) load(kc + Q);
+#pragma unroll
+                for (int kk = 0; kk < kChunkK; kk += kTileK) {
+                    const bf16x8 av = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(la + li * kLdk + kk + 8 * h));
+#pragma unroll
+                    for (int t = 0; t < kBlockTiles; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(nn_row_operand<RowNnGeo::kLdb>(lb, t, kk, lane),
+                                                                         av, acc[t], 0, 0, 0);
+                }
+                wave_lds_sync();
+            }
+            // the partial sums, as rows, over the wave's own slices
+            float* const part = reinterpret_cast<float*>(la);
+#pragma unroll
+            for (int t = 0; t < kBlockTiles; ++t)
+#pragma unroll
+                for (int g = 0; g < 4; ++g)
+                    *reinterpret_cast<f32x4*>(part + li * kRowLdc + t * kTileN + 8 * g + 4 * h) =
+                        f32x4{acc[t][4 * g], acc[t][4 * g + 1], acc[t][4 * g + 2], acc[t][4 * g + 3]};
+            __syncthreads();
+            // wave q adds rows 8 q .. 8 q + 7 (Q = 4), eight lanes of eight columns per row
+            static_assert(kTileM == 8 * Q, "the waves share the tile's rows");
+            const int r = 8 * wave + (lane >> 3), col = (lane & 7) * 8;
+            f32x4 v[2] = {};
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const float* from = reinterpret_cast<const float*>(lds + q * (kRowNnWaveBytes / 2)) + r * kRowLdc + col;
+                v[0] += *reinterpret_cast<const f32x4*>(from);
+                v[1] += *reinterpret_cast<const f32x4*>(from + 4);
+            }
+            v[0] *= s.alpha;
+            v[1] *= s.alpha;
+            const int left = s.n - j0 - col;  // columns from this lane's first one on
+            const int64_t at = bidx * s.c_batch + static_cast<int64_t>(i0 + r) * s.n + j0 + col;
+            if (r < rows && left > 0) {
+                if constexpr (BF16OUT) {
+                    uint16_t* const cp = static_cast<uint16_t*>(c) + at;
+                    const u32x4 w{pack_bf16(v[0][0], v[0][1]), pack_bf16(v[0][2], v[0][3]),
+                                  pack_bf16(v[1][0], v[1][1]), pack_bf16(v[1][2], v[1][3])};
+                    if (left >= 8) {
+                        if constexpr (TEMPORAL) *reinterpret_cast<u32x4_any*>(cp) = w;
+                        else __builtin_nontemporal_store(w, reinterpret_cast<u32x4_any*>(cp));
+                    } else {
+                        const u16x8 e8 = __builtin_bit_cast(u16x8, w);
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (e < left) cp[e] = e8[e];
+                    }
+                } else {
+                    float* const cp = static_cast<float*>(c) + at;
+                    if (left >= 8) {
+#pragma unroll
+                        for (int e = 0; e < 2; ++e) {
+                            if constexpr (TEMPORAL) reinterpret_cast<f32x4_any*>(cp)[e] = v[e];
+                            else __builtin_nontemporal_store(v[e], reinterpret_cast<f32x4_any*>(cp) + e);
+                        }
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e)
+                            if (e < left) cp[e] = v[e / 4][e % 4];
+                    }
+                }
+            }
+            __syncthreads();  // the sums are read before the regions are written again
+        }
+        if (wave == 0) done += static_cast<uint32_t>(rows);
+    }
+    return done;
+}
+
 extern __shared__ uint16_t bsm_gemm_row_lds[];  // row_lds_bytes(Q)
 
 // Two waves per SIMD: the held products take 128 registers.
@@ -310,6 +497,30 @@ bsm_gemm_row_kernel(const uint16_t* a, const uint16_t* b, void* c, Shape s,
     const Rounds rounds{items, worker_ptr[w], worker_ptr[w + 1], kTileM};
     const uint32_t done = row_softmax_worker<BF16OUT, OPS, TEMPORAL, NK, Q>(a, b, c, s, rounds, wave, lane, lw, la, lstat);
     if (trace && lane == 0) write_trace(trace, w, wave, Q, done, t0);
+}
+
+// The plain products: gridDim.y parts of the columns of every worker's rows; only the first
+// leaves a trace.
+template <int LAYOUT, bool BF16OUT, int OPS, bool TEMPORAL, int NK>
+__global__ void __launch_bounds__(64 * kRowWaves, kWavesPerSimd)
+bsm_gemm_few_rows_kernel(const uint16_t* a, const uint16_t* b, void* c, Shape s,
+                         const int32_t* __restrict__ worker_ptr, const bsm_item* __restrict__ items,
+                         bsm_trace_rec* __restrict__ trace) {
+    constexpr int Q = kRowWaves;
+    const int w = blockIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6);
+    const int lane = static_cast<int>(threadIdx.x) & 63;
+    const uint64_t t0 = trace ? __builtin_amdgcn_s_memrealtime() : 0;
+    const Rounds rounds{items, worker_ptr[w], worker_ptr[w + 1], kTileM};
+    uint32_t done;
+    if constexpr (LAYOUT == kNT)
+        done = row_nt_worker<BF16OUT, OPS, TEMPORAL, NK, Q>(a, b, c, s, rounds, wave, lane, Q * blockIdx.y + wave,
+                                                            Q * gridDim.y, bsm_gemm_row_lds + wave * (kRowWaveBytes / 2),
+                                                            bsm_gemm_row_lds + Q * (kRowWaveBytes / 2));
+    else
+        done = row_nn_worker<BF16OUT, OPS, TEMPORAL, Q>(a, b, c, s, rounds, wave, lane, blockIdx.y, gridDim.y,
+                                                        bsm_gemm_row_lds);
+    if (trace && lane == 0 && blockIdx.y == 0) write_trace(trace, w, wave, Q, done, t0);
 }
 
 }  // namespace bsm_mm

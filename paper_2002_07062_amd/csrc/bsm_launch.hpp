@@ -64,12 +64,20 @@ hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pas
                        hipStream_t stream);
 
 // The score softmax by row-tile workgroups of q = 4 or 8 waves (64 q threads, 32 rows per round):
-// 0 < k <= 128, n <= gemm_row_max_cols(q), operands of at least eight elements.
+// gemm_row_softmax_waves says which q a shape takes, 0 for none.
 int gemm_row_lds_bytes_per_wg(int q);
-int gemm_row_max_cols(int q);
+int gemm_row_softmax_waves(int64_t batch, int m, int n, int k);
 hipError_t launch_gemm_row(int q, bool bf16_out, bool temporal, const void* a, const void* b, void* c, int64_t batch,
                            int m, int n, int k, float alpha, const int32_t* d_worker_ptr, const bsm_item* d_items,
                            int n_wg, void* trace, hipStream_t stream);
+
+// NT and NN by row-tile workgroups (gemm_wg_threads() threads, 32 rows per round).  parts:
+// workgroups that share a worker's rows, each with its own columns; gemm_row_parts says how many
+// a shape takes, 0 for the general form.
+int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k);
+hipError_t launch_gemm_few_rows(int layout, int parts, bool bf16_out, bool temporal, const void* a, const void* b, void* c,
+                                int64_t batch, int m, int n, int k, float alpha, const int32_t* d_worker_ptr,
+                                const bsm_item* d_items, int n_wg, void* trace, hipStream_t stream);
 
 // Workgroups of the plan's forward instance that fit on one CU at once (registers and LDS).
 hipError_t resident_wgs_per_cu(bsm_dtype dtype, int kernel_class, bool shifted, int wg_threads,

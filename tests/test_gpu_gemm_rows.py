@@ -1,5 +1,5 @@
-"""GPU parity of the score softmax by row-tile workgroups (512 < n <= 2048, k <= 128) against the
-fp64 oracle: both workgroup sizes at the edges of their columns, reductions that do and do not
+"""GPU parity of the products by row-tile workgroups, and of the general forms on the shapes they
+take, against the fp64 oracle.  The score softmax (k <= 128, n <= 2048): both workgroup sizes at the edges of their columns, reductions that do and do not
 fill their slices, partial row tiles, several rounds per workgroup, operands at any element
 boundary, negative and zero scale, and infinities in columns that are not there."""
 
@@ -9,7 +9,9 @@ import torch
 
 import paper_2002_07062_amd as bsm
 from gpu_util import bits_to_f64
+from test_gpu_gemm import _check as check_product
 from test_gpu_gemm import _dev_bf16, _operands
+from test_gpu_gemm_forms import SHAPES as FORM_SHAPES
 from test_gpu_gemm_forms import _product
 from test_gpu_gemm_softmax import _check
 
@@ -69,3 +71,48 @@ def test_plan_takes_the_row_tiles():
     assert describe(2049, 128) == (256, 2) and describe(1100, 136) == (256, 3)
     assert describe(600, 64, {"wg_threads": 256}) == (256, 3) and describe(1100, 64, {"wg_threads": 256}) == (256, 3)
     assert describe(1100, 64, {"wg_per_cu": 2}) == (256, 2)
+
+
+# row tiles of one and several rounds, columns split over several workgroups, reductions of fewer
+# slices than waves and of more, the operand's last piece
+PLAIN = [("nt", (2, 33, 65, 72)), ("nt", (1, 1, 2050, 128)), ("nt", (5, 40, 300, 1)), ("nt", (3, 97, 511, 127)),
+         ("nt", (900, 3, 130, 40)), ("nn", (2, 33, 65, 130)), ("nn", (1, 31, 513, 64)), ("nn", (4, 70, 96, 333)),
+         ("nn", (3, 5, 7, 600)), ("nn", (1, 64, 128, 8)), ("nn", (700, 2, 64, 65))]
+
+
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+@pytest.mark.parametrize("layout,shape", PLAIN, ids=lambda s: s if isinstance(s, str) else "x".join(map(str, s)))
+def test_plain_row_tiles_against_the_oracle(layout, shape, out):
+    batch, m, n, k = shape
+    print(f"[plain rows {layout} {shape} {out}]", flush=True)
+    a, b = _operands(batch, m, n, k, seed=600 + n)
+    a_d, b_d = _dev_bf16(a), _dev_bf16(b)
+    want = _product(shape, layout, out, a_d, b_d, 0.25)
+    check_product(want, a, b, batch, m, n, k, layout, out, 0.25)
+    for topology in ({"n_cu": 3, "n_xcd": 1, "flags": bsm.BSM_FLAG_TEMPORAL}, {"wg_per_cu": 4 if out == "bf16" else 3}):
+        assert np.array_equal(_product(shape, layout, out, a_d, b_d, 0.25, topology=topology), want)
+    for schedule in ("rr", "xcd"):
+        assert np.array_equal(_product(shape, layout, out, a_d, b_d, 0.25, schedule=schedule), want)
+    odd = [torch.cat([torch.zeros(3, device="cuda", dtype=torch.bfloat16), t])[3:] for t in (a_d, b_d)]
+    assert np.array_equal(_product(shape, layout, out, *odd, 0.25), want)
+
+
+@pytest.mark.parametrize("out", ["f32", "bf16"])
+@pytest.mark.parametrize("layout", ["nt", "nn", "nt_softmax"])
+@pytest.mark.parametrize("shape", FORM_SHAPES + [(2, 70, 520, 128), (2, 70, 700, 72)], ids=lambda s: "x".join(map(str, s)))
+def test_general_forms_on_small_shapes(shape, layout, out):
+    """A topology that names the workgroup size keeps the general forms: the small shapes that
+    row tiles take by default, through every one of them."""
+    batch, m, n, k = shape
+    print(f"[general {layout} {shape} {out}]", flush=True)
+    a, b = _operands(batch, m, n, k, seed=700 + m + n)
+    a_d, b_d = _dev_bf16(a), _dev_bf16(b)
+    alpha = 1.0 / np.sqrt(k)
+    got = _product(shape, layout, out, a_d, b_d, alpha, topology={"wg_threads": 256})
+    if layout == "nt_softmax":
+        _check(got, a, b, batch, m, n, k, alpha, out)
+    else:
+        check_product(got, a, b, batch, m, n, k, layout, out, alpha)
+    assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha, topology={"wg_threads": 256}, schedule="rr"), got)
+    if layout == "nt":  # the same sums in the same order
+        assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha), got)
