@@ -319,9 +319,9 @@ typedef enum {
      * default to 2 workgroups per CU and take rounds of 64 rows (a topology asking for 3 or
      * more workgroups per CU keeps the two-pass form, whose rounds are 128 rows).  So it is for
      * k <= 128 and 512 < n <= 2048, and for shapes of fewer columns with few rows, any operands,
-     * in rounds of 32 rows: plans default to 2
-     * workgroups per CU of 256 threads, for n > 1024 to one of 512 (a topology that names
-     * wg_threads, or asks for more workgroups per CU, keeps the two-pass form).  Otherwise
+     * in rounds of 32 rows: plans default to 2 workgroups per CU of 256 threads, for n > 1024
+     * to one of 512 (a topology that names wg_threads, or asks for more workgroups per CU,
+     * keeps the forms above).  Otherwise
      * each round forms its products twice (row maximum and sum, then the probabilities). */
     BSM_GEMM_NT_SOFTMAX = 2,
     BSM_GEMM_LAYOUT_MAX_ENUM = 0x7FFFFFFF
