@@ -688,7 +688,7 @@ __device__ __forceinline__ void team_row_two_pass(const typename E::T* in, typen
         team_unpack<E, L>(raw, x);
         team_mask<E, L, SHIFT, NT>(rv, t, s0, x, kNegInf);
         const float cm = lane_reduce<K, OpMax>(x);
-        if (cm > m) {
+        if (!(cm <= m)) {  // a larger maximum, or NaN, which the sum then keeps
             s *= __builtin_amdgcn_exp2f((m - cm) * kLog2e);
             m = cm;
         }

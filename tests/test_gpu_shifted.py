@@ -77,3 +77,31 @@ def test_special_values_among_duplicates(dtype):
     bits = to_host_bits(out)
     compare(bits, ref, dtype, mask & ~nan_rows)
     assert np.all(np.isnan(bits_to_f64(bits)[nan_rows]))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_nan_anywhere_in_rows_read_twice(dtype):
+    """Rows of more than 32768 elements, aligned and shifted: a NaN in a lane's first vectors, in
+    its last ones, or after vectors that are all masked makes the whole row NaN, and only that row."""
+    cols = [32776, 32769, 40001]
+    w = workloads.custom([5] * len(cols), cols, dtype=dtype, sigma=1.0, seed=61, gap=1, base=8)
+    x = bits_to_f64(w.x) if dtype == "bf16" else w.x.astype(np.float64)
+    nan_rows = np.zeros(x.size, bool)
+    for o, c in zip(w.offsets, cols):
+        r = x[o:o + 5 * c].reshape(5, c)
+        r[0, 5] = np.nan
+        r[0, 6] = 30.0               # the row's maximum, in the same lane
+        r[1, c - 1] = np.nan
+        r[2, :32768] = -np.inf
+        r[2, c - 1] = np.nan
+        r[3, :32768] = -np.inf       # no NaN: the probabilities of the rest
+        nan_rows[o:o + 3 * c] = True
+    t = torch.from_numpy(x.astype(np.float32)).to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    host = t.numpy() if dtype == "f32" else t.view(torch.int16).numpy().view(np.uint16)
+    ref = oracle.softmax(host, dtype, w.offsets[: w.batch], w.rows, w.cols)
+    mask = covered_mask(w.offsets[: w.batch], w.rows, w.cols, x.size)
+    out, st = run_plan(w, "balanced", x=t.cuda())
+    assert st["kernel_class"] == 6
+    bits = to_host_bits(out)
+    compare(bits, ref, dtype, mask & ~nan_rows)
+    assert np.all(np.isnan(bits_to_f64(bits)[nan_rows]))
