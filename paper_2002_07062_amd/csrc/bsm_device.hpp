@@ -304,7 +304,8 @@ __device__ __forceinline__ float row_sum(const RowVecs<E, SHIFT, STRIDE, V>& rv,
     }
 }
 
-// The same for the products a g (lane_dot's tree).
+// The same for the products a g (lane_dot's tree).  Both factors of a duplicate are left out: an
+// infinite one times 0 would make the sum NaN.
 template <class E, int V, bool SHIFT, int STRIDE>
 __device__ __forceinline__ float row_dot(const RowVecs<E, SHIFT, STRIDE, V>& rv, int i, const float* a, const float* g) {
     constexpr int EPV = E::kEPV;
@@ -316,10 +317,13 @@ __device__ __forceinline__ float row_dot(const RowVecs<E, SHIFT, STRIDE, V>& rv,
         for (int v = 0; v < V; ++v) {
             if (v == (V > 1 ? 1 : 0)) {
                 const int d = rv.dup(i, v);
-                float z[EPV];
+                float z[EPV], w[EPV];
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) z[e] = e < d ? 0.0f : g[v * EPV + e];
-                sv[v] = lane_dot<EPV>(a + v * EPV, z);
+                for (int e = 0; e < EPV; ++e) {
+                    z[e] = e < d ? 0.0f : a[v * EPV + e];
+                    w[e] = e < d ? 0.0f : g[v * EPV + e];
+                }
+                sv[v] = lane_dot<EPV>(z, w);
             } else {
                 sv[v] = lane_dot<EPV>(a + v * EPV, g + v * EPV);
             }
@@ -881,7 +885,10 @@ __device__ __forceinline__ void rows_u_bwd(const typename E::T* y, const typenam
             if (SHIFT && v == 1) {
                 const int d = rv.dup(lane, v);
 #pragma unroll
-                for (int e = 0; e < EPV; ++e) g[e] = e < d ? 0.0f : g[e];
+                for (int e = 0; e < EPV; ++e) {
+                    a[e] = e < d ? 0.0f : a[e];
+                    g[e] = e < d ? 0.0f : g[e];
+                }
             }
             sv[v] = lane_dot<EPV>(a, g);
         }
@@ -1115,9 +1122,9 @@ __device__ __forceinline__ void team_row_bwd_two_pass(const typename E::T* y,
         team_load<E, L, SHIFT, NT>(dy, rv, t, s0, true, rg, 0.0f);
         team_unpack<E, L>(ra, a);
         team_unpack<E, L>(rg, g);
-        team_mask<E, L, SHIFT, NT>(rv, t, s0, g, 0.0f);
 #pragma unroll
         for (int k = 0; k < K; ++k) g[k] *= a[k];
+        team_mask<E, L, SHIFT, NT>(rv, t, s0, g, 0.0f);
         s += lane_reduce<K, OpAdd>(g);
     }
     float d[1] = {group_reduce<64, OpAdd>(s)};

@@ -105,3 +105,27 @@ def test_nan_anywhere_in_rows_read_twice(dtype):
     bits = to_host_bits(out)
     compare(bits, ref, dtype, mask & ~nan_rows)
     assert np.all(np.isnan(bits_to_f64(bits)[nan_rows]))
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_infinite_y_among_duplicates(dtype):
+    """Backward rows with one infinite y where slots meet: every other dx follows from the row's
+    infinite sum (an element that two lanes hold must not add inf * 0 to it)."""
+    epv = 4 if dtype == "f32" else 8
+    cols = [77, 333, 1001, 1999, 2051, 8193, 33001]  # every tile, workgroup-held, read twice
+    at = [[p for p in [c - epv, c - 1] + [g * epv - 1 for g in (8, 16, 32, 64, 256, 512)] if p < c] for c in cols]
+    w = workloads.custom([len(a) for a in at], cols, dtype=dtype, sigma=1.0, seed=62, gap=1, base=1)
+    yb, dyb = backward_inputs(w)
+    inf = np.inf if dtype == "f32" else 0x7F80
+    one = 1.0 if dtype == "f32" else 0x3F80
+    for o, c, ps in zip(w.offsets, cols, at):
+        for r, p in enumerate(ps):
+            yb[o + r * c + p] = inf
+            dyb[o + r * c + p] = one
+    ref = oracle.softmax_backward(yb, dyb, dtype, w.offsets[: w.batch], w.rows, w.cols, nthreads=16)
+    mask = covered_mask(w.offsets[: w.batch], w.rows, w.cols, yb.size)
+    dx, st = run_plan_backward(w, to_device(yb, dtype), to_device(dyb, dtype), "balanced")
+    assert st["kernel_class"] == 6
+    got = bits_to_f64(to_host_bits(dx))
+    assert np.count_nonzero(np.isinf(ref[mask])) > mask.sum() // 2
+    assert np.array_equal(got[mask], ref[mask], equal_nan=True)
