@@ -443,12 +443,13 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
         return fail(BSM_ERR_INVALID_ARG, "matrix-product plans run %d-thread workgroups (got %d)",
                     wg_threads, t.wg_threads);
     // Row-tile workgroups, where they are the faster form, unless the topology names a workgroup
-    // size (or, for the score softmax, asks for more workgroups than fit).
+    // size or asks for more workgroups than a CU holds of them.
     int row = 0, parts = 0;
     if (t.wg_threads == 0 && batch > 0 && m > 0 && n > 0 && k > 0) {
         if (layout == BSM_GEMM_NT_SOFTMAX) row = bsm::gemm_row_softmax_waves(batch, m, n, k);
         else parts = bsm::gemm_row_parts(layout, out_dtype == BSM_BF16, batch, m, n, k);
         if (row > 0 && t.wg_per_cu > 8 / row) row = 0;
+        if (parts > 0 && t.wg_per_cu > bsm::gemm_few_rows_wgs_per_cu(layout)) parts = 0;
         // one row tile per workgroup or less: no second and third workgroup per CU without any
         if (parts > 0 && t.wg_per_cu == 0 && batch * ((m + 31) / 32) <= 256) t.wg_per_cu = 1;
     }
@@ -467,7 +468,9 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
         hipDeviceProp_t prop;
         if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
         if (e != hipSuccess) return hip_fail(e, "hipGetDeviceProperties");
-        const int64_t per_wg = row > 0 ? bsm::gemm_row_lds_bytes_per_wg(row) : bsm::gemm_lds_bytes_per_wg(bf16_out, single);
+        const int64_t per_wg = row > 0     ? bsm::gemm_row_lds_bytes_per_wg(row)
+                               : parts > 0 ? bsm::gemm_few_rows_lds_bytes_per_wg(layout)
+                                           : bsm::gemm_lds_bytes_per_wg(bf16_out, single);
         if (per_wg > static_cast<int64_t>(prop.sharedMemPerBlock) ||
             per_wg * t.wg_per_cu > static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor))
             return fail(BSM_ERR_INVALID_ARG, "wg_per_cu %d: %lld bytes of LDS per workgroup do not fit",

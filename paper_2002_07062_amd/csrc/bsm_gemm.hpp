@@ -107,6 +107,8 @@ struct Geo {
     // three workgroups' LDS fits a CU
     static constexpr int kStageF = kBCols > kChunkK ? kTileN : kBlockN;
     static constexpr int kLdc = kStageF + 4;                    // padded LDS row of it, floats
+    // element of A's block in the wave's LDS that holds its row r, columns c .. c + 7
+    __device__ __forceinline__ static int a_at(int r, int c) { return r * kLdk + c; }
 };
 template <int LAYOUT, int FORM>
 constexpr int wave_bytes(bool bf16_out) {
@@ -246,13 +248,13 @@ __device__ __forceinline__ void load_a(const uint16_t* a, int64_t a_row, const S
     }
 }
 
-template <int OPS>
+template <int OPS, class G>
 __device__ __forceinline__ void write_a(const u16x8 (&pa)[kAPieces], int64_t a_row, const Shape& s, int rows,
                                         int k0, int lane, uint16_t* la) {
 #pragma unroll
     for (int q = 0; q < kAPieces; ++q) {
         const int r = piece_row(lane, q), c = piece_col(lane, q);
-        *reinterpret_cast<u16x8*>(la + r * kLdk + c) =
+        *reinterpret_cast<u16x8*>(la + G::a_at(r, c)) =
             keep8<OPS>(pa[q], a_row + static_cast<int64_t>(r) * s.k, k0 + c, s.k, s.a_total, r < rows,
                        k0 + kChunkK <= s.k);
     }
@@ -283,7 +285,7 @@ template <int LAYOUT, int OPS, class G>
 __device__ __forceinline__ void write_step(const Pieces<G>& p, int64_t a_row, int64_t b_row, const Shape& s,
                                            int rows, int j0, int k0, int wave, int lane, uint16_t* la,
                                            uint16_t* lb) {
-    if constexpr (!G::kAReg) write_a<OPS>(p.a, a_row, s, rows, k0, lane, la);
+    if constexpr (!G::kAReg) write_a<OPS, G>(p.a, a_row, s, rows, k0, lane, la);
 #pragma unroll
     for (int q = 0; q < G::kBPieces; ++q) {
         const int r = piece_row<G::kBCols>(lane, G::kBPieces * wave + q);
@@ -435,7 +437,7 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
             load_a<OPS>(a, a_row, s, rows, sl * kChunkK, lane, !TEMPORAL, pa[sl]);  // read once
 #pragma unroll
         for (int sl = 0; sl < kSlices; ++sl) {
-            write_a<OPS>(pa[sl], a_row, s, rows, sl * kChunkK, lane, la);
+            write_a<OPS, G>(pa[sl], a_row, s, rows, sl * kChunkK, lane, la);
             wave_lds_sync();
 #pragma unroll
             for (int q = 0; q < kChunkK / kTileK; ++q)

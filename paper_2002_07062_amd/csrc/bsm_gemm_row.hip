@@ -71,6 +71,8 @@ hipError_t pick_few(Launch& l, int parts, int layout, bool temporal, bool vec) {
 namespace bsm {
 
 int gemm_row_lds_bytes_per_wg(int q) { return row_lds_bytes(q); }
+int gemm_few_rows_lds_bytes_per_wg(int layout) { return few_rows_lds_bytes(layout); }
+int gemm_few_rows_wgs_per_cu(int layout) { return few_rows_wgs_per_cu(layout); }
 
 // us below: the other form -> row tiles.
 int gemm_row_softmax_waves(int64_t batch, int m, int n, int k) {
@@ -112,7 +114,7 @@ int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k
     } else {
         // NN's waves split the reduction, A is read once per 64 columns and B once per 32 rows:
         // for few tiles.  us at tiles x blocks: 504 (4 x (2000 x 2000)(2000 x 128)) 58 -> 20, 800
-        // (200 x (128 x 500)(500 x 64)) 24.6 -> 14.9, 876 33.6 -> 29.9, 1000 16.5 -> 19.5, 1024 27 -> 31, 1512 32 -> 37.
+        // (200 x (128 x 500)(500 x 64)) 24.6 -> 13.7, 876 33.6 -> 29.9, 1000 16.5 -> 19.5, 1024 27 -> 31, 1512 32 -> 37.
         if (tiles * blocks > 896) return 0;
     }
     // column parts until three workgroups per CU have rows, at least four blocks (NN: one) to a part

@@ -375,8 +375,13 @@ struct RowNnGeo {
     static constexpr int kBCols = kBlockN;
     static constexpr int kLdb = kBlockN + 8;
     static constexpr int kBPieces = kRowPieces;
+    // A's rows are not padded, but their 16-byte pieces permuted by the row (eight rows' reads of
+    // one column still fall on eight different pieces): padded, three workgroups' LDS took 2 KB
+    // more than a CU has, and the third waited (us, padded -> this: 200 x (128 x 500)(500 x 64) 15.6 ->
+    // 13.7, 438 x (64 x 333)(333 x 64) 21.9 -> 16.5, 4 x (2000 x 2000)(2000 x 128), two at most, 19.3 -> 19.4)
+    __device__ __forceinline__ static int a_at(int r, int c) { return r * kChunkK + (c ^ (8 * (r & 7))); }
 };
-constexpr int kRowNnA = kTileM * kLdk * 2;  // bytes of a wave's A slice
+constexpr int kRowNnA = kTileM * kChunkK * 2;  // bytes of a wave's A slice
 constexpr int kRowNnWaveBytes = kRowNnA + kChunkK * RowNnGeo::kLdb * 2;
 constexpr int kRowLdc = kBlockN + 4;        // floats, the partial sums' row
 static_assert(kRowNnWaveBytes >= kTileM * kRowLdc * 4, "a wave's partial sums fit its region");
@@ -384,6 +389,13 @@ static_assert(kRowNnWaveBytes >= kTileM * kRowLdc * 4, "a wave's partial sums fi
 constexpr int few_rows_lds_bytes(int layout) {
     return layout == kNN ? kRowWaves * kRowNnWaveBytes : kRowWaves * kRowWaveBytes + kTileM * kRowLda<2> * 2;
 }
+// Workgroups of the plain products that a CU holds: three by registers (launch bounds) and by
+// LDS (160 KB, given out in pieces of 1280 bytes).
+constexpr int few_rows_wgs_per_cu(int layout) {
+    const int by_lds = 160 * 1024 / ((few_rows_lds_bytes(layout) + 1279) / 1280 * 1280);
+    return by_lds < kWavesPerSimd ? by_lds : kWavesPerSimd;
+}
+static_assert(few_rows_wgs_per_cu(kNT) == 3 && few_rows_wgs_per_cu(kNN) == 3, "the column parts count on three");
 
 template <bool BF16OUT, int OPS, bool TEMPORAL, int Q>
 __device__ __forceinline__ uint32_t row_nn_worker(const uint16_t* a, const uint16_t* b, void* c, const Shape& s,
@@ -412,7 +424,7 @@ __device__ __forceinline__ uint32_t row_nn_worker(const uint16_t* a, const uint1
                 if (kc + Q < nk) load(kc + Q);
 #pragma unroll
                 for (int kk = 0; kk < kChunkK; kk += kTileK) {
-                    const bf16x8 av = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(la + li * kLdk + kk + 8 * h));
+                    const bf16x8 av = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u16x8*>(la + RowNnGeo::a_at(li, kk + 8 * h)));
 #pragma unroll
                     for (int t = 0; t < kBlockTiles; ++t)
                         acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(nn_row_operand<RowNnGeo::kLdb>(lb, t, kk, lane),

@@ -74,6 +74,8 @@ hipError_t launch_gemm_row(int q, bool bf16_out, bool temporal, const void* a, c
 // NT and NN by row-tile workgroups (gemm_wg_threads() threads, 32 rows per round).  parts:
 // workgroups that share a worker's rows, each with its own columns; gemm_row_parts says how many
 // a shape takes, 0 for the general form.
+int gemm_few_rows_lds_bytes_per_wg(int layout);
+int gemm_few_rows_wgs_per_cu(int layout);  // that a CU holds at once
 int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k);
 hipError_t launch_gemm_few_rows(int layout, int parts, bool bf16_out, bool temporal, const void* a, const void* b, void* c,
                                 int64_t batch, int m, int n, int k, float alpha, const int32_t* d_worker_ptr,

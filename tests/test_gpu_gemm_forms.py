@@ -52,8 +52,10 @@ def test_forms_against_the_oracle_and_each_other(shape, layout, out):
         check_product(got, a, b, batch, m, n, k, layout, out, alpha)
     assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha, schedule="rr"), got)
     if layout != "nt_softmax" and out == "bf16":
-        # four workgroups per CU leave no room for the 128-wide forms: the same bits without them
-        assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha, topology={"wg_per_cu": 4}), got)
+        # the general forms (a named workgroup size keeps row tiles out); four workgroups per CU
+        # leave no room for the 128-wide ones: the same bits without them
+        general = _product(shape, layout, out, a_d, b_d, alpha, topology={"wg_threads": 256})
+        assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha, topology={"wg_threads": 256, "wg_per_cu": 4}), general)
 
 
 @pytest.mark.parametrize("n,k", [(520, 128), (700, 72), (513, 64)])

@@ -89,7 +89,7 @@ def test_plain_row_tiles_against_the_oracle(layout, shape, out):
     a_d, b_d = _dev_bf16(a), _dev_bf16(b)
     want = _product(shape, layout, out, a_d, b_d, 0.25)
     check_product(want, a, b, batch, m, n, k, layout, out, 0.25)
-    for topology in ({"n_cu": 3, "n_xcd": 1, "flags": bsm.BSM_FLAG_TEMPORAL}, {"wg_per_cu": 4 if out == "bf16" else 3}):
+    for topology in ({"n_cu": 3, "n_xcd": 1, "flags": bsm.BSM_FLAG_TEMPORAL}, {"wg_per_cu": 3}):
         assert np.array_equal(_product(shape, layout, out, a_d, b_d, 0.25, topology=topology), want)
     for schedule in ("rr", "xcd"):
         assert np.array_equal(_product(shape, layout, out, a_d, b_d, 0.25, schedule=schedule), want)

@@ -494,3 +494,18 @@ def test_rounds_of_nn_and_score_softmax_start_over_in_every_batch_index(layout, 
         for it in items:
             starts = it["elem_offset"] // n + np.arange(it["reps"]) * it["rep_stride"]
             assert np.all(starts % m % unit == 0)
+
+
+@pytest.mark.parametrize("wg_per_cu", [0, 1, 2, 3, 4])
+@pytest.mark.parametrize("layout,shape", [("nt", (40, 512, 200, 64)), ("nn", (12, 512, 64, 333)), ("nn", (3, 512, 128, 40))])
+def test_plain_products_take_row_tiles_where_their_workgroups_fit(layout, shape, wg_per_cu):
+    """A CU's LDS holds three workgroups of the plain row tiles (rounds of 32 rows); a topology
+    that asks for four keeps the general form (rounds of 128 rows), four of which fit."""
+    batch, m, n, k = shape
+    p = bsm.bsm_gemm_plan_create(batch, m, n, k, layout, "bf16", "balanced",
+                                 topology=dict(n_cu=256, n_xcd=8, wg_per_cu=wg_per_cu), device=-1)
+    ptr, items, _, _ = bsm.bsm_plan_export(p)
+    p.destroy()
+    starts = np.concatenate([it["elem_offset"] // n + np.arange(it["reps"]) * it["rep_stride"] for it in items])
+    assert np.all(starts % (32 if wg_per_cu < 4 else 128) == 0)
+    assert np.any(starts % 128 != 0) == (wg_per_cu < 4)
