@@ -40,7 +40,7 @@ struct bsm_plan_s {
     bool gemm_single = false;  // layout 2 in one pass (products held in registers)
     int gemm_row = 0;          // layout 2 by row-tile workgroups of this many waves
     int gemm_parts = 0;        // layouts 0 and 1 by row-tile workgroups, so many to a worker's rows
-    bool gemm_wide = false;    // the CU's LDS holds its workgroups' 128-wide B blocks
+    bool gemm_wide = false;    // the forms with a 128-wide B block pay, and the CU's LDS holds them
     int64_t gemm_batch = 0;
     int32_t flags = 0;            // BSM_FLAG_* bits
     void* d_table = nullptr;  // device copy: worker_ptr, then items (256-byte aligned)
@@ -475,8 +475,9 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
             per_wg * t.wg_per_cu > static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor))
             return fail(BSM_ERR_INVALID_ARG, "wg_per_cu %d: %lld bytes of LDS per workgroup do not fit",
                         t.wg_per_cu, static_cast<long long>(per_wg));
-        wide = static_cast<int64_t>(bsm::gemm_wide_lds_bytes_per_wg(bf16_out)) * t.wg_per_cu <=
-               static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor);
+        wide = bsm::gemm_wide_pays(k, t.wg_per_cu) &&
+               static_cast<int64_t>(bsm::gemm_wide_lds_bytes_per_wg(bf16_out)) * t.wg_per_cu <=
+                   static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor);
     }
     // planned with one-wave workgroups, so that every worker is a workgroup (same index, same
     // XCD); the launch then runs the real workgroup size

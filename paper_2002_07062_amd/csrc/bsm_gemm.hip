@@ -43,12 +43,17 @@ int gemm_wide_lds_bytes_per_wg(bool bf16_out) {
     return std::max(bsm_mm::wg_bytes<bsm_mm::kNT, bsm_mm::kFormA2>(bf16_out),
                     bsm_mm::wg_bytes<bsm_mm::kNN, bsm_mm::kFormWide>(bf16_out));
 }
+// kFormWide is compiled for two workgroups per CU.  With a third, which waits, it still pays over
+// several reduction steps (32 x (2048 x 2048)(2048 x 128) 105 us against kFormStep's 113), but not
+// over one (384 x (512 x 64)(64 x 100) 27.8 against 25.2; two per CU 23.9).
+bool gemm_wide_pays(int k, int wgs_per_cu) { return k > bsm_mm::kChunkK || wgs_per_cu <= bsm_mm::kS1WavesPerSimd; }
 int gemm_waves_per_simd(bool single_pass) {
     return single_pass ? bsm_mm::kS1WavesPerSimd : bsm_mm::kWavesPerSimd;
 }
 int gemm_default_wgs_per_cu(int layout, int n, int k, bool single_pass) {
     if (single_pass) return bsm_mm::kS1WavesPerSimd;
-    const int form = bsm_mm::form_of(layout, k % 8 == 0, true, n, k);
+    const bool vec = k % 8 == 0 && (layout != bsm_mm::kNN || n % 8 == 0);  // as launch_gemm, aligned operands
+    const int form = bsm_mm::form_of(layout, vec, true, n, k);
     return form == bsm_mm::kFormStep ? bsm_mm::kWavesPerSimd : bsm_mm::waves_per_simd(layout, form);
 }
 int gemm_rows_per_wg(bool single_pass) {

@@ -47,6 +47,7 @@ int gemm_wg_threads();
 bool gemm_single_pass_shape(int n, int k);
 int gemm_lds_bytes_per_wg(bool bf16_out, bool single_pass);
 int gemm_wide_lds_bytes_per_wg(bool bf16_out);  // of the forms with a 128-wide B block
+bool gemm_wide_pays(int k, int wgs_per_cu);
 int gemm_waves_per_simd(bool single_pass);
 // Workgroups per CU when the topology does not say: as many as the form the shape takes is
 // compiled for.
@@ -56,8 +57,8 @@ int gemm_rows_per_wg(bool single_pass);
 // Worker w of the table is workgroup w (gemm_wg_threads() threads, gemm_rows_per_wg() rows
 // per round).  temporal: ordinary instead of nontemporal stores of C and loads of A.
 // single_pass (layout 2): the one-pass form where the shape and 16-byte operands allow it,
-// else the two-pass form.  wide: the plan's workgroups per CU leave room for the LDS of the
-// forms with a 128-wide B block.
+// else the two-pass form.  wide: the forms with a 128-wide B block pay (gemm_wide_pays), and the
+// plan's workgroups per CU leave room for their LDS.
 hipError_t launch_gemm(int layout, bool bf16_out, bool temporal, bool single_pass, bool wide, const void* a,
                        const void* b, void* c, int64_t batch, int m, int n, int k, float alpha,
                        const int32_t* d_worker_ptr, const bsm_item* d_items, int n_wg, void* trace,

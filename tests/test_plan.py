@@ -509,3 +509,12 @@ def test_plain_products_take_row_tiles_where_their_workgroups_fit(layout, shape,
     starts = np.concatenate([it["elem_offset"] // n + np.arange(it["reps"]) * it["rep_stride"] for it in items])
     assert np.all(starts % (32 if wg_per_cu < 4 else 128) == 0)
     assert np.any(starts % 128 != 0) == (wg_per_cu < 4)
+
+
+@pytest.mark.parametrize("n,k,per_cu", [(100, 64, 2), (104, 64, 3), (100, 72, 2), (104, 72, 2), (64, 333, 3), (65, 60, 2)])
+def test_context_products_default_to_the_workgroups_their_form_is_compiled_for(n, k, per_cu):
+    """NN takes the 128-column form, two workgroups per CU, unless A's operands stay in registers
+    (k <= 64, rows of both operands whole 16-byte pieces) or one column block is all there is."""
+    p = bsm.bsm_gemm_plan_create(384, 512, n, k, "nn", "bf16", "balanced", topology=dict(n_cu=256, n_xcd=8), device=-1)
+    assert bsm.bsm_plan_describe(p)["n_wg"] == 256 * per_cu
+    p.destroy()
