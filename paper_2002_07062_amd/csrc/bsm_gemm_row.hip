@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 #include <cstdint>
 
 #include "bsm.h"
@@ -102,24 +103,37 @@ int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k
     if (batch * std::min(m, n) * k < 8 || (layout == kNT && k > 2 * kChunkK)) return 0;
     const int64_t tiles = batch * ((m + kTileM - 1) / kTileM);
     const int64_t blocks = (n + kBlockN - 1) / kBlockN;
-    const int64_t rounds = batch * ((m + 127) / 128);  // of the general form
+    // column parts until three workgroups per CU have rows, at least four blocks (NN: one) to a part
+    const int64_t most = layout == kNT ? (blocks + kRowWaves - 1) / kRowWaves : blocks;
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>({most, 8, 768 / tiles}));
     if (layout == kNT) {
-        // The general form keeps full rounds of bf16 rows of whole 128-byte lines, once they
-        // fill the chip (384 x 512 x 512 44 -> 54, 200 x 512 x 512 25.1 -> 27.7, 400 x 256 x 256 (k = 128)
-        // 22.4 -> 26.5; B is staged once for 128 rows).  Otherwise row tiles: fewer rounds
-        // (96 x 512 x 512 17.9 -> 11.9, 4 x 2048 x 2048 (k = 128) 48 -> 12), partly empty ones (512 x 16 x 936
-        // 142 -> 30, 800 x 65 x 500 44 -> 34), lines that two blocks share, here stored at about the
-        // same time (1000 x 128 x 300 62 -> 38, 300 x 333 x 333 57 -> 38), fp32 (384 x 512 x 512 78.7 -> 72.8).
-        if (bf16_out && n % kBlockN == 0 && rounds >= 768 && 4 * rounds * 10 <= 13 * tiles) return 0;
+        // Both forms' time by what their workgroups do, three to a CU, in steps of one 64-column
+        // block.  The general form's units are 128 rows of the row stream, dealt whole; a unit
+        // starts over in every batch index that it meets.  Its steps take longer in fp32, and
+        // where two blocks share 128-byte lines (which row tiles store at about the same time).
+        // A row tile takes 0.9 steps and 0.75 for every four blocks, a quarter more with two
+        // slices of k.  Fitted to 4140 shapes (n 16 .. 2048, m 8 .. 2048, 1 to 60 million outputs,
+        // both types): 95% get the faster form, or one within 5% of it, the worst one of 1.43
+        // times its time.  us, general -> row tiles: 384 x 512 x 512 44 -> 54 (fp32 78.7 -> 72.8), 190 x
+        // 512 x 512 (k = 128) 27.5 -> 36.6, 7324 x 512 x 16 120 -> 299, fp32 384 x 512 x 64 13.7 -> 19.1;
+        // 4 x 2048 x 2048 (k = 128) 48 -> 12, 512 x 16 x 936 142 -> 30, 1000 x 128 x 300 62 -> 38, 473 x 33 x
+        // 64 14.5 -> 8.7.
+        const double resident = 768.0;
+        const int64_t units = (batch * m + 127) / 128;
+        const double per_unit = m % 128 == 0 ? 1.0 : 128 % m == 0 ? 128.0 / m : 1.0 + 128.0 / m;
+        const bool shared_lines = blocks > 1 && n % (bf16_out ? 64 : 32) != 0;
+        const double general = std::ceil(units / resident) * per_unit * (0.6 + (bf16_out ? 1.0 : 1.6) * blocks) *
+                               (shared_lines ? 3.0 : 1.0);
+        const double row = std::max(1.0, tiles * parts / resident) * (k > kChunkK ? 1.25 : 1.0) *
+                           (0.9 + 0.75 * static_cast<double>((blocks + 4 * parts - 1) / (4 * parts)));
+        if (general <= row) return 0;
     } else {
         // NN's waves split the reduction, A is read once per 64 columns and B once per 32 rows:
         // for few tiles.  us at tiles x blocks: 504 (4 x (2000 x 2000)(2000 x 128)) 58 -> 20, 800
         // (200 x (128 x 500)(500 x 64)) 24.6 -> 13.7, 876 33.6 -> 29.9, 1000 16.5 -> 19.5, 1024 27 -> 31, 1512 32 -> 37.
         if (tiles * blocks > 896) return 0;
     }
-    // column parts until three workgroups per CU have rows, at least four blocks (NN: one) to a part
-    const int64_t most = layout == kNT ? (blocks + kRowWaves - 1) / kRowWaves : blocks;
-    return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>({most, 8, 768 / tiles})));
+    return static_cast<int>(parts);
 }
 
 hipError_t launch_gemm_row(int q, bool bf16_out, bool temporal, const void* a, const void* b, void* c, int64_t batch,

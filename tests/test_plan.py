@@ -518,3 +518,20 @@ def test_context_products_default_to_the_workgroups_their_form_is_compiled_for(n
     p = bsm.bsm_gemm_plan_create(384, 512, n, k, "nn", "bf16", "balanced", topology=dict(n_cu=256, n_xcd=8), device=-1)
     assert bsm.bsm_plan_describe(p)["n_wg"] == 256 * per_cu
     p.destroy()
+
+
+@pytest.mark.parametrize("dtype,batch,m,n,k,row_tiles", [
+    ("f32", 384, 512, 64, 64, False), ("bf16", 1831, 2048, 16, 40, False), ("bf16", 190, 512, 512, 128, False),
+    ("bf16", 384, 512, 512, 64, False), ("f32", 384, 512, 512, 64, True), ("bf16", 473, 33, 64, 64, True),
+    ("bf16", 1000, 128, 300, 64, True), ("bf16", 4, 2048, 2048, 128, True), ("bf16", 512, 16, 936, 128, True)])
+def test_plain_scores_take_the_faster_form(dtype, batch, m, n, k, row_tiles):
+    """NT keeps 128-row units of the row stream where row tiles (rounds of 32 rows of a batch
+    index) were measured slower: one column block, or units that fill the chip evenly."""
+    p = bsm.bsm_gemm_plan_create(batch, m, n, k, "nt", dtype, "balanced", topology=dict(n_cu=256, n_xcd=8), device=-1)
+    _, items, _, _ = bsm.bsm_plan_export(p)
+    p.destroy()
+    starts = np.concatenate([it["elem_offset"] // n + np.arange(it["reps"]) * it["rep_stride"] for it in items])
+    if row_tiles:
+        assert np.all(starts % m % 32 == 0) and np.any(starts % 128 != 0)
+    else:
+        assert np.all(starts % 128 == 0)
