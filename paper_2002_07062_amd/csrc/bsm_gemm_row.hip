@@ -81,8 +81,9 @@ int gemm_row_softmax_waves(int64_t batch, int m, int n, int k) {
     if (k > 2 * kChunkK || n > row_max_cols(8) || batch * std::min(m, n) * k < 8) return 0;
     const int64_t tiles = batch * ((m + kTileM - 1) / kTileM);  // of 32 rows
     const int blocks = (n + kBlockN - 1) / kBlockN;             // of 64 columns
-    // Past 512 columns the other form takes two passes.
-    if (!single_pass_shape(n, k) && n > kBlockN) return n <= row_max_cols(4) ? 4 : 8;
+    // Past 512 columns, and where k is no whole number of 16-byte pieces, the other form takes two
+    // passes (384 x 512 x 512 (k = 100) 303 -> 94, 9469 x 33 x 128 (k = 100) 269 -> 204).
+    if (n > kBlockN && (k % 8 != 0 || !single_pass_shape(n, k))) return n <= row_max_cols(4) ? 4 : 8;
     // One column block (the other form: two passes of 128-row rounds; here one wave of four
     // works): where the chip is not full of rounds, or they are mostly empty.  1000 x 30 x 60
     // 23.6 -> 8.5, 40 x 500 x 60 (k = 128) 20.9 -> 9.3, 100 x 500 x 40 20.1 -> 13.9; past the line
@@ -92,11 +93,14 @@ int gemm_row_softmax_waves(int64_t batch, int m, int n, int k) {
     // the columns over two waves.  Four must not leave more of them idle (1000 x 33 x 300
     // 22.4 -> 27.5, 2000 x 128 x 128 34 -> 43), and win where the rounds do not fill the chip a few times
     // (16 x 512 x 512 13.4 -> 8.7, 96 x 512 x 512 20.6 -> 17.1; 192 x 512 x 512 (k = 128) 40 -> 45, 384 x 512 x 512
-    // 65 -> 71) or where rows are not whole 128-byte lines, whose halves the waves then
-    // store at about the same time (1000 x 128 x 500 77 -> 61, 1000 x 64 x 200 19.0 -> 17.4).
+    // 65 -> 71; with two slices of k once, 488 x 64 x 512 (k = 128) 21.2 -> 27.1) or where rows are
+    // not whole 128-byte lines, whose halves the waves then store at about the same time, and the
+    // rounds are mostly full (1000 x 128 x 500 77 -> 61, 1000 x 64 x 200 19.0 -> 17.4; 969 x 33 x 500
+    // 28.6 -> 31.0, 2424 x 33 x 500 (k = 128) 104 -> 120).
     const int64_t rounds = batch * ((m + kS1Rows - 1) / kS1Rows);
     if (tiles * ((blocks + 3) / 4) > rounds * ((blocks + 1) / 2)) return 0;
-    return rounds <= 800 || m <= kTileM || n % kBlockN != 0 ? 4 : 0;
+    if (rounds <= (k > kChunkK ? 440 : 800) || m <= kTileM) return 4;
+    return n % kBlockN != 0 && 5 * batch * m > 4 * rounds * kS1Rows ? 4 : 0;
 }
 
 int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k) {
