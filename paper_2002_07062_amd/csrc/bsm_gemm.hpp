@@ -167,7 +167,8 @@ __device__ __forceinline__ u16x8 load8(const uint16_t* base, int64_t row, int c,
 }
 
 // Zeroes the elements of a piece loaded by load8 that lie past `len`, or all of them when !ok.
-// kVec: the piece is wholly in or wholly out, four 32-bit selects.  Otherwise the piece may hold
+// kVec: the piece is wholly in or wholly out, four 32-bit selects (asking for `whole` too cost the
+// two-pass score softmax 5%: 64 x 1024 x 1024 (k = 256) 252 us, so 238).  Otherwise the piece may hold
 // any number of the row's elements (`whole`, the same for the wave: the step's columns all lie
 // inside the rows, so that only !ok is left), and the operand's last piece is first moved down
 // by the elements it was loaded early.
@@ -175,7 +176,7 @@ template <int OPS>
 __device__ __forceinline__ u16x8 keep8(u16x8 v, int64_t row, int c, int len, int64_t total, bool ok, bool whole) {
     u32x4 w = __builtin_bit_cast(u32x4, v);
     if (OPS == kVec || whole) {
-        const bool in = ok && (whole || c < len);
+        const bool in = ok && (OPS != kVec || c < len);
 #pragma unroll
         for (int e = 0; e < 4; ++e) w[e] = in ? w[e] : 0u;
         return __builtin_bit_cast(u16x8, w);
@@ -415,8 +416,13 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
     const int li = lane & 31;
     const int h = lane >> 5;
     uint16_t* const la = lw;
-    const int64_t a_row = rows > 0 ? bidx * s.a_batch + static_cast<int64_t>(i0) * s.k : 0;
-    const int64_t b_row = bidx * s.b_batch;
+    int64_t a_row = rows > 0 ? bidx * s.a_batch + static_cast<int64_t>(i0) * s.k : 0;
+    int64_t b_row = bidx * s.b_batch;
+    if constexpr (OPS == kVec) {  // whole pieces need no offset in the operand: 5 to 10 spilled registers less
+        a += a_row;
+        b += b_row;
+        a_row = b_row = 0;
+    }
     const int nk = AREG ? 1 : (s.k + kChunkK - 1) / kChunkK;  // k > 0 here
     const int nj = (s.n + G::kN - 1) / G::kN;
     const int nsteps = nk * nj;
@@ -588,13 +594,6 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
                 const float bs = acc[0][0] + acc[1][0];
                 sm_sum = sm_sum * __builtin_amdgcn_exp2f(sm_max - ms) + bs;
                 sm_max = mx;
-                if (jb + 1 == nj) {  // the row's last block: both lanes' maxima and sums, and 1 / sum
-                    const float all = half_pair(sm_max, lane, [](float u, float v) { return __builtin_elementwise_maximum(u, v); });
-                    const float mine = sm_max == kNegInfF ? 0.0f : sm_sum * __builtin_amdgcn_exp2f(sm_max - all);
-                    const float tot = half_pair(mine, lane, [](float u, float v) { return u + v; });
-                    sm_max = all;
-                    sm_inv = tot == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(tot);
-                }
                 if constexpr (!AREG) {
 #pragma unroll
                     for (int t = 0; t < kBlockTiles; ++t) acc[t] = f32x16{};
@@ -687,6 +686,12 @@ __device__ __forceinline__ void round_rows(const uint16_t* a, const uint16_t* b,
         run(P0{}, nall, false);
     } else {
         run(P1{}, nsteps, false);
+        // the row's two lanes meet: both lanes' maxima and sums, and 1 / sum
+        const float all = half_pair(sm_max, lane, [](float u, float v) { return __builtin_elementwise_maximum(u, v); });
+        const float mine = sm_max == kNegInfF ? 0.0f : sm_sum * __builtin_amdgcn_exp2f(sm_max - all);
+        const float tot = half_pair(mine, lane, [](float u, float v) { return u + v; });
+        sm_max = all;
+        sm_inv = tot == 0.0f ? 0.0f : __builtin_amdgcn_rcpf(tot);
         run(P2{}, nall, (nsteps & 1) != 0);
     }
 }
