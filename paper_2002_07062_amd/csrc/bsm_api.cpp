@@ -459,7 +459,7 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     }
     const bool single = layout == BSM_GEMM_NT_SOFTMAX && bsm::gemm_single_pass_shape(n, k) &&
                         (t.wg_per_cu == 0 || t.wg_per_cu <= bsm::gemm_waves_per_simd(true));
-    if (t.wg_per_cu == 0) t.wg_per_cu = bsm::gemm_default_wgs_per_cu(layout, n, k, single);
+    if (t.wg_per_cu == 0) t.wg_per_cu = bsm::gemm_default_wgs_per_cu(layout, batch, m, n, k, single);
     const bool bf16_out = out_dtype == BSM_BF16;
     bool wide = false;
     if (device >= 0) {
@@ -475,7 +475,7 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
             per_wg * t.wg_per_cu > static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor))
             return fail(BSM_ERR_INVALID_ARG, "wg_per_cu %d: %lld bytes of LDS per workgroup do not fit",
                         t.wg_per_cu, static_cast<long long>(per_wg));
-        wide = bsm::gemm_wide_pays(k, t.wg_per_cu) &&
+        wide = bsm::gemm_wide_pays(layout, batch, m, n, k, t.wg_per_cu) &&
                static_cast<int64_t>(bsm::gemm_wide_lds_bytes_per_wg(bf16_out)) * t.wg_per_cu <=
                    static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor);
     }

@@ -43,17 +43,33 @@ int gemm_wide_lds_bytes_per_wg(bool bf16_out) {
     return std::max(bsm_mm::wg_bytes<bsm_mm::kNT, bsm_mm::kFormA2>(bf16_out),
                     bsm_mm::wg_bytes<bsm_mm::kNN, bsm_mm::kFormWide>(bf16_out));
 }
+// NN's rounds of 128 rows come to between two and three per CU: three workgroups per CU of the
+// 64-column form then take one each, where two of the 128-column form leave some CUs a second
+// turn.  us, two -> three: 192 x (512 x 512)(512 x 128) 41.8 -> 39.3, 192 x (512 x 128)(128 x 128)
+// 16.7 -> 12.9, 150 x (512 x 333)(333 x 128) 36.7 -> 35.3; past the lines 129 x (512 x 512)(512 x 128)
+// 31.7 -> 36.5, 225 x (512 x 512)(512 x 128) 43 -> 75, 192 x (512 x 512)(512 x 80) 39.5 -> 40.9, 96 x (1024 x
+// 1024)(1024 x 128) 64 -> 72; n = 512 gains too (192 x (512 x 512)(512 x 512) 145 -> 138) unless every
+// round has a batch index of its own (768 x (128 x 512)(512 x 256) 83 -> 93).
+static bool nn_three_per_cu(int64_t batch, int m, int n, int k) {
+    const int64_t rounds = batch * ((m + 127) / 128);
+    return n > 80 && (n <= 128 || m > 128) && k <= 768 && rounds > 563 && rounds <= 768;
+}
 // kFormWide is compiled for two workgroups per CU.  With a third, which waits, it still pays over
 // several reduction steps (32 x (2048 x 2048)(2048 x 128) 105 us against kFormStep's 113), but not
-// over one (384 x (512 x 64)(64 x 100) 27.8 against 25.2; two per CU 23.9).
-bool gemm_wide_pays(int k, int wgs_per_cu) { return k > bsm_mm::kChunkK || wgs_per_cu <= bsm_mm::kS1WavesPerSimd; }
+// over one (384 x (512 x 64)(64 x 100) 27.8 against 25.2; two per CU 23.9), nor where three is the
+// better number.
+bool gemm_wide_pays(int layout, int64_t batch, int m, int n, int k, int wgs_per_cu) {
+    if (wgs_per_cu <= bsm_mm::kS1WavesPerSimd) return true;
+    return k > bsm_mm::kChunkK && !(layout == bsm_mm::kNN && nn_three_per_cu(batch, m, n, k));
+}
 int gemm_waves_per_simd(bool single_pass) {
     return single_pass ? bsm_mm::kS1WavesPerSimd : bsm_mm::kWavesPerSimd;
 }
-int gemm_default_wgs_per_cu(int layout, int n, int k, bool single_pass) {
+int gemm_default_wgs_per_cu(int layout, int64_t batch, int m, int n, int k, bool single_pass) {
     if (single_pass) return bsm_mm::kS1WavesPerSimd;
     const bool vec = k % 8 == 0 && (layout != bsm_mm::kNN || n % 8 == 0);  // as launch_gemm, aligned operands
     const int form = bsm_mm::form_of(layout, vec, true, n, k);
+    if (form == bsm_mm::kFormWide && nn_three_per_cu(batch, m, n, k)) return bsm_mm::kWavesPerSimd;
     return form == bsm_mm::kFormStep ? bsm_mm::kWavesPerSimd : bsm_mm::waves_per_simd(layout, form);
 }
 int gemm_rows_per_wg(bool single_pass) {

@@ -511,11 +511,14 @@ def test_plain_products_take_row_tiles_where_their_workgroups_fit(layout, shape,
     assert np.any(starts % 128 != 0) == (wg_per_cu < 4)
 
 
-@pytest.mark.parametrize("n,k,per_cu", [(100, 64, 2), (104, 64, 3), (100, 72, 2), (104, 72, 2), (64, 333, 3), (65, 60, 2)])
-def test_context_products_default_to_the_workgroups_their_form_is_compiled_for(n, k, per_cu):
+@pytest.mark.parametrize("batch,n,k,per_cu", [
+    (384, 100, 64, 2), (384, 104, 64, 3), (384, 100, 72, 2), (384, 104, 72, 2), (384, 64, 333, 3), (384, 65, 60, 2),
+    (192, 128, 512, 3), (192, 128, 333, 3), (140, 128, 512, 2), (193, 128, 512, 2), (192, 80, 512, 2), (192, 128, 776, 2)])
+def test_context_products_default_to_the_workgroups_their_form_is_compiled_for(batch, n, k, per_cu):
     """NN takes the 128-column form, two workgroups per CU, unless A's operands stay in registers
-    (k <= 64, rows of both operands whole 16-byte pieces) or one column block is all there is."""
-    p = bsm.bsm_gemm_plan_create(384, 512, n, k, "nn", "bf16", "balanced", topology=dict(n_cu=256, n_xcd=8), device=-1)
+    (k <= 64, rows of both operands whole 16-byte pieces), one column block is all there is, or
+    there is one 128-row round for each of three workgroups per CU."""
+    p = bsm.bsm_gemm_plan_create(batch, 512, n, k, "nn", "bf16", "balanced", topology=dict(n_cu=256, n_xcd=8), device=-1)
     assert bsm.bsm_plan_describe(p)["n_wg"] == 256 * per_cu
     p.destroy()
 
