@@ -98,12 +98,15 @@ struct DeviceGuard {
 
 // Waves per CU that measured fastest on MI355X: 8 for fp32 rows (more waves only add DRAM
 // page conflicts), 16 for bf16 rows, which carry twice the ALU work per byte and need the
-// extra waves to overlap it with memory.  Plans with rows beyond the register tile run two
+// extra waves to overlap it with memory; 12 where one wave holds 8 KiB of a row (class 3; us,
+// 16 -> 12 waves: 76 x 64 x 4096 20.5 -> 17.6 (backward 28.4 -> 23.7), 300 x 128 x 2304 69.2 -> 67.4,
+// 300 x 64 x 4096 58.5 -> 60.6), 8 if they are shifted (12 -> 8: 300 x 64 x 3333 54.3 -> 52.3,
+// backward 78.1 -> 76.1).  Plans with rows beyond the register tile run two
 // 256-thread workgroups per CU (8 waves), each holding one or two rows in its registers.
 constexpr int kLongRowClass = 4;
-int default_waves_per_cu(bsm_dtype d, int kclass) {
-    if (kclass >= kLongRowClass) return 8;
-    return d == BSM_BF16 ? 16 : 8;
+int default_waves_per_cu(bsm_dtype d, int kclass, bool shifted) {
+    if (kclass >= kLongRowClass || d != BSM_BF16) return 8;
+    return kclass < 3 ? 16 : shifted ? 8 : 12;
 }
 
 constexpr int kDefaultPieceBytes = 8192;
@@ -177,7 +180,7 @@ bsm_status resolve_topology(const bsm_topology* user, int device, bsm_dtype dtyp
         if (user->row_cost > 0.0f) t.row_cost = user->row_cost;
     }
     if (t.wg_per_cu <= 0 && t.wg_threads >= 64) {
-        const int want = std::max(1, default_waves_per_cu(dtype, kclass) / (t.wg_threads / 64));
+        const int want = std::max(1, default_waves_per_cu(dtype, kclass, shifted) / (t.wg_threads / 64));
         t.wg_per_cu = want;
         if (device >= 0 && t.wg_threads <= 1024 && t.wg_threads % 64 == 0) {
             int n = 0;

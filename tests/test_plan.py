@@ -556,3 +556,15 @@ def test_score_softmax_takes_the_faster_form(batch, m, n, k, wg_threads, wg_per_
     assert np.all(starts % (32 if row_tiles else 64) == 0)
     if m > 32:
         assert np.any(starts % 64 != 0) == row_tiles
+
+
+@pytest.mark.parametrize("dtype,cols,n_wg", [("bf16", 2049, 512), ("bf16", 2056, 768), ("bf16", 4096, 768), ("bf16", 2048, 1024), ("bf16", 64, 1024),
+                                             ("f32", 2048, 512), ("bf16", 4097, 512)])
+def test_default_workgroups_by_row_length(dtype, cols, n_wg):
+    """16 waves per CU for bf16 rows, 12 where a wave holds 257 to 512 vectors (8 if the
+    rows do not start and end on vectors), 8 for fp32 rows
+    and for rows that workgroups hold, whatever the instance's registers would let run."""
+    p = bsm.bsm_plan_create([64], [cols], batch=64, dtype=dtype, schedule="balanced", device=-1,
+                            topology=dict(n_cu=256, n_xcd=8))
+    assert bsm.bsm_plan_describe(p)["n_wg"] == n_wg
+    p.destroy()
