@@ -302,7 +302,11 @@ bsm_status bsm_softmax_backward(const void* y, const void* dy, void* dx,
  * of whole 128-row blocks (the rows a workgroup takes per round, 32 per wave).  Shapes that leave
  * such rounds few or partly empty, and others where it is faster, run by row-tile workgroups
  * instead, in rounds of 32 rows whose columns (NN: reduction) the waves split; a topology that
- * names wg_threads keeps the 128-row rounds.
+ * names wg_threads keeps the 128-row rounds (one with every field filled in, as
+ * bsm_default_topology leaves it, names none: it gives the same plan as NULL).  Which form runs
+ * depends on the shape and the topology, and with it the last bits of NN's and the score
+ * softmax's results: they are the same for every schedule, n_cu and flag, but not for every batch
+ * or m, wg_threads or wg_per_cu, nor for operands off 16-byte boundaries.
  *   BSM_GEMM_NT:  C_b = alpha * A_b * B_b^T    A_b m x k,  B_b n x k  (scores Q K^T)
  *   BSM_GEMM_NN:  C_b = alpha * A_b * B_b      A_b m x k,  B_b k x n  (context P V)
  * All operands row-major, batch after batch (A_b at b*m*k, B_b at b*n*k, C_b at b*m*n

@@ -445,6 +445,9 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     if (t.wg_threads != 0 && t.wg_threads != wg_threads)
         return fail(BSM_ERR_INVALID_ARG, "matrix-product plans run %d-thread workgroups (got %d)",
                     wg_threads, t.wg_threads);
+    // A topology with every field filled in, as bsm_default_topology leaves it, names no workgroup
+    // size of its own: the same plan as without a topology.
+    if (t.n_cu > 0 && t.n_xcd > 0 && t.piece_bytes > 0 && t.item_cost > 0.0f && t.row_cost > 0.0f) t.wg_threads = 0;
     // Row-tile workgroups, where they are the faster form, unless the topology names a workgroup
     // size or asks for more workgroups than a CU holds of them.
     int row = 0, parts = 0;

@@ -116,3 +116,19 @@ def test_general_forms_on_small_shapes(shape, layout, out):
     assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha, topology={"wg_threads": 256}, schedule="rr"), got)
     if layout == "nt":  # the same sums in the same order
         assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha), got)
+
+
+def test_default_topology_is_no_topology():
+    """bsm_default_topology's own values give the plan, and the bits, that NULL gives."""
+    shape = (2, 70, 1100, 72)
+    a, b = _operands(*shape, seed=9)
+    a_d, b_d = _dev_bf16(a), _dev_bf16(b)
+    stats = []
+    for topo in (None, bsm.bsm_default_topology(0)):
+        p = bsm.bsm_gemm_plan_create(*shape, "nt_softmax", "bf16", topology=topo, device=0)
+        st = bsm.bsm_plan_describe(p)
+        stats.append((st["wg_threads"], st["n_wg"], st["n_items"]))
+        p.destroy()
+    assert stats[0] == stats[1] and stats[0][0] == 512
+    assert np.array_equal(_product(shape, "nt_softmax", "bf16", a_d, b_d, 0.125, topology=bsm.bsm_default_topology(0)),
+                          _product(shape, "nt_softmax", "bf16", a_d, b_d, 0.125))

@@ -568,3 +568,23 @@ def test_default_workgroups_by_row_length(dtype, cols, n_wg):
                             topology=dict(n_cu=256, n_xcd=8))
     assert bsm.bsm_plan_describe(p)["n_wg"] == n_wg
     p.destroy()
+
+
+@pytest.mark.parametrize("layout,shape", [("nt", (473, 33, 64, 64)), ("nn", (16, 24, 96, 560)), ("nt_softmax", (32, 256, 2048, 128)),
+                                          ("nn", (384, 512, 128, 512))])
+def test_a_filled_in_topology_is_the_default_plan(layout, shape):
+    """A topology as bsm_default_topology fills it in (wg_threads 256 among its fields) gives the
+    plan that no topology gives, with any flag; wg_threads alone is a choice."""
+    def plan(topo):
+        p = bsm.bsm_gemm_plan_create(*shape, layout, "bf16", "balanced", topology=topo, device=-1)
+        st = bsm.bsm_plan_describe(p)
+        ptr, items, _, _ = bsm.bsm_plan_export(p)
+        p.destroy()
+        return (st["wg_threads"], st["n_wg"], st["trace_bytes"]), ptr, items
+
+    filled = dict(n_cu=256, n_xcd=8, wg_per_cu=0, wg_threads=256, piece_bytes=8192, item_cost=1024.0, row_cost=64.0)
+    want = plan(dict(n_cu=256, n_xcd=8))
+    for topo in (filled, dict(filled, flags=bsm.BSM_FLAG_TEMPORAL)):
+        got = plan(topo)
+        assert got[0] == want[0] and np.array_equal(got[1], want[1]) and np.array_equal(got[2], want[2])
+    assert plan(dict(n_cu=256, n_xcd=8, wg_threads=256))[0][0] == 256
