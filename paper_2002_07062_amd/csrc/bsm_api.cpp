@@ -445,6 +445,14 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     if (t.wg_threads != 0 && t.wg_threads != wg_threads)
         return fail(BSM_ERR_INVALID_ARG, "matrix-product plans run %d-thread workgroups (got %d)",
                     wg_threads, t.wg_threads);
+    hipDeviceProp_t prop{};
+    if (device >= 0) {
+        DeviceGuard g;
+        hipError_t e = g.enter(device);
+        if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
+        if (e != hipSuccess) return hip_fail(e, "hipGetDeviceProperties");
+    }
+    const int n_cu = t.n_cu > 0 ? t.n_cu : device >= 0 ? prop.multiProcessorCount : 256;
     // A topology with every field filled in, as bsm_default_topology leaves it, names no workgroup
     // size of its own: the same plan as without a topology.
     if (t.n_cu > 0 && t.n_xcd > 0 && t.piece_bytes > 0 && t.item_cost > 0.0f && t.row_cost > 0.0f) t.wg_threads = 0;
@@ -453,11 +461,11 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     int row = 0, parts = 0;
     if (t.wg_threads == 0 && batch > 0 && m > 0 && n > 0 && k > 0) {
         if (layout == BSM_GEMM_NT_SOFTMAX) row = bsm::gemm_row_softmax_waves(batch, m, n, k);
-        else parts = bsm::gemm_row_parts(layout, out_dtype == BSM_BF16, batch, m, n, k);
+        else parts = bsm::gemm_row_parts(layout, out_dtype == BSM_BF16, batch, m, n, k, n_cu);
         if (row > 0 && t.wg_per_cu > 8 / row) row = 0;
         if (parts > 0 && t.wg_per_cu > bsm::gemm_few_rows_wgs_per_cu(layout)) parts = 0;
         // one row tile per workgroup or less: no second and third workgroup per CU without any
-        if (parts > 0 && t.wg_per_cu == 0 && batch * ((m + 31) / 32) <= 256) t.wg_per_cu = 1;
+        if (parts > 0 && t.wg_per_cu == 0 && batch * ((m + 31) / 32) <= n_cu) t.wg_per_cu = 1;
     }
     if (row > 0) {
         wg_threads = 64 * row;
@@ -465,15 +473,10 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     }
     const bool single = layout == BSM_GEMM_NT_SOFTMAX && bsm::gemm_single_pass_shape(n, k) &&
                         (t.wg_per_cu == 0 || t.wg_per_cu <= bsm::gemm_waves_per_simd(true));
-    if (t.wg_per_cu == 0) t.wg_per_cu = bsm::gemm_default_wgs_per_cu(layout, batch, m, n, k, single);
+    if (t.wg_per_cu == 0) t.wg_per_cu = bsm::gemm_default_wgs_per_cu(layout, batch, m, n, k, n_cu, single);
     const bool bf16_out = out_dtype == BSM_BF16;
     bool wide = false;
     if (device >= 0) {
-        DeviceGuard g;
-        hipError_t e = g.enter(device);
-        hipDeviceProp_t prop;
-        if (e == hipSuccess) e = hipGetDeviceProperties(&prop, device);
-        if (e != hipSuccess) return hip_fail(e, "hipGetDeviceProperties");
         const int64_t per_wg = row > 0     ? bsm::gemm_row_lds_bytes_per_wg(row)
                                : parts > 0 ? bsm::gemm_few_rows_lds_bytes_per_wg(layout)
                                            : bsm::gemm_lds_bytes_per_wg(bf16_out, single);
@@ -481,7 +484,7 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
             per_wg * t.wg_per_cu > static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor))
             return fail(BSM_ERR_INVALID_ARG, "wg_per_cu %d: %lld bytes of LDS per workgroup do not fit",
                         t.wg_per_cu, static_cast<long long>(per_wg));
-        wide = bsm::gemm_wide_pays(layout, batch, m, n, k, t.wg_per_cu) &&
+        wide = bsm::gemm_wide_pays(layout, batch, m, n, k, n_cu, t.wg_per_cu) &&
                static_cast<int64_t>(bsm::gemm_wide_lds_bytes_per_wg(bf16_out)) * t.wg_per_cu <=
                    static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor);
     }

@@ -50,26 +50,26 @@ int gemm_wide_lds_bytes_per_wg(bool bf16_out) {
 // 31.7 -> 36.5, 225 x (512 x 512)(512 x 128) 43 -> 75, 192 x (512 x 512)(512 x 80) 39.5 -> 40.9, 96 x (1024 x
 // 1024)(1024 x 128) 64 -> 72; n = 512 gains too (192 x (512 x 512)(512 x 512) 145 -> 138) unless every
 // round has a batch index of its own (768 x (128 x 512)(512 x 256) 83 -> 93).
-static bool nn_three_per_cu(int64_t batch, int m, int n, int k) {
+static bool nn_three_per_cu(int64_t batch, int m, int n, int k, int n_cu) {
     const int64_t rounds = batch * ((m + 127) / 128);
-    return n > 80 && (n <= 128 || m > 128) && k <= 768 && rounds > 563 && rounds <= 768;
+    return n > 80 && (n <= 128 || m > 128) && k <= 768 && 10 * rounds > 22 * n_cu && rounds <= 3 * n_cu;
 }
 // kFormWide is compiled for two workgroups per CU.  With a third, which waits, it still pays over
 // several reduction steps (32 x (2048 x 2048)(2048 x 128) 105 us against kFormStep's 113), but not
 // over one (384 x (512 x 64)(64 x 100) 27.8 against 25.2; two per CU 23.9), nor where three is the
 // better number.
-bool gemm_wide_pays(int layout, int64_t batch, int m, int n, int k, int wgs_per_cu) {
+bool gemm_wide_pays(int layout, int64_t batch, int m, int n, int k, int n_cu, int wgs_per_cu) {
     if (wgs_per_cu <= bsm_mm::kS1WavesPerSimd) return true;
-    return k > bsm_mm::kChunkK && !(layout == bsm_mm::kNN && nn_three_per_cu(batch, m, n, k));
+    return k > bsm_mm::kChunkK && !(layout == bsm_mm::kNN && nn_three_per_cu(batch, m, n, k, n_cu));
 }
 int gemm_waves_per_simd(bool single_pass) {
     return single_pass ? bsm_mm::kS1WavesPerSimd : bsm_mm::kWavesPerSimd;
 }
-int gemm_default_wgs_per_cu(int layout, int64_t batch, int m, int n, int k, bool single_pass) {
+int gemm_default_wgs_per_cu(int layout, int64_t batch, int m, int n, int k, int n_cu, bool single_pass) {
     if (single_pass) return bsm_mm::kS1WavesPerSimd;
     const bool vec = k % 8 == 0 && (layout != bsm_mm::kNN || n % 8 == 0);  // as launch_gemm, aligned operands
     const int form = bsm_mm::form_of(layout, vec, true, n, k);
-    if (form == bsm_mm::kFormWide && nn_three_per_cu(batch, m, n, k)) return bsm_mm::kWavesPerSimd;
+    if (form == bsm_mm::kFormWide && nn_three_per_cu(batch, m, n, k, n_cu)) return bsm_mm::kWavesPerSimd;
     return form == bsm_mm::kFormStep ? bsm_mm::kWavesPerSimd : bsm_mm::waves_per_simd(layout, form);
 }
 int gemm_rows_per_wg(bool single_pass) {

@@ -103,13 +103,15 @@ int gemm_row_softmax_waves(int64_t batch, int m, int n, int k) {
     return n % kBlockN != 0 && 5 * batch * m > 4 * rounds * kS1Rows ? 4 : 0;
 }
 
-int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k) {
+// Lines that decide the last bits of a result (row tiles or not, for NN and the score softmax) are
+// those of a 256-CU card whatever n_cu the topology names, so that the bits do not depend on it.
+int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k, int n_cu) {
     if (batch * std::min(m, n) * k < 8 || (layout == kNT && k > 2 * kChunkK)) return 0;
     const int64_t tiles = batch * ((m + kTileM - 1) / kTileM);
     const int64_t blocks = (n + kBlockN - 1) / kBlockN;
     // column parts until three workgroups per CU have rows, at least four blocks (NN: one) to a part
     const int64_t most = layout == kNT ? (blocks + kRowWaves - 1) / kRowWaves : blocks;
-    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>({most, 8, 768 / tiles}));
+    const int64_t parts = std::max<int64_t>(1, std::min<int64_t>({most, 8, 3 * n_cu / tiles}));
     if (layout == kNT) {
         // Both forms' time by what their workgroups do, three to a CU, in steps of one 64-column
         // block.  The general form's units are 128 rows of the row stream, dealt whole; a unit
@@ -122,7 +124,7 @@ int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k
         // 512 x 512 (k = 128) 27.5 -> 36.6, 7324 x 512 x 16 120 -> 299, fp32 384 x 512 x 64 13.7 -> 19.1;
         // 4 x 2048 x 2048 (k = 128) 48 -> 12, 512 x 16 x 936 142 -> 30, 1000 x 128 x 300 62 -> 38, 473 x 33 x
         // 64 14.5 -> 8.7.
-        const double resident = 768.0;
+        const double resident = 3.0 * n_cu;  // either form: the same bits
         const int64_t units = (batch * m + 127) / 128;
         const double per_unit = m % 128 == 0 ? 1.0 : 128 % m == 0 ? 128.0 / m : 1.0 + 128.0 / m;
         const bool shared_lines = blocks > 1 && n % (bf16_out ? 64 : 32) != 0;

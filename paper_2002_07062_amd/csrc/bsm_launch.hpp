@@ -47,11 +47,11 @@ int gemm_wg_threads();
 bool gemm_single_pass_shape(int n, int k);
 int gemm_lds_bytes_per_wg(bool bf16_out, bool single_pass);
 int gemm_wide_lds_bytes_per_wg(bool bf16_out);  // of the forms with a 128-wide B block
-bool gemm_wide_pays(int layout, int64_t batch, int m, int n, int k, int wgs_per_cu);
+bool gemm_wide_pays(int layout, int64_t batch, int m, int n, int k, int n_cu, int wgs_per_cu);
 int gemm_waves_per_simd(bool single_pass);
 // Workgroups per CU when the topology does not say: as many as the form the shape takes is
 // compiled for.
-int gemm_default_wgs_per_cu(int layout, int64_t batch, int m, int n, int k, bool single_pass);
+int gemm_default_wgs_per_cu(int layout, int64_t batch, int m, int n, int k, int n_cu, bool single_pass);
 int gemm_rows_per_wg(bool single_pass);
 
 // Worker w of the table is workgroup w (gemm_wg_threads() threads, gemm_rows_per_wg() rows
@@ -77,7 +77,7 @@ hipError_t launch_gemm_row(int q, bool bf16_out, bool temporal, const void* a, c
 // a shape takes, 0 for the general form.
 int gemm_few_rows_lds_bytes_per_wg(int layout);
 int gemm_few_rows_wgs_per_cu(int layout);  // that a CU holds at once
-int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k);
+int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k, int n_cu);
 hipError_t launch_gemm_few_rows(int layout, int parts, bool bf16_out, bool temporal, const void* a, const void* b, void* c,
                                 int64_t batch, int m, int n, int k, float alpha, const int32_t* d_worker_ptr,
                                 const bsm_item* d_items, int n_wg, void* trace, hipStream_t stream);

@@ -588,3 +588,14 @@ def test_a_filled_in_topology_is_the_default_plan(layout, shape):
         got = plan(topo)
         assert got[0] == want[0] and np.array_equal(got[1], want[1]) and np.array_equal(got[2], want[2])
     assert plan(dict(n_cu=256, n_xcd=8, wg_threads=256))[0][0] == 256
+
+
+@pytest.mark.parametrize("layout,shape,small,large", [("nn", (8, 1024, 64, 333), 3, 1), ("nt", (8, 1024, 700, 64), 3, 1),
+                                                      ("nn", (24, 512, 128, 512), 3, 2), ("nn", (100, 512, 128, 512), 2, 2)])
+def test_workgroups_per_cu_follow_the_cus(layout, shape, small, large):
+    """Whether row tiles number no more than the CUs, and rounds no more than three per CU, is
+    asked of the CUs that the topology names: 32 here, against 256."""
+    for n_cu, per_cu in ((32, small), (256, large)):
+        p = bsm.bsm_gemm_plan_create(*shape, layout, "bf16", "balanced", topology=dict(n_cu=n_cu, n_xcd=8), device=-1)
+        assert bsm.bsm_plan_describe(p)["n_wg"] // n_cu == per_cu
+        p.destroy()
