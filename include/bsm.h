@@ -89,7 +89,8 @@ typedef enum bsm_schedule {
 typedef struct bsm_topology {
     int32_t n_cu;        /* compute units (MI355X: 256) */
     int32_t n_xcd;       /* XCDs (MI355X: 8); workgroup w is taken to run on XCD w mod n_xcd */
-    int32_t wg_per_cu;   /* persistent workgroups per CU; the grid has n_cu * wg_per_cu */
+    int32_t wg_per_cu;   /* persistent workgroups per CU; the grid has n_cu * wg_per_cu (matrix
+                            products of few rows: that many for each of several column parts) */
     int32_t wg_threads;  /* threads per workgroup, a multiple of 64 in [64, 1024]; plans with
                             rows longer than 2048 fp32 / 4096 bf16 elements run 256 (512 when
                             a row spans more than 16384 elements) whatever is asked: the
@@ -147,7 +148,8 @@ typedef struct bsm_plan_stats {
     int32_t n_workers;         /* entries of the work table's row pointer minus one */
     int32_t per_wave;          /* 1: workers are waves (w * waves_per_wg + wave); 0: workgroups
                                   (RR, and every plan with rows beyond the register tile) */
-    int32_t n_wg;              /* persistent workgroups in the grid */
+    int32_t n_wg;              /* persistent workgroups in the grid (matrix products whose rows
+                                  have column parts: n_workers for each part) */
     int32_t n_xcd;
     int32_t wg_threads;
     int32_t schedule;          /* bsm_schedule */
@@ -172,11 +174,12 @@ typedef struct bsm_plan_stats {
 
 /* One record per wave when a trace buffer is passed to bsm_plan_execute (32 bytes). */
 typedef struct bsm_trace_rec {
-    uint32_t wg;      /* workgroup index in the grid */
+    uint32_t wg;      /* workgroup index in the grid (with column parts: worker + n_workers * part) */
     uint32_t xcc_id;  /* XCD the wave ran on, from the hardware XCC_ID register */
     uint32_t hw_id;   /* raw hardware HW_ID register (wave, SIMD, CU, shader engine) */
-    uint32_t rows;    /* rows this wave processed (the one-pass score softmax of
-                       * BSM_GEMM_NT_SOFTMAX: two waves share each row, the first counts it) */
+    uint32_t rows;    /* rows this wave processed (matrix products whose waves share rows count
+                       * each once: the one-pass score softmax in the first wave of a pair, row
+                       * tiles in the first wave of the first column part's workgroup) */
     uint64_t t_start; /* constant-rate (100 MHz) real-time counter when the wave started */
     uint64_t t_end;   /* ... when it finished its last row */
 } bsm_trace_rec;

@@ -506,7 +506,8 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     p->table.per_wave = false;
     p->table.stats.per_wave = 0;
     p->table.stats.wg_threads = wg_threads;
-    p->table.stats.trace_bytes = static_cast<int64_t>(p->topo.n_wg()) * (wg_threads / 64) *
+    p->table.stats.n_wg = p->topo.n_wg() * std::max(1, parts);  // the workgroups of all column parts
+    p->table.stats.trace_bytes = static_cast<int64_t>(p->table.stats.n_wg) * (wg_threads / 64) *
                                  static_cast<int64_t>(sizeof(bsm_trace_rec));
     p->gemm = true;
     p->gemm_m = m;

@@ -511,8 +511,8 @@ bsm_gemm_row_kernel(const uint16_t* a, const uint16_t* b, void* c, Shape s,
     if (trace && lane == 0) write_trace(trace, w, wave, Q, done, t0);
 }
 
-// The plain products: gridDim.y parts of the columns of every worker's rows; only the first
-// leaves a trace.
+// The plain products: gridDim.y parts of the columns of every worker's rows.  In a trace, the
+// workgroups of the first part come first and count the rows.
 template <int LAYOUT, bool BF16OUT, int OPS, bool TEMPORAL, int NK>
 __global__ void __launch_bounds__(64 * kRowWaves, kWavesPerSimd)
 bsm_gemm_few_rows_kernel(const uint16_t* a, const uint16_t* b, void* c, Shape s,
@@ -532,7 +532,8 @@ bsm_gemm_few_rows_kernel(const uint16_t* a, const uint16_t* b, void* c, Shape s,
     else
         done = row_nn_worker<BF16OUT, OPS, TEMPORAL, Q>(a, b, c, s, rounds, wave, lane, blockIdx.y, gridDim.y,
                                                         bsm_gemm_row_lds);
-    if (trace && lane == 0 && blockIdx.y == 0) write_trace(trace, w, wave, Q, done, t0);
+    if (trace && lane == 0)
+        write_trace(trace, w + static_cast<int>(blockIdx.y * gridDim.x), wave, Q, blockIdx.y == 0 ? done : 0, t0);
 }
 
 }  // namespace bsm_mm

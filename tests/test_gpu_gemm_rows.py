@@ -132,3 +132,27 @@ def test_default_topology_is_no_topology():
     assert stats[0] == stats[1] and stats[0][0] == 512
     assert np.array_equal(_product(shape, "nt_softmax", "bf16", a_d, b_d, 0.125, topology=bsm.bsm_default_topology(0)),
                           _product(shape, "nt_softmax", "bf16", a_d, b_d, 0.125))
+
+
+@pytest.mark.parametrize("layout,shape", [("nt", (1, 40, 2050, 128)), ("nn", (2, 64, 500, 130)), ("nt", (40, 200, 300, 64))])
+def test_trace_has_every_column_part(layout, shape):
+    """Column parts leave a record per wave each, with the times of their own work; the rows are
+    counted once."""
+    batch, m, n, k = shape
+    print(f"[trace parts {layout} {shape}]", flush=True)
+    a, b = _operands(*shape, seed=10)
+    p = bsm.bsm_gemm_plan_create(*shape, layout, "f32", device=0)
+    st = bsm.bsm_plan_describe(p)
+    waves = st["wg_threads"] // 64
+    assert st["n_wg"] > st["n_workers"]
+    c = torch.empty(batch * m * n, device="cuda")
+    trace = torch.full((st["trace_bytes"] + 32,), 255, dtype=torch.uint8, device="cuda")
+    bsm.bsm_gemm_execute(p, _dev_bf16(a), _dev_bf16(b), c, 0.25, trace=trace)
+    torch.cuda.synchronize()
+    p.destroy()
+    rec = trace.cpu().numpy().view(bsm.TRACE_DTYPE)
+    assert rec["wg"][-1] == 0xFFFFFFFF, "written past the trace"
+    rec = rec[:-1]
+    assert np.array_equal(rec["wg"], np.repeat(np.arange(st["n_wg"], dtype=np.uint32), waves))
+    assert np.all(rec["t_start"] > 0) and np.all(rec["t_end"] >= rec["t_start"])
+    assert int(rec["rows"].sum()) == batch * m

@@ -597,5 +597,18 @@ def test_workgroups_per_cu_follow_the_cus(layout, shape, small, large):
     asked of the CUs that the topology names: 32 here, against 256."""
     for n_cu, per_cu in ((32, small), (256, large)):
         p = bsm.bsm_gemm_plan_create(*shape, layout, "bf16", "balanced", topology=dict(n_cu=n_cu, n_xcd=8), device=-1)
-        assert bsm.bsm_plan_describe(p)["n_wg"] // n_cu == per_cu
+        assert bsm.bsm_plan_describe(p)["n_workers"] // n_cu == per_cu
         p.destroy()
+
+
+@pytest.mark.parametrize("layout,shape,parts", [("nt", (1, 1, 2050, 128), 8), ("nn", (1, 64, 500, 130), 8), ("nt", (40, 200, 300, 64), 2),
+                                                ("nn", (16, 512, 64, 64), 1), ("nt_softmax", (4, 64, 600, 64), 1)])
+def test_plan_stats_count_every_column_part(layout, shape, parts):
+    """Row tiles of few rows split a worker's columns over several workgroups: the grid and the
+    trace have records for all of them."""
+    p = bsm.bsm_gemm_plan_create(*shape, layout, "f32", "balanced", topology=dict(n_cu=256, n_xcd=8), device=-1)
+    d = bsm.bsm_plan_describe(p)
+    assert p.trace_bytes == d["trace_bytes"]
+    p.destroy()
+    assert d["n_wg"] == parts * d["n_workers"]
+    assert d["trace_bytes"] == d["n_wg"] * (d["wg_threads"] // 64) * bsm.TRACE_DTYPE.itemsize
