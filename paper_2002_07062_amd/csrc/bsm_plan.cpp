@@ -43,20 +43,20 @@ int64_t row_cost_of(const Topology& t, int elem_bytes, int32_t cols) {
     return static_cast<int64_t>(std::llround(t.row_cost)) + static_cast<int64_t>(cols) * 2 * elem_bytes;
 }
 
-// Appends a span, merging it into the previous one when it continues it in memory with the
-// same row length (adjacent slices of equal C form one longer run of rows; with slice_elems > 0
-// only rows of one slice do).
+// Extends a span by one that continues it in memory with the same row length (adjacent slices of
+// equal C form one longer run of rows; with slice_elems > 0 only rows of one slice do).
+bool extend_span(Span* b, const Span& s, int64_t slice_elems) {
+    if (b->cols != s.cols || b->off + static_cast<int64_t>(b->nrows) * b->cols != s.off ||
+        static_cast<int64_t>(b->nrows) + s.nrows > std::numeric_limits<int32_t>::max() ||
+        (slice_elems > 0 && s.off % slice_elems == 0))
+        return false;
+    b->nrows += s.nrows;
+    return true;
+}
+
+// Appends a span, or extends the last one.
 void push_span(std::vector<Span>* v, Span s, int64_t slice_elems = 0) {
-    if (s.nrows <= 0) return;
-    if (!v->empty()) {
-        Span& b = v->back();
-        if ((slice_elems == 0 || b.off / slice_elems == s.off / slice_elems) && b.cols == s.cols && b.off + static_cast<int64_t>(b.nrows) * b.cols == s.off &&
-            static_cast<int64_t>(b.nrows) + s.nrows <= std::numeric_limits<int32_t>::max()) {
-            b.nrows += s.nrows;
-            return;
-        }
-    }
-    v->push_back(s);
+    if (s.nrows > 0 && (v->empty() || !extend_span(&v->back(), s, slice_elems))) v->push_back(s);
 }
 
 // A stream segment of n_units equal units of unit_rows rows, each costing unit_cost.
@@ -85,66 +85,143 @@ std::vector<Segment> segments_of(const std::vector<Span>& stream, const Topology
     return segs;
 }
 
+// Consecutive bins of a stream: bin j holds spans [first[j], first[j + 1]).
+struct Bins {
+    std::vector<Span> spans;
+    std::vector<int64_t> first;
+};
+
 // Cuts the stream into K consecutive bins with costs proportional to `weights` (all equal when
 // empty), at unit boundaries.  A unit occupying cost interval [a, a + c) of the total T goes to
 // the bin whose cumulative-weight interval holds its scaled midpoint: the largest j with
 // cw[j] <= W (a + c/2) / T.  Every bin is then within one unit's cost of its share; bins of
-// zero weight get nothing.
+// zero weight get nothing.  Midpoints only grow along the stream, so the bin is counted up from
+// the last unit's (80 thousand units of 20000 x 128 x 600: 22 ms with a search and a 128-bit
+// division for each and a vector per bin, 4.5 ms so).
 void cut_stream(const std::vector<Segment>& segs, const std::vector<int64_t>& weights, int64_t K,
-                std::vector<std::vector<Span>>* bins) {
-    bins->assign(static_cast<size_t>(K), {});
+                Bins* bins) {
+    bins->spans.clear();
+    bins->first.assign(static_cast<size_t>(std::max<int64_t>(K, 0)) + 1, 0);
     if (K <= 0) return;
-    std::vector<i128> cw(static_cast<size_t>(K) + 1, 0);
-    for (int64_t j = 0; j < K; ++j)
-        cw[j + 1] = cw[j] + (weights.empty() ? 1 : std::max<int64_t>(0, weights[j]));
-    const i128 W = cw[K];
+    std::vector<i128> cw;  // cumulative weights; all equal: cw[j] = j
+    if (!weights.empty()) {
+        cw.assign(static_cast<size_t>(K) + 1, 0);
+        for (int64_t j = 0; j < K; ++j) cw[j + 1] = cw[j] + std::max<int64_t>(0, weights[j]);
+    }
+    const i128 W = weights.empty() ? static_cast<i128>(K) : cw[K];
     i128 T = 0;
     for (const Segment& s : segs) T += static_cast<i128>(s.n_units) * s.unit_cost;
     if (T == 0 || W == 0) return;
 
+    std::vector<Span>& out = bins->spans;
+    int64_t bin = 0;
+    // bins before the last one end where the scaled cost reaches 2 T cw[bin + 1]
+    auto end_of = [&](int64_t j) { return 2 * T * (weights.empty() ? static_cast<i128>(j + 1) : cw[j + 1]); };
+    i128 bound = end_of(0);
     i128 A0 = 0;  // stream cost before the current segment
     for (const Segment& s : segs) {
-        const i128 c = s.unit_cost;
-        // Unit u's midpoint scaled by 2W: pos(u) = W (2 A0 + (2u + 1) c); its bin is the
-        // largest j with 2 T cw[j] <= pos(u).
-        auto bin_of = [&](int64_t u) -> int64_t {
-            const i128 pos = W * (2 * A0 + (2 * static_cast<i128>(u) + 1) * c);
-            int64_t lo = 0, hi = K - 1;
-            while (lo < hi) {
-                const int64_t mid = (lo + hi + 1) / 2;
-                if (2 * T * cw[mid] <= pos) lo = mid; else hi = mid - 1;
-            }
-            return lo;
-        };
+        // unit u's midpoint scaled by 2 W: W (2 A0 + (2 u + 1) c)
+        const i128 step = 2 * W * s.unit_cost;
+        i128 pos = W * (2 * A0 + s.unit_cost);
         int64_t u = 0;
         while (u < s.n_units) {
-            const int64_t b = bin_of(u);
-            int64_t u_end = s.n_units;
-            if (b + 1 < K) {
-                // first unit v with W (2 A0 + (2v + 1) c) >= 2 T cw[b+1]
-                const i128 need = 2 * T * cw[b + 1] - W * (2 * A0 + c);
-                const i128 den = 2 * W * c;
-                i128 v = need <= 0 ? 0 : (need + den - 1) / den;
-                if (v < u + 1) v = u + 1;
-                if (v < u_end) u_end = static_cast<int64_t>(v);
+            while (bin + 1 < K && bound <= pos) {
+                bins->first[++bin] = static_cast<int64_t>(out.size());
+                bound = end_of(bin);
             }
-            const int64_t r0 = u * s.unit_rows;
-            const int64_t nr = (u_end - u) * s.unit_rows;
-            push_span(&(*bins)[b], Span{s.off + r0 * s.cols, s.cols, static_cast<int32_t>(nr)});
-            u = u_end;
+            int64_t n = s.n_units - u;  // units that stay in this bin: those whose midpoint is below its end
+            if (bin + 1 < K && n > 1) {
+                const i128 room = bound - pos;  // > 0
+                if (room <= step) {
+                    n = 1;
+                } else {
+                    const i128 fit = (room >> 62) == 0 && (step >> 62) == 0
+                                         ? (static_cast<int64_t>(room) + static_cast<int64_t>(step) - 1) / static_cast<int64_t>(step)
+                                         : (room + step - 1) / step;
+                    if (fit < n) n = static_cast<int64_t>(fit);
+                }
+            }
+            const Span v{s.off + u * s.unit_rows * s.cols, s.cols, static_cast<int32_t>(n * s.unit_rows)};
+            if (static_cast<int64_t>(out.size()) == bins->first[bin] || !extend_span(&out.back(), v, 0)) out.push_back(v);
+            u += n;
+            pos += n * step;
         }
-        A0 += static_cast<i128>(s.n_units) * c;
+        A0 += static_cast<i128>(s.n_units) * s.unit_cost;
     }
+    while (bin < K) bins->first[++bin] = static_cast<int64_t>(out.size());
 }
 
 i128 span_cost(const Span& s, const Topology& t, int es) {
     return static_cast<i128>(s.nrows) * row_cost_of(t, es, s.cols);
 }
 
+// The worker that takes each bin of every round: in each round the largest pieces go to the
+// workers with the least accumulated cost (ties to the lower bin and worker).  Cost: an integer
+// type that holds the stream's total.
+template <class Cost>
+void deal_rounds(const Bins& bins, int64_t n_rounds, const std::vector<int32_t>& workers, const Topology& t, int es,
+                 std::vector<std::vector<Span>>* per_worker) {
+    const int64_t W = static_cast<int64_t>(workers.size());
+    struct Entry {
+        Cost key;
+        int32_t at;
+    };
+    std::vector<Cost> acc(static_cast<size_t>(W), 0);
+    std::vector<Entry> piece(static_cast<size_t>(W)), slot(static_cast<size_t>(W));
+    // Ascending keys, equal ones in index order (as they come in).  Most rounds come sorted, and
+    // where all slices are alike the keys take a few values: such entries are dealt to one
+    // bucket per value.
+    constexpr int kBuckets = 32;
+    std::vector<Entry> sorted(static_cast<size_t>(W));
+    std::vector<uint8_t> bucket(static_cast<size_t>(W));
+    auto order = [&](std::vector<Entry>* v) {
+        auto less = [](const Entry& a, const Entry& b) { return a.key < b.key || (a.key == b.key && a.at < b.at); };
+        if (std::is_sorted(v->begin(), v->end(), less)) return;
+        Cost value[kBuckets];
+        int64_t start[kBuckets] = {}, count[kBuckets] = {};
+        int n = 0;
+        for (int64_t k = 0; k < W; ++k) {
+            int i = 0;
+            while (i < n && value[i] != (*v)[k].key) ++i;
+            if (i == n) {
+                if (n == kBuckets) {
+                    std::sort(v->begin(), v->end(), less);
+                    return;
+                }
+                value[n++] = (*v)[k].key;
+            }
+            bucket[k] = static_cast<uint8_t>(i);
+            ++count[i];
+        }
+        for (int i = 0; i < n; ++i)
+            for (int j = 0; j < n; ++j)
+                if (value[j] < value[i]) start[i] += count[j];
+        for (int64_t k = 0; k < W; ++k) sorted[start[bucket[k]]++] = (*v)[k];
+        v->swap(sorted);
+    };
+    for (int32_t w : workers) (*per_worker)[w].reserve(static_cast<size_t>(std::min<int64_t>(n_rounds, 64)));
+    for (int64_t r = 0; r < n_rounds; ++r) {
+        for (int64_t k = 0; k < W; ++k) {
+            Cost c = 0;
+            for (int64_t i = bins.first[r * W + k]; i < bins.first[r * W + k + 1]; ++i)
+                c += static_cast<Cost>(span_cost(bins.spans[i], t, es));
+            piece[k] = Entry{-c, static_cast<int32_t>(k)};
+            slot[k] = Entry{acc[k], static_cast<int32_t>(k)};
+        }
+        order(&piece);
+        order(&slot);
+        for (int64_t k = 0; k < W; ++k) {
+            const int64_t bin = r * W + piece[k].at;
+            acc[slot[k].at] -= piece[k].key;
+            std::vector<Span>& mine = (*per_worker)[workers[slot[k].at]];
+            for (int64_t i = bins.first[bin]; i < bins.first[bin + 1]; ++i) push_span(&mine, bins.spans[i]);
+        }
+    }
+}
+
 // Rounds for one team: the stream is cut into n_rounds * W bins of equal cost (whole tile
-// steps of the kernel where possible); in each round the largest pieces go to the workers
-// with the least accumulated cost (ties to the lower worker), which keeps every worker's total
-// within about one piece-granule of the others.
+// steps of the kernel where possible), dealt to the workers round by round, which keeps every
+// worker's total within about one piece-granule of the others.
 int64_t assign_rounds(const std::vector<Span>& stream, const std::vector<int32_t>& workers,
                       const Topology& t, int es, int kernel_class,
                       std::vector<std::vector<Span>>* per_worker) {
@@ -161,28 +238,10 @@ int64_t assign_rounds(const std::vector<Span>& stream, const std::vector<int32_t
     int64_t n_rounds = static_cast<int64_t>(std::llround(static_cast<double>(total) / per_round));
     n_rounds = std::min<int64_t>(n_rounds, n_units / W);
     n_rounds = std::max<int64_t>(1, std::min<int64_t>(n_rounds, kMaxBins / W));
-    std::vector<std::vector<Span>> bins;
+    Bins bins;
     cut_stream(segs, {}, n_rounds * W, &bins);
-
-    std::vector<i128> acc(static_cast<size_t>(W), 0);
-    std::vector<i128> cost(static_cast<size_t>(W));
-    std::vector<int64_t> ob(static_cast<size_t>(W)), ow(static_cast<size_t>(W));
-    for (int64_t r = 0; r < n_rounds; ++r) {
-        for (int64_t k = 0; k < W; ++k) {
-            i128 c = 0;
-            for (const Span& s : bins[r * W + k]) c += span_cost(s, t, es);
-            cost[k] = c;
-        }
-        std::iota(ob.begin(), ob.end(), 0);
-        std::iota(ow.begin(), ow.end(), 0);
-        std::stable_sort(ob.begin(), ob.end(), [&](int64_t a, int64_t b) { return cost[a] > cost[b]; });
-        std::stable_sort(ow.begin(), ow.end(), [&](int64_t a, int64_t b) { return acc[a] < acc[b]; });
-        for (int64_t k = 0; k < W; ++k) {
-            const int64_t slot = ow[k], bin = ob[k];
-            acc[slot] += cost[bin];
-            for (const Span& s : bins[r * W + bin]) push_span(&(*per_worker)[workers[slot]], s);
-        }
-    }
+    if ((total >> 62) == 0) deal_rounds<int64_t>(bins, n_rounds, workers, t, es, per_worker);
+    else deal_rounds<i128>(bins, n_rounds, workers, t, es, per_worker);
     return n_rounds;
 }
 
@@ -373,10 +432,10 @@ std::vector<std::vector<Span>> xcd_streams(const Geometry& g, const Topology& t,
             moved_cost += static_cast<double>(p.nrows) * row_cost_of(t, es, g.C[p.slice]);
             moved_bytes += static_cast<int64_t>(p.nrows) * g.C[p.slice] * 2 * es;
         }
-        std::vector<std::vector<Span>> recv;
+        Bins recv;
         cut_stream(segments_of(pool_spans, t, es, 0, false), deficit, n, &recv);
         for (int x = 0; x < n; ++x)
-            for (const Span& s : recv[x]) push_span(&stream[x], s, t.slice_elems);
+            for (int64_t i = recv.first[x]; i < recv.first[x + 1]; ++i) push_span(&stream[x], recv.spans[i], t.slice_elems);
         tab->stats.moved_cost = moved_cost;
         tab->stats.moved_bytes = moved_bytes;
         // Each XCD takes its rows in memory order, received ones included, so that the eight
@@ -394,12 +453,18 @@ std::vector<std::vector<Span>> xcd_streams(const Geometry& g, const Topology& t,
 // Locates the slice holding element `e` (which lies inside some non-empty slice).
 struct SliceIndex {
     std::vector<std::pair<int64_t, int32_t>> starts;  // (offset, slice), non-empty slices
+    int64_t per_slice = 0;                            // > 0: slice s starts at s * per_slice
     explicit SliceIndex(const Geometry& g) {
+        if (g.batch > 0) per_slice = static_cast<int64_t>(g.R[0]) * g.C[0];
+        for (int64_t s = 0; s < g.batch && per_slice > 0; ++s)
+            if (g.off[s] != s * per_slice || static_cast<int64_t>(g.R[s]) * g.C[s] != per_slice) per_slice = 0;
+        if (per_slice > 0) return;
         for (int64_t s = 0; s < g.batch; ++s)
             if (g.R[s] > 0 && g.C[s] > 0) starts.emplace_back(g.off[s], static_cast<int32_t>(s));
-        std::sort(starts.begin(), starts.end());
+        if (!std::is_sorted(starts.begin(), starts.end())) std::sort(starts.begin(), starts.end());
     }
     int32_t find(int64_t e) const {
+        if (per_slice > 0) return static_cast<int32_t>(e / per_slice);
         auto it = std::upper_bound(starts.begin(), starts.end(),
                                    std::make_pair(e, std::numeric_limits<int32_t>::max()));
         return (it == starts.begin()) ? -1 : std::prev(it)->second;

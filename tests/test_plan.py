@@ -612,3 +612,58 @@ def test_plan_stats_count_every_column_part(layout, shape, parts):
     p.destroy()
     assert d["n_wg"] == parts * d["n_workers"]
     assert d["trace_bytes"] == d["n_wg"] * (d["wg_threads"] // 64) * bsm.TRACE_DTYPE.itemsize
+
+
+def _balanced_by_the_book(batch, m, n, es, unit, workers, row_cost=64, piece_bytes=8192):
+    """BALANCED for `batch` slices of m x n rows cut in units of `unit` rows that start over in
+    every slice, by the rule's words: every unit goes to the bin that holds its cost midpoint,
+    and in every round the largest bins go to the least loaded workers."""
+    rc = row_cost + 2 * n * es
+    units = [(s * m + r, min(unit, m - r)) for s in range(batch) for r in range(0, m, unit)]
+    total = batch * m * rc
+    W = len(workers)
+    rounds = max(1, min(int(total / (W * piece_bytes) + 0.5), len(units) // W))
+    K, at = rounds * W, 0
+    bins = [[] for _ in range(K)]
+    for row, rows in units:
+        c = rows * rc
+        b = bins[min(K - 1, K * (2 * at + c) // (2 * total))]
+        if b and b[-1][0] + b[-1][1] == row:
+            b[-1] = (b[-1][0], b[-1][1] + rows)
+        else:
+            b.append((row, rows))
+        at += c
+    load, mine = [0] * W, {w: [] for w in workers}
+    for r in range(rounds):
+        mass = [sum(x[1] for x in b) * rc for b in bins[r * W:(r + 1) * W]]
+        pieces = sorted(range(W), key=lambda k: (-mass[k], k))
+        for k, slot in zip(pieces, sorted(range(W), key=lambda k: (load[k], k))):
+            load[slot] += mass[k]
+            for row, rows in bins[r * W + k]:
+                v = mine[workers[slot]]
+                if v and v[-1][0] + v[-1][1] == row:
+                    v[-1] = (v[-1][0], v[-1][1] + rows)
+                else:
+                    v.append((row, rows))
+    return mine
+
+
+@pytest.mark.parametrize("n_cu,n_xcd", [(256, 8), (5, 2), (1, 1)])
+@pytest.mark.parametrize("shape", [(7, 129, 600, 128), (90, 333, 700, 64), (700, 24, 520, 96), (31, 70, 2048, 8), (900, 3, 1000, 40)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_balanced_products_follow_the_rule(shape, n_cu, n_xcd):
+    """The table of a product by row tiles, item by item, against the rule done naively: few
+    and many rounds, pieces of a few sizes and of many, workers that get nothing."""
+    batch, m, n, k = shape
+    p = bsm.bsm_gemm_plan_create(*shape, "nt_softmax", "bf16", "balanced", topology=dict(n_cu=n_cu, n_xcd=n_xcd), device=-1)
+    d = bsm.bsm_plan_describe(p)
+    ptr, items, _, _ = bsm.bsm_plan_export(p)
+    p.destroy()
+    order = [w for x in range(n_xcd) for w in range(x, d["n_workers"], n_xcd)]
+    want = _balanced_by_the_book(batch, m, n, 2, 32, order)
+    for w in range(d["n_workers"]):
+        got = [(int(it["elem_offset"]) // n + j * int(it["rep_stride"]), int(it["nrows"]))
+               for it in items[ptr[w]:ptr[w + 1]] for j in range(it["reps"])]
+        assert got == want[w], (w, got[:3], want[w][:3])
+    assert np.array_equal(items["slice"], items["elem_offset"] // (m * n))
+    assert np.array_equal(items["row_begin"], items["elem_offset"] // n % m)
