@@ -10,6 +10,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <limits>
 #include <list>
 #include <memory>
 #include <mutex>
@@ -272,7 +273,8 @@ bsm_status create_plan(bsm_plan* out_plan, const int64_t* offs, const int32_t* r
                        const int32_t* cols, int64_t batch, bsm_dtype dtype, bsm_schedule schedule,
                        const int8_t* home_xcd, const float* xcd_weight,
                        const bsm_topology* topology, int device, int32_t row_unit = 0,
-                       bool product = false, bool upload = true, int64_t slice_elems = 0) {
+                       bool product = false, bool upload = true, int64_t slice_elems = 0,
+                       bool class_of_longer_rows = false) {
     if (!out_plan) return fail(BSM_ERR_INVALID_ARG, "out_plan is NULL");
     *out_plan = nullptr;
     if (!valid_dtype(dtype)) return fail(BSM_ERR_INVALID_ARG, "unknown dtype %d", static_cast<int>(dtype));
@@ -293,6 +295,8 @@ bsm_status create_plan(bsm_plan* out_plan, const int64_t* offs, const int32_t* r
         if (!err.empty()) return fail(BSM_ERR_INVALID_ARG, "geometry: %s", err.c_str());
         p->shifted = any_shifted(p->geo);
         p->kernel_class = bsm::kernel_class_for(p->geo.max_cols, elem_bytes_of(dtype));
+        if (class_of_longer_rows && p->geo.max_cols <= std::numeric_limits<int32_t>::max() - bsm::kVecBytes)
+            p->kernel_class = bsm::kernel_class_for(p->geo.max_cols + bsm::kVecBytes / elem_bytes_of(dtype), elem_bytes_of(dtype));
         // Rows beyond the register tile are worked by whole workgroups (team_threads of the
         // class), one row at a time: such plans run that workgroup size whatever the topology
         // asks (a row's bits depend on it), and every worker of their table is a workgroup.
@@ -1069,6 +1073,16 @@ bsm_status softmax_noalloc(const void* in, void* out, const int64_t* slice_offse
                      nullptr, device, 0, false, false);
     if (st != BSM_OK) return st;
     std::unique_ptr<bsm_plan_s> p(raw);  // host table only
+    // Shifted rows were once counted as the aligned vectors around them, one vector longer, which
+    // put the longest rows of a class into the next one.  That may have fewer workers, and a
+    // smaller table: what fitted then still has to.
+    if (p->shifted && table_bytes(p->table) > static_cast<size_t>(BSM_NOALLOC_SCRATCH_BYTES)) {
+        st = create_plan(&raw, slice_offsets, rows, cols, batch, dtype, schedule, nullptr, nullptr,
+                         nullptr, device, 0, false, false, 0, true);
+        if (st != BSM_OK) return st;
+        std::unique_ptr<bsm_plan_s> q(raw);
+        if (table_bytes(q->table) <= static_cast<size_t>(BSM_NOALLOC_SCRATCH_BYTES)) p.swap(q);
+    }
     const size_t need = table_bytes(p->table);
     if (need > static_cast<size_t>(BSM_NOALLOC_SCRATCH_BYTES))
         return fail(BSM_ERR_INVALID_ARG,

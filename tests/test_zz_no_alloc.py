@@ -111,3 +111,26 @@ def test_noalloc_rejects_a_table_beyond_the_buffer():
     assert "exceeds" in e.value.message and str(bsm.BSM_NOALLOC_SCRATCH_BYTES) in e.value.message
     torch.cuda.synchronize()
     assert np.all(to_host_bits(out) == np.uint32(0x7FC0DEAD))
+
+
+@pytest.mark.parametrize("dtype,longest,B", [("f32", 2048, 262340), ("bf16", 4093, 262000)])
+def test_noalloc_takes_a_table_that_fits_with_fewer_workers(dtype, longest, B):
+    """One-row slices that hardly an item joins, and one of the longest shifted rows of kernel
+    class 3: with that class's workers (one per wave) the table is a few KiB too large for the
+    buffer, with those of class 4 (one per workgroup) it fits. The bits are bsm_softmax's."""
+    cols = np.where(np.arange(B) % 2 == 0, 5, 6).astype(np.int32)
+    cols[0] = longest
+    rows = np.ones(B, np.int32)
+    offs = np.concatenate([[1], 1 + np.cumsum(cols.astype(np.int64) + 1)])[:B]
+    n = int(offs[-1] + cols[-1])
+    x = torch.randn(n, device="cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+    print(f"[noalloc table {dtype}]", flush=True)
+    out, ref = sentinel_like(n, dtype), sentinel_like(n, dtype)
+    bsm.bsm_softmax_noalloc(x, out, rows, cols, slice_offsets=offs)
+    bsm.bsm_softmax(x, ref, rows, cols, slice_offsets=offs)
+    torch.cuda.synchronize()
+    assert np.array_equal(to_host_bits(out), to_host_bits(ref))
+    ends = torch.tensor(offs, device="cuda")[None, 1::2] + torch.arange(6, device="cuda")[:, None]
+    want = torch.softmax(x[ends].double(), 0)
+    assert float((out[ends].double() - want).abs().max()) < (1e-6 if dtype == "f32" else 2.0 ** -8)
+    bsm.bsm_cache_clear()
