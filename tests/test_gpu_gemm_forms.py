@@ -58,12 +58,17 @@ def test_forms_against_the_oracle_and_each_other(shape, layout, out):
         assert np.array_equal(_product(shape, layout, out, a_d, b_d, alpha, topology={"wg_threads": 256, "wg_per_cu": 4}), general)
 
 
-@pytest.mark.parametrize("n,k", [(520, 128), (700, 72), (513, 64)])
-def test_two_pass_softmax_forms_past_512_columns(n, k):
+@pytest.mark.parametrize("n,k", [(520, 128), (700, 72), (513, 64), (600, 136), (513, 100), (64, 40)])
+def test_two_pass_softmax_forms(n, k):
+    """A named workgroup size keeps the two passes: A in registers for one and for two slices
+    of k, A staged at every step, operands at any boundary, and one column block."""
     batch, m = 2, 70
     a, b = _operands(batch, m, n, k, seed=400 + n)
     a_d, b_d = _dev_bf16(a), _dev_bf16(b)
     for alpha in (0.125, -0.125):
-        got = _product((batch, m, n, k), "nt_softmax", "f32", a_d, b_d, alpha)
-        check_softmax(got, a, b, batch, m, n, k, alpha, "f32")
-        assert np.array_equal(_product((batch, m, n, k), "nt_softmax", "f32", a_d, b_d, alpha, schedule="xcd"), got)
+        for out in ("f32", "bf16"):
+            got = _product((batch, m, n, k), "nt_softmax", out, a_d, b_d, alpha, topology={"wg_threads": 256})
+            check_softmax(got, a, b, batch, m, n, k, alpha, out)
+            for topology in ({"wg_threads": 256, "flags": bsm.BSM_FLAG_TEMPORAL}, {"wg_threads": 256, "n_cu": 3}):
+                assert np.array_equal(_product((batch, m, n, k), "nt_softmax", out, a_d, b_d, alpha, topology=topology,
+                                               schedule="xcd"), got)

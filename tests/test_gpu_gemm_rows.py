@@ -40,8 +40,9 @@ def test_row_tiles_against_the_oracle(shape, out):
     assert np.array_equal(_product(shape, "nt_softmax", out, *odd, 0.125), want)
 
 
+@pytest.mark.parametrize("topology", [None, {"wg_threads": 256}], ids=["row tiles", "two passes"])
 @pytest.mark.parametrize("n,k", [(520, 72), (1100, 64)])
-def test_infinite_operands(n, k):
+def test_infinite_operands(n, k, topology):
     """-inf, +inf and NaN in one row of B reach the row's column only as the softmax says: a
     logit of -inf is a probability of 0, one of +inf or NaN makes its row NaN; the last row of B,
     that stands in for rows past n, is -inf."""
@@ -50,11 +51,14 @@ def test_infinite_operands(n, k):
     b = _operands(1, m, n, k, seed=8)[1].copy()
     b.reshape(n, k)[[3, n - 1]] = 0xFF80
     a_d, b_d = _dev_bf16(a), _dev_bf16(b)
-    got = bits_to_f64(_product((1, m, n, k), "nt_softmax", "f32", a_d, b_d, 0.01)).reshape(m, n)
+    got = bits_to_f64(_product((1, m, n, k), "nt_softmax", "f32", a_d, b_d, 0.01, topology=topology)).reshape(m, n)
     assert np.all(got[:, [3, n - 1]] == 0.0) and np.allclose(got.sum(1), 1.0, atol=1e-5)
-    b.reshape(n, k)[5, 0] = 0x7F80
-    got = bits_to_f64(_product((1, m, n, k), "nt_softmax", "f32", a_d, _dev_bf16(b), 0.01))
-    assert np.all(np.isnan(got))
+    for special in (0x7F80, 0x7FC0):
+        for row in (5, n // 2, n - 2):  # the first, a middle and the last column block
+            c = b.copy()
+            c.reshape(n, k)[row, 0] = special
+            got = bits_to_f64(_product((1, m, n, k), "nt_softmax", "f32", a_d, _dev_bf16(c), 0.01, topology=topology))
+            assert np.all(np.isnan(got))
 
 
 def test_plan_takes_the_row_tiles():
