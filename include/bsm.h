@@ -157,8 +157,7 @@ typedef struct bsm_plan_stats {
     int32_t n_overlap;         /* XCD: slices straddling two or more virtual banks */
     int32_t max_cols;          /* longest row */
     int32_t kernel_class;      /* which kernel instance the plan launches (internal) */
-    int32_t lds_bytes_per_wave; /* LDS each wave may stage a row in; 0: none (rows are held in
-                                   registers, or read twice) */
+    int32_t lds_bytes_per_wave; /* 0: no kernel stages rows in LDS (the field keeps its place) */
     int32_t flags;             /* the BSM_FLAG_* bits the plan runs with */
     double max_worker_cost;    /* planner cost of the most loaded worker */
     double mean_worker_cost;   /* total planner cost / n_workers */

@@ -222,8 +222,9 @@ struct BF16 {
 // bits, and only one counts it in the row's sums (row_sum, row_dot; `mask` where a whole pass
 // leaves duplicates out).  Which slot holds them is known when the code is compiled, and the
 // slots past it lie at constant distances, so shifted rows need few registers that aligned ones
-// do not (moving the last slot instead, known only for each row, spilled up to 53 registers;
-// moving only the last vector 124).  Before, shifted rows were read as the aligned vectors around them, with
+// do not (moving the last slot instead, known only for each row, spilled up to 53 registers more;
+// moving only the last vector 124; so the shifted fp32 backward instances of classes 5 and 6 spill
+// 63, 216 bytes per lane, and no other).  Before, shifted rows were read as the aligned vectors around them, with
 // the outside elements masked and the first and last vectors stored element by element (GB/s,
 // 30-400 MB, before -> now): forward bf16 77 2370 -> 3900, 333 3490 -> 4140, 4105 5170 -> 5210, 8193
 // 2730 -> 4870; fp32 77 2380 -> 2750, 333 4470 -> 5440, 1001 5440 -> 5730, 4097 3820 -> 4940;
@@ -543,14 +544,14 @@ __device__ __forceinline__ uint32_t run_item(const typename E::T* in, typename E
 }
 
 // ------------------------------------------------------------------------ workgroup rows
-// Aligned rows beyond the register tile, one row at a time per workgroup: all of its
+// Rows beyond the register tile, one row (or two) at a time per workgroup: all of its
 // nt = 64 * nwaves lanes share the row, lane t holding vectors t, t + nt, ..., t + (L-1) nt (so
 // each load instruction of a wave covers 1 KiB of consecutive bytes).  The row is read once
 // into registers; max and sum are the in-lane tree, the wave's butterfly, then the waves'
 // values combined in wave order through LDS (two barriers per row), so every lane of the
 // workgroup ends with the same bits and a row's result depends on its values, its length and
 // the workgroup size only.  Rows beyond L vectors per lane take two passes over HBM with a
-// per-lane running max and rescaled sum (as in long_row), combined the same way.
+// per-lane running max and rescaled sum, combined the same way.
 constexpr int kTeamMaxRows = 2;  // rows a workgroup keeps in flight
 __shared__ float team_slots[2][kTeamMaxRows][16];  // [max, sum][row][wave]: lane 0 of each wave
 
@@ -852,8 +853,8 @@ __device__ __forceinline__ uint32_t dispatch_item(const typename E::T* in, typen
 // forward output and dy the gradient with respect to y, dx = y * (dy - d), d = sum_j dy_j y_j.
 // Same register tiles as the forward pass: d is an in-lane pairwise tree of the products, then
 // the group's fixed butterfly, so the bits depend on the row's values and length only.  Two
-// input streams: half as many rows per group in flight, and tiles up to 4 vectors per lane
-// (longer rows take the long-row path).
+// input streams: half as many rows per group in flight, and tiles up to 8 vectors per lane
+// (longer rows are held by a workgroup).
 
 template <class E, int G, int V, int U, bool VEC, bool SHIFT = false>
 __device__ __forceinline__ void rows_u_bwd(const typename E::T* y, const typename E::T* dy,
@@ -1198,7 +1199,7 @@ __device__ __forceinline__ uint32_t dispatch_item_bwd(const typename E::T* y,
                                                       int lane64, bool team) {
     const int nvec = span_vecs<E>(cols);
     if constexpr (VEC && KCLASS >= 4) {
-        // rows beyond the forward register tile: the workgroup's waves share each row
+        // rows beyond the register tile: the workgroup's waves share each row
         if (team && nvec > 512)
             return team_item_bwd<E, KCLASS, SHIFT>(y, dy, dx, base, cols, nrows, reps, stride,
                                                    wave, nwaves, lane64);

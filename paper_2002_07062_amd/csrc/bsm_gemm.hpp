@@ -371,9 +371,9 @@ __device__ __forceinline__ void store_block_bf16(uint16_t* c, const Shape& s, in
 // A workgroup's round: output rows [i0, i0 + rows) of batch bidx for this wave (rows <= 32;
 // 0 for a wave past the round's end, which still loads its quarter of B and meets every
 // barrier), as a sequence of steps (column block, reduction slice) that all four waves take
-// together; step t + kDepth's loads are issued before step t's arithmetic.  AREG (the whole
-// reduction in one step, k <= 64): A's operands are read from LDS once and kept in registers
-// for every column block, so later steps move only B.
+// together; step t + kDepth's loads are issued before step t's arithmetic.  AREG (kFormA1 and
+// kFormA2: the whole reduction, k <= 64 or 128, in one step): A's operands are read from LDS once
+// and kept in registers for every column block, so later steps move only B.
 // Wave priority 0..3 (s_setprio takes an immediate).  The three workgroups on a CU get the
 // same rows, but the SQ favours older waves, so without this the first one dispatched finishes
 // far ahead of the last (31 vs 47 us on the context product) and the CU ends on one
@@ -1005,8 +1005,8 @@ enum { kModeNt = 0, kModeNn = 1, kModeNtSoftmax = 2, kModeNtSoftmax1 = 3 };
 constexpr int kWavesPerSimd = 3;
 
 // Worker loop: workgroup w runs its items; an item's rows are taken up to 128 at a time (cut
-// where a batch ends), 32 per wave (single-pass softmax: 64 at a time, 32 per wave pair).  Every bound of these loops is the same for the four
-// waves, so they meet the same barriers.
+// where a batch ends), 32 per wave (single-pass softmax: 64 at a time, 32 per wave pair).  Every
+// bound of these loops is the same for the four waves, so they meet the same barriers.
 template <int MODE, bool BF16OUT, int OPS, bool TEMPORAL, int FORM>
 __device__ __forceinline__ void gemm_worker(const uint16_t* a, const uint16_t* b, void* c,
                                             const Shape& s, const int32_t* __restrict__ worker_ptr,

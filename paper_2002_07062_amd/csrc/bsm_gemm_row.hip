@@ -82,7 +82,7 @@ int gemm_row_softmax_waves(int64_t batch, int m, int n, int k) {
     const int64_t tiles = batch * ((m + kTileM - 1) / kTileM);  // of 32 rows
     const int blocks = (n + kBlockN - 1) / kBlockN;             // of 64 columns
     // Past 512 columns, and where k is no whole number of 16-byte pieces, the other form takes two
-    // passes (384 x 512 x 512 (k = 100) 303 -> 94, 9469 x 33 x 128 (k = 100) 269 -> 204).
+    // passes (384 x 512 x 512 (k = 100) 303 -> 114, 9469 x 33 x 128 (k = 100) 269 -> 203).
     if (n > kBlockN && (k % 8 != 0 || !single_pass_shape(n, k))) return n <= row_max_cols(4) ? 4 : 8;
     // One column block (the other form: two passes of 128-row rounds; here one wave of four
     // works): where the chip is not full of rounds, or they are mostly empty.  1000 x 30 x 60
@@ -92,15 +92,20 @@ int gemm_row_softmax_waves(int64_t batch, int m, int n, int k) {
     // Up to 512 columns the other form is one pass of 64-row rounds by wave pairs, which splits
     // the columns over two waves.  Four must not leave more of them idle (1000 x 33 x 300
     // 22.4 -> 27.5, 2000 x 128 x 128 34 -> 43), and win where the rounds do not fill the chip a few times
-    // (16 x 512 x 512 13.4 -> 8.7, 96 x 512 x 512 20.6 -> 17.1; 192 x 512 x 512 (k = 128) 40 -> 45, 384 x 512 x 512
-    // 65 -> 71; with two slices of k once, 488 x 64 x 512 (k = 128) 21.2 -> 27.1) or where rows are
-    // not whole 128-byte lines, whose halves the waves then store at about the same time, and the
-    // rounds are mostly full (1000 x 128 x 500 77 -> 61, 1000 x 64 x 200 19.0 -> 17.4; 969 x 33 x 500
-    // 28.6 -> 31.0, 2424 x 33 x 500 (k = 128) 104 -> 120).
+    // (16 x 512 x 512 13.4 -> 8.7, 96 x 512 x 512 20.6 -> 17.1, 300 x 90 x 448 (k = 128) 29.9 -> 22.2; 192 x 512 x 512
+    // (k = 128) 40 -> 45, 384 x 512 x 512 65 -> 71) or where rows are not whole 128-byte lines, whose
+    // halves the waves then store at about the same time, and the rounds are mostly full
+    // (1000 x 128 x 500 77 -> 61, 1000 x 64 x 200 19.0 -> 17.4; 969 x 33 x 500 28.6 -> 31.0).  With two
+    // slices of k, and as many column blocks to a wave, few rows do not make up for B read once
+    // per 32 of them (488 x 64 x 512 (k = 128) 21.2 -> 27.1, 200 x 100 x 440 (k = 96) 20.4 -> 23.1).
     const int64_t rounds = batch * ((m + kS1Rows - 1) / kS1Rows);
-    if (tiles * ((blocks + 3) / 4) > rounds * ((blocks + 1) / 2)) return 0;
-    if (rounds <= (k > kChunkK ? 440 : 800) || m <= kTileM) return 4;
-    return n % kBlockN != 0 && 5 * batch * m > 4 * rounds * kS1Rows ? 4 : 0;
+    const int64_t work = tiles * ((blocks + 3) / 4), other = rounds * ((blocks + 1) / 2);
+    if (work > other) return 0;
+    if (m <= kTileM) return 4;
+    const bool full = 5 * batch * m > 4 * rounds * kS1Rows, lines = n % kBlockN == 0;
+    if (rounds > 800) return !lines && full ? 4 : 0;
+    const bool b_twice = k > kChunkK && n > 4 * kBlockN && rounds > 256 && 10 * work > 9 * other;
+    return b_twice && (lines ? m <= 2 * kS1Rows : !full) ? 0 : 4;
 }
 
 // Lines that decide the last bits of a result (row tiles or not, for NN and the score softmax) are

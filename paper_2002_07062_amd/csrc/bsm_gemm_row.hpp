@@ -8,10 +8,10 @@
 //   NN: the waves split the reduction instead and add their sums at the end.
 //   NT + softmax: the products of a row stay in registers until it is done, for n <= 256 Q.
 //   The two-pass form forms every product and every exponential twice, with a barrier at every
-//   64 columns.  us, two passes -> this: 237 x (241 x 64)(64 x 920) bf16 99 -> 56, 64 x (1000 x 64)
-//   (64 x 777) 103 -> 52, 32 x (1024 x 128)(128 x 2048) fp32 125 -> 74, 32 x (2048 x 128)(128 x 2048)
-//   bf16 132 -> 113; 16 x (24 x 96)(96 x 560), where 128-row rounds leave most of the chip idle,
-//   23.8 -> 8.7.  At Q = 8 the round's 28k clocks go to the waves' LDS traffic and exponentials
+//   64 columns.  us, two passes -> this, calls back to back: 237 x (241 x 64)(64 x 920) bf16 100 ->
+//   57, 64 x (1000 x 64)(64 x 777) 103 -> 53, 32 x (1024 x 128)(128 x 2048) fp32 126 -> 74, 32 x
+//   (2048 x 128)(128 x 2048) bf16 127 -> 105 (the profiler's kernel times are 119 to 152 there);
+//   16 x (24 x 96)(96 x 560), where 128-row rounds leave most of the chip idle, 24.3 -> 9.4.  At Q = 8 the round's 28k clocks go to the waves' LDS traffic and exponentials
 //   (15k) and to the output's staging and stores (8k); skipping the stores changes nothing.
 #pragma once
 
@@ -57,12 +57,6 @@ struct Rounds {
     }
 };
 
-// A 64 x 64 chunk of B: rows [j0, j0 + 64) of a batch index, reduction [k0, k0 + 64), into
-// registers and from there to the wave's LDS.  All offsets are 32-bit and relative to `base`,
-// element (j0, 0) of the batch index (the same for the wave): eight 64-bit addresses per lane
-// and their clamps, kept over the rounds, spilled.  Rows past n are row n - 1 again: they give
-// columns that nobody takes.  Columns past k are zeroed.  kVec and kAny as in load8 and keep8;
-// `end` is the offset of the last whole piece of the operand.
 // The lane index as a value the compiler knows nothing about: what is computed from it stays
 // where it is used.  Offsets and masks of every block and slice, kept over a worker's rounds as
 // invariants, spilled up to 186 registers.
@@ -71,6 +65,12 @@ __device__ __forceinline__ int here(int lane) {
     return lane;
 }
 
+// A 64 x 64 chunk of B: rows [j0, j0 + 64) of a batch index, reduction [k0, k0 + 64), into
+// registers and from there to the wave's LDS.  All offsets are 32-bit and relative to `base`,
+// element (j0, 0) of the batch index (the same for the wave): eight 64-bit addresses per lane
+// and their clamps, kept over the rounds, spilled.  Rows past n are row n - 1 again: they give
+// columns that nobody takes.  Columns past k are zeroed.  kVec and kAny as in load8 and keep8;
+// `end` is the offset of the last whole piece of the operand.
 template <int OPS>
 __device__ __forceinline__ void row_load(const uint16_t* base, const Shape& s, int j0, int k0, int end, int lane,
                                          u16x8 (&p)[kRowPieces]) {

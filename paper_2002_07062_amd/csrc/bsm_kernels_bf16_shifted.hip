@@ -1,5 +1,5 @@
 // Softmax kernel instances, bf16, for plans with rows that do not start or end on 16-byte
-// vectors (read as shifted vectors).
+// vectors (shifted rows), and for any plan on buffers that are not 16-byte aligned.
 #include <hip/hip_runtime.h>
 
 #include "bsm_kernel_set.hpp"

@@ -1,5 +1,5 @@
-// Softmax kernel instances, fp32, for plans whose rows all start and end on 16-byte vectors
-// (and for any plan on buffers that are not 16-byte aligned).
+// Softmax kernel instances, fp32, for plans whose rows all start and end on 16-byte vectors, on
+// 16-byte aligned buffers.
 #include <hip/hip_runtime.h>
 
 #include "bsm_kernel_set.hpp"

@@ -542,11 +542,13 @@ def test_plain_scores_take_the_faster_form(dtype, batch, m, n, k, row_tiles):
 
 @pytest.mark.parametrize("batch,m,n,k,wg_threads,wg_per_cu", [
     (384, 512, 512, 100, 256, 2), (384, 512, 512, 104, 256, 2), (40, 64, 1100, 100, 512, 1),
-    (488, 64, 512, 128, 256, 2), (96, 512, 512, 64, 256, 2), (969, 33, 500, 64, 256, 2), (1000, 128, 500, 64, 256, 2)])
+    (488, 64, 512, 128, 256, 2), (96, 512, 512, 64, 256, 2), (969, 33, 500, 64, 256, 2), (1000, 128, 500, 64, 256, 2),
+    (250, 144, 440, 128, 256, 2), (300, 90, 448, 128, 256, 2), (200, 100, 440, 96, 256, 2)])
 def test_score_softmax_takes_the_faster_form(batch, m, n, k, wg_threads, wg_per_cu):
     """Row tiles (rounds of 32 rows) where the other form would take two passes (k % 8 != 0
     among them) or leave the chip idle; else one pass of 64-row rounds."""
-    row_tiles = (batch, m, n, k) in [(384, 512, 512, 100), (40, 64, 1100, 100), (96, 512, 512, 64), (1000, 128, 500, 64)]
+    row_tiles = (batch, m, n, k) in [(384, 512, 512, 100), (40, 64, 1100, 100), (96, 512, 512, 64), (1000, 128, 500, 64),
+                                       (250, 144, 440, 128), (300, 90, 448, 128)]
     p = bsm.bsm_gemm_plan_create(batch, m, n, k, "nt_softmax", "bf16", "balanced", topology=dict(n_cu=256, n_xcd=8), device=-1)
     st = bsm.bsm_plan_describe(p)
     _, items, _, _ = bsm.bsm_plan_export(p)
