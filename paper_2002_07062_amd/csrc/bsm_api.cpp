@@ -500,10 +500,18 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     // A round that runs on into the next batch index takes two: its operands start over there.
     // NN and the score softmax, which read all of B in every round, therefore cut whole batch
     // indices (192 x (333 x 333)(333 x 64): 36.6 -> 32.6 us); the plain scores' rounds are
-    // short and keep the row stream's blocks.
-    const int64_t slice_elems = layout == BSM_GEMM_NT && parts == 0 ? 0 : static_cast<int64_t>(m) * n;
+    // short and keep the row stream's blocks, and so do the others where the stream's blocks
+    // number no more than the workgroups but the rounds of whole batch indices do, and few of
+    // them run on (NN 214 x (448 x 512)(512 x 64) 37.3 -> 30.6, 140 x (430 x 512)(512 x 128) 35.0 -> 30.2,
+    // score softmax 214 x 448 x 600 (k = 256) 329 -> 241; NN 400 x (200 x 333)(333 x 64) 29.8 -> 31.1).
+    const int unit = row > 0 || parts > 0 ? 32 : bsm::gemm_rows_per_wg(single);
+    const int64_t workgroups = static_cast<int64_t>(n_cu) * t.wg_per_cu;
+    const bool evenly = m > 2 * unit && (batch * m + unit - 1) / unit <= workgroups &&
+                        batch * ((m + unit - 1) / unit) > workgroups;
+    const bool stream = row == 0 && parts == 0 && (layout == BSM_GEMM_NT || evenly);
+    const int64_t slice_elems = stream ? 0 : static_cast<int64_t>(m) * n;
     bsm_status st = create_plan(&p, nullptr, rows, cols, m == 0 || n == 0 ? 0 : batch, out_dtype,
-                                schedule, home_xcd, nullptr, &t, device, row > 0 || parts > 0 ? 32 : bsm::gemm_rows_per_wg(single), true,
+                                schedule, home_xcd, nullptr, &t, device, unit, true,
                                 upload, slice_elems);
     if (st != BSM_OK) return st;
     p->topo.wg_threads = wg_threads;

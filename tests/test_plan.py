@@ -669,3 +669,21 @@ def test_balanced_products_follow_the_rule(shape, n_cu, n_xcd):
         assert got == want[w], (w, got[:3], want[w][:3])
     assert np.array_equal(items["slice"], items["elem_offset"] // (m * n))
     assert np.array_equal(items["row_begin"], items["elem_offset"] // n % m)
+
+
+@pytest.mark.parametrize("layout,shape,unit,stream", [
+    ("nn", (214, 448, 64, 512), 128, True), ("nn", (192, 333, 64, 333), 128, False), ("nn", (400, 200, 64, 333), 128, False),
+    ("nn", (384, 512, 64, 512), 128, False), ("nn", (140, 430, 128, 512), 128, True), ("nt_softmax", (214, 448, 600, 256), 128, True),
+    ("nt_softmax", (300, 300, 60, 128), 128, True), ("nt_softmax", (400, 448, 600, 256), 128, False)])
+def test_products_keep_the_row_stream_where_it_is_one_round_per_workgroup(layout, shape, unit, stream):
+    """Rounds of NN and the score softmax start over in every batch index, unless they then
+    outnumber the workgroups and blocks of the row stream do not."""
+    batch, m, n, k = shape
+    p = bsm.bsm_gemm_plan_create(*shape, layout, "bf16", "balanced", topology=dict(n_cu=256, n_xcd=8), device=-1)
+    d = bsm.bsm_plan_describe(p)
+    ptr, items, _, _ = bsm.bsm_plan_export(p)
+    p.destroy()
+    starts = np.concatenate([it["elem_offset"] // n + np.arange(it["reps"]) * it["rep_stride"] for it in items])
+    assert np.all((starts if stream else starts % m) % unit == 0)
+    if stream:
+        assert -(-batch * m // unit) - d["n_items"] in (0, 1) and np.max(np.diff(ptr)) == 1  # the last, partial block may join another
