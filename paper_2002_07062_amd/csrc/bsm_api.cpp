@@ -41,6 +41,7 @@ struct bsm_plan_s {
     bool gemm_single = false;  // layout 2 in one pass (products held in registers)
     int gemm_row = 0;          // layout 2 by row-tile workgroups of this many waves
     int gemm_parts = 0;        // layouts 0 and 1 by row-tile workgroups, so many to a worker's rows
+    int gemm_few_lds = 0;      // bytes of LDS that each of these asks for
     bool gemm_wide = false;    // the forms with a 128-wide B block pay, and the CU's LDS holds them
     int64_t gemm_batch = 0;
     int32_t flags = 0;            // BSM_FLAG_* bits
@@ -529,6 +530,20 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
     p->gemm_single = single;
     p->gemm_row = row;
     p->gemm_parts = parts;
+    if (parts > 0) {
+        // NN's column parts, two workgroups per CU: a third, where LDS lets it in, is given to the
+        // first CUs of an XCD while others have one, unless the busiest XCD has more than three
+        // for each (workgroups without items leave at once).  us, three -> two: XCD order 18 x
+        // (128 x 1024)(1024 x 256) 13.6 -> 11.3, 2 x (512 x 2048)(2048 x 512) 23.7 -> 19.3; balanced 1 x
+        // (256 x 512)(512 x 2048) 26.2 -> 23.5, but 2 x (512 x 2048)(2048 x 512) 55 -> 62: 256 on one XCD.
+        const int n_xcd = p->topo.n_xcd;
+        std::vector<int64_t> busy(n_xcd, 0);
+        for (int w = 0; w < p->topo.n_wg(); ++w)
+            busy[w % n_xcd] += p->table.worker_ptr[w + 1] > p->table.worker_ptr[w];
+        const int64_t most = *std::max_element(busy.begin(), busy.end()) * parts;
+        const bool two = layout == BSM_GEMM_NN && parts > 1 && most * n_xcd <= 3 * static_cast<int64_t>(p->topo.n_cu);
+        p->gemm_few_lds = two ? bsm::gemm_few_rows_lds_bytes_two_per_cu(layout) : bsm::gemm_few_rows_lds_bytes_per_wg(layout);
+    }
     p->gemm_wide = wide;
     p->gemm_batch = batch;
     p->table.stats.algorithmic_bytes =
@@ -569,8 +584,8 @@ bsm_status execute_gemm(bsm_plan p, const void* a, const void* b, void* c, float
         e = bsm::launch_gemm_row(p->gemm_row, bf16_out, temporal, a, b, c, p->gemm_batch, p->gemm_m, p->gemm_n, p->gemm_k,
                                  alpha, p->d_worker_ptr, p->d_items, p->topo.n_wg(), trace, s);
     else if (p->gemm_parts > 0)
-        e = bsm::launch_gemm_few_rows(p->gemm_layout, p->gemm_parts, bf16_out, temporal, a, b, c, p->gemm_batch, p->gemm_m,
-                                      p->gemm_n, p->gemm_k, alpha, p->d_worker_ptr, p->d_items, p->topo.n_wg(), trace, s);
+        e = bsm::launch_gemm_few_rows(p->gemm_layout, p->gemm_parts, p->gemm_few_lds, bf16_out, temporal, a, b, c, p->gemm_batch,
+                                      p->gemm_m, p->gemm_n, p->gemm_k, alpha, p->d_worker_ptr, p->d_items, p->topo.n_wg(), trace, s);
     else
         e = bsm::launch_gemm(p->gemm_layout, p->dtype == BSM_BF16, (p->flags & BSM_FLAG_TEMPORAL) != 0,
                          p->gemm_single, p->gemm_wide, a, b, c, p->gemm_batch, p->gemm_m, p->gemm_n,

@@ -49,22 +49,22 @@ hipError_t pick_ops(Launch& l, int q, bool temporal, bool vec) {
 }
 
 template <int LAYOUT, bool BF16OUT, int OPS, bool TEMPORAL, int NK>
-hipError_t launch_few(Launch& l, int parts) {
+hipError_t launch_few(Launch& l, int parts, int lds_bytes) {
     void* args[] = {&l.a, &l.b, &l.c, &l.s, &l.worker_ptr, &l.items, &l.trace};
     return hipLaunchKernel(reinterpret_cast<const void*>(&bsm_gemm_few_rows_kernel<LAYOUT, BF16OUT, OPS, TEMPORAL, NK>),
-                           dim3(l.n_wg, parts), dim3(64 * kRowWaves), args, few_rows_lds_bytes(LAYOUT), l.stream);
+                           dim3(l.n_wg, parts), dim3(64 * kRowWaves), args, lds_bytes, l.stream);
 }
 template <bool BF16OUT, int OPS, bool TEMPORAL>
-hipError_t pick_layout(Launch& l, int parts, int layout) {
-    if (layout == kNN) return launch_few<kNN, BF16OUT, OPS, TEMPORAL, 1>(l, parts);
-    return l.s.k <= kChunkK ? launch_few<kNT, BF16OUT, OPS, TEMPORAL, 1>(l, parts)
-                            : launch_few<kNT, BF16OUT, OPS, TEMPORAL, 2>(l, parts);
+hipError_t pick_layout(Launch& l, int parts, int layout, int lds) {
+    if (layout == kNN) return launch_few<kNN, BF16OUT, OPS, TEMPORAL, 1>(l, parts, lds);
+    return l.s.k <= kChunkK ? launch_few<kNT, BF16OUT, OPS, TEMPORAL, 1>(l, parts, lds)
+                            : launch_few<kNT, BF16OUT, OPS, TEMPORAL, 2>(l, parts, lds);
 }
 template <bool BF16OUT>
-hipError_t pick_few(Launch& l, int parts, int layout, bool temporal, bool vec) {
+hipError_t pick_few(Launch& l, int parts, int layout, int lds, bool temporal, bool vec) {
     if (vec)
-        return temporal ? pick_layout<BF16OUT, kVec, true>(l, parts, layout) : pick_layout<BF16OUT, kVec, false>(l, parts, layout);
-    return temporal ? pick_layout<BF16OUT, kAny, true>(l, parts, layout) : pick_layout<BF16OUT, kAny, false>(l, parts, layout);
+        return temporal ? pick_layout<BF16OUT, kVec, true>(l, parts, layout, lds) : pick_layout<BF16OUT, kVec, false>(l, parts, layout, lds);
+    return temporal ? pick_layout<BF16OUT, kAny, true>(l, parts, layout, lds) : pick_layout<BF16OUT, kAny, false>(l, parts, layout, lds);
 }
 
 }  // namespace
@@ -73,6 +73,7 @@ namespace bsm {
 
 int gemm_row_lds_bytes_per_wg(int q) { return row_lds_bytes(q); }
 int gemm_few_rows_lds_bytes_per_wg(int layout) { return few_rows_lds_bytes(layout); }
+int gemm_few_rows_lds_bytes_two_per_cu(int layout) { return std::max(few_rows_lds_bytes(layout), kTwoPerCuBytes); }
 int gemm_few_rows_wgs_per_cu(int layout) { return few_rows_wgs_per_cu(layout); }
 
 // us below: the other form -> row tiles.
@@ -157,14 +158,14 @@ hipError_t launch_gemm_row(int q, bool bf16_out, bool temporal, const void* a, c
     return bf16_out ? pick_ops<true>(l, q, temporal, vec) : pick_ops<false>(l, q, temporal, vec);
 }
 
-hipError_t launch_gemm_few_rows(int layout, int parts, bool bf16_out, bool temporal, const void* a, const void* b, void* c,
-                                int64_t batch, int m, int n, int k, float alpha, const int32_t* d_worker_ptr,
+hipError_t launch_gemm_few_rows(int layout, int parts, int lds_bytes, bool bf16_out, bool temporal, const void* a,
+                                const void* b, void* c, int64_t batch, int m, int n, int k, float alpha, const int32_t* d_worker_ptr,
                                 const bsm_item* d_items, int n_wg, void* trace, hipStream_t stream) {
     Launch l{static_cast<const uint16_t*>(a), static_cast<const uint16_t*>(b), c,
              product_shape(batch, m, n, k, alpha), d_worker_ptr, d_items,
              static_cast<bsm_trace_rec*>(trace), n_wg, stream};
     const bool vec = aligned_pieces(a, b, k) && (layout != kNN || n % 8 == 0);
-    return bf16_out ? pick_few<true>(l, parts, layout, temporal, vec) : pick_few<false>(l, parts, layout, temporal, vec);
+    return bf16_out ? pick_few<true>(l, parts, layout, lds_bytes, temporal, vec) : pick_few<false>(l, parts, layout, lds_bytes, temporal, vec);
 }
 
 }  // namespace bsm

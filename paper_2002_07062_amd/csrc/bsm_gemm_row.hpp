@@ -395,6 +395,8 @@ constexpr int few_rows_wgs_per_cu(int layout) {
     const int by_lds = 160 * 1024 / ((few_rows_lds_bytes(layout) + 1279) / 1280 * 1280);
     return by_lds < kWavesPerSimd ? by_lds : kWavesPerSimd;
 }
+constexpr int kTwoPerCuBytes = 43 * 1280;  // of which a CU gives out two
+static_assert(3 * kTwoPerCuBytes > 160 * 1024);
 static_assert(few_rows_wgs_per_cu(kNT) == 3 && few_rows_wgs_per_cu(kNN) == 3, "the column parts count on three");
 
 template <bool BF16OUT, int OPS, bool TEMPORAL, int Q>

@@ -76,10 +76,11 @@ hipError_t launch_gemm_row(int q, bool bf16_out, bool temporal, const void* a, c
 // workgroups that share a worker's rows, each with its own columns; gemm_row_parts says how many
 // a shape takes, 0 for the general form.
 int gemm_few_rows_lds_bytes_per_wg(int layout);
+int gemm_few_rows_lds_bytes_two_per_cu(int layout);  // so many that a CU holds two
 int gemm_few_rows_wgs_per_cu(int layout);  // that a CU holds at once
 int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k, int n_cu);
-hipError_t launch_gemm_few_rows(int layout, int parts, bool bf16_out, bool temporal, const void* a, const void* b, void* c,
-                                int64_t batch, int m, int n, int k, float alpha, const int32_t* d_worker_ptr,
+hipError_t launch_gemm_few_rows(int layout, int parts, int lds_bytes, bool bf16_out, bool temporal, const void* a,
+                                const void* b, void* c, int64_t batch, int m, int n, int k, float alpha, const int32_t* d_worker_ptr,
                                 const bsm_item* d_items, int n_wg, void* trace, hipStream_t stream);
 
 // Workgroups of the plan's forward instance that fit on one CU at once (registers and LDS).

@@ -102,6 +102,23 @@ def test_plain_row_tiles_against_the_oracle(layout, shape, out):
 
 
 @pytest.mark.parametrize("out", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [(2, 512, 512, 200), (1, 256, 400, 72), (8, 500, 256, 133)], ids=lambda s: "x".join(map(str, s)))
+def test_context_column_parts_under_every_schedule(shape, out):
+    """Two or three workgroups to a CU, by how many the busiest XCD has (the balanced order deals few
+    row tiles to one XCD, the XCD order to all): the same bits."""
+    batch, m, n, k = shape
+    print(f"[context parts {shape} {out}]", flush=True)
+    a, b = _operands(batch, m, n, k, seed=800 + n)
+    a_d, b_d = _dev_bf16(a), _dev_bf16(b)
+    want = _product(shape, "nn", out, a_d, b_d, 0.5)
+    check_product(want, a, b, batch, m, n, k, "nn", out, 0.5)
+    for schedule in ("rr", "xcd"):
+        assert np.array_equal(_product(shape, "nn", out, a_d, b_d, 0.5, schedule=schedule), want)
+    assert np.array_equal(_product(shape, "nn", out, a_d, b_d, 0.5, topology={"wg_per_cu": 3}), want)
+    assert np.array_equal(_product(shape, "nn", out, a_d, b_d, 0.5, topology={"n_cu": 5, "n_xcd": 4}), want)
+
+
+@pytest.mark.parametrize("out", ["f32", "bf16"])
 @pytest.mark.parametrize("layout", ["nt", "nn", "nt_softmax"])
 @pytest.mark.parametrize("shape", FORM_SHAPES + [(2, 70, 520, 128), (2, 70, 700, 72)], ids=lambda s: "x".join(map(str, s)))
 def test_general_forms_on_small_shapes(shape, layout, out):
