@@ -534,8 +534,8 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
         // NN's column parts, two workgroups per CU: a third, where LDS lets it in, is given to the
         // first CUs of an XCD while others have one, unless the busiest XCD has more than three
         // for each (workgroups without items leave at once).  us, three -> two: XCD order 18 x
-        // (128 x 1024)(1024 x 256) 13.6 -> 11.3, 2 x (512 x 2048)(2048 x 512) 23.7 -> 19.3; balanced 1 x
-        // (256 x 512)(512 x 2048) 26.2 -> 23.5, but 2 x (512 x 2048)(2048 x 512) 55 -> 62: 256 on one XCD.
+        // (128 x 1024)(1024 x 256) 13.6 -> 11.7, 2 x (512 x 2048)(2048 x 512) 23.7 -> 19.8; balanced 1 x
+        // (256 x 512)(512 x 2048) 26.2 -> 22.9, but 2 x (512 x 2048)(2048 x 512) 55 -> 62: 256 on one XCD.
         const int n_xcd = p->topo.n_xcd;
         std::vector<int64_t> busy(n_xcd, 0);
         for (int w = 0; w < p->topo.n_wg(); ++w)
