@@ -489,7 +489,7 @@ bsm_status create_gemm_plan(bsm_plan* out_plan, int64_t batch, int32_t m, int32_
             per_wg * t.wg_per_cu > static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor))
             return fail(BSM_ERR_INVALID_ARG, "wg_per_cu %d: %lld bytes of LDS per workgroup do not fit",
                         t.wg_per_cu, static_cast<long long>(per_wg));
-        wide = bsm::gemm_wide_pays(layout, batch, m, n, k, n_cu, t.wg_per_cu) &&
+        wide = bsm::gemm_wide_pays(layout, bf16_out, batch, m, n, k, n_cu, t.wg_per_cu) &&
                static_cast<int64_t>(bsm::gemm_wide_lds_bytes_per_wg(bf16_out)) * t.wg_per_cu <=
                    static_cast<int64_t>(prop.maxSharedMemoryPerMultiProcessor);
     }

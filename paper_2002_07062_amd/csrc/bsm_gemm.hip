@@ -58,8 +58,21 @@ static bool nn_three_per_cu(int64_t batch, int m, int n, int k, int n_cu) {
 // several reduction steps (32 x (2048 x 2048)(2048 x 128) 105 us against kFormStep's 113), but not
 // over one (384 x (512 x 64)(64 x 100) 27.8 against 25.2; two per CU 23.9), nor where three is the
 // better number.
-bool gemm_wide_pays(int layout, int64_t batch, int m, int n, int k, int n_cu, int wgs_per_cu) {
+//
+// fp32 plain scores of whole rounds, 64 < k <= 128: kFormA2 stores the same bits, later (its step is
+// the whole reduction, of which k <= 96 leaves a quarter or more empty).  It loses where a workgroup
+// takes its only round, and after that where two of few columns, a short reduction and long slices
+// meet; more columns read A more often, and each new batch index starts over at every step.  us,
+// kFormA2 -> kFormStep: 92 x 1024 x 128 (k = 128) 16.8 -> 14.5, 175 x 512 x 128 (k = 96) 15.3 -> 13.4, 92 x
+// 1024 x 256 (k = 80) 25.1 -> 21.3, 190 x 1024 x 512 (k = 80) 88.5 -> 80.5, 1100 x 128 x 128 (k = 72) 24.0 ->
+// 23.3; past the lines 175 x 512 x 512 (k = 128) 42.6 -> 44.6, 700 x 128 x 160 (k = 128) 20.9 -> 23.3, 575 x
+// 512 x 256 (k = 128) 76 -> 87.
+bool gemm_wide_pays(int layout, bool bf16_out, int64_t batch, int m, int n, int k, int n_cu, int wgs_per_cu) {
     if (wgs_per_cu <= bsm_mm::kS1WavesPerSimd) return true;
+    if (layout == bsm_mm::kNT && !bf16_out && m % 128 == 0 && n <= (k <= 96 ? 512 : 256)) {
+        const bool one_round = batch * m <= 128 * static_cast<int64_t>(bsm_mm::kWavesPerSimd) * n_cu;
+        if (one_round ? m >= 512 || n <= 128 : (m >= 1024) + (k <= 96) + (n <= 128) >= 2) return false;
+    }
     return k > bsm_mm::kChunkK && !(layout == bsm_mm::kNN && nn_three_per_cu(batch, m, n, k, n_cu));
 }
 int gemm_waves_per_simd(bool single_pass) {

@@ -47,7 +47,7 @@ int gemm_wg_threads();
 bool gemm_single_pass_shape(int n, int k);
 int gemm_lds_bytes_per_wg(bool bf16_out, bool single_pass);
 int gemm_wide_lds_bytes_per_wg(bool bf16_out);  // of the forms with a 128-wide B block
-bool gemm_wide_pays(int layout, int64_t batch, int m, int n, int k, int n_cu, int wgs_per_cu);
+bool gemm_wide_pays(int layout, bool bf16_out, int64_t batch, int m, int n, int k, int n_cu, int wgs_per_cu);
 int gemm_waves_per_simd(bool single_pass);
 // Workgroups per CU when the topology does not say: as many as the form the shape takes is
 // compiled for.

@@ -72,3 +72,17 @@ def test_two_pass_softmax_forms(n, k):
             for topology in ({"wg_threads": 256, "flags": bsm.BSM_FLAG_TEMPORAL}, {"wg_threads": 256, "n_cu": 3}):
                 assert np.array_equal(_product((batch, m, n, k), "nt_softmax", out, a_d, b_d, alpha, topology=topology,
                                                schedule="xcd"), got)
+
+
+@pytest.mark.parametrize("shape", [(2, 128, 65, 72), (3, 512, 256, 128), (1, 512, 260, 96), (1, 512, 260, 104)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_both_forms_of_the_plain_scores(shape):
+    """fp32 scores of whole rounds, 64 < k <= 128: with A staged at every step, where that is faster, and
+    (two workgroups per CU) with A in registers the same sums in the same order."""
+    batch, m, n, k = shape
+    print(f"[plain scores, both forms {shape}]", flush=True)
+    a, b = _operands(batch, m, n, k, seed=900 + n)
+    a_d, b_d = _dev_bf16(a), _dev_bf16(b)
+    got = _product(shape, "nt", "f32", a_d, b_d, 0.25, topology={"wg_threads": 256})
+    check_product(got, a, b, batch, m, n, k, "nt", "f32", 0.25)
+    assert np.array_equal(_product(shape, "nt", "f32", a_d, b_d, 0.25, topology={"wg_threads": 256, "wg_per_cu": 2}), got)
