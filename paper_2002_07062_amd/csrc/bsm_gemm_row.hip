@@ -122,9 +122,11 @@ int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k
         // Both forms' time by what their workgroups do, three to a CU, in steps of one 64-column
         // block.  The general form's units are 128 rows of the row stream, dealt whole; a unit
         // starts over in every batch index that it meets.  Its steps take longer in fp32, and
-        // where two blocks share 128-byte lines (which row tiles store at about the same time).
+        // where two blocks share 64 bytes of a line (which row tiles store at about the same time;
+        // halves of a line cost nothing: bf16 846 x 640 x 160 (k = 72) 66 -> 82, 253 x 1024 x 96 (k = 96)
+        // 26 -> 36).
         // A row tile takes 0.9 steps and 0.75 for every four blocks, a quarter more with two
-        // slices of k.  Fitted to 4140 shapes (n 16 .. 2048, m 8 .. 2048, 1 to 60 million outputs,
+        // slices of k.  Fitted to 4840 shapes (n 16 .. 2048, m 8 .. 2048, 1 to 60 million outputs,
         // both types): 95% get the faster form, or one within 5% of it, the worst one of 1.43
         // times its time.  us, general -> row tiles: 384 x 512 x 512 44 -> 54 (fp32 78.7 -> 72.8), 190 x
         // 512 x 512 (k = 128) 27.5 -> 36.6, 7324 x 512 x 16 120 -> 299, fp32 384 x 512 x 64 13.7 -> 19.1;
@@ -133,8 +135,8 @@ int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k
         const double resident = 3.0 * n_cu;  // either form: the same bits
         const int64_t units = (batch * m + 127) / 128;
         const double per_unit = m % 128 == 0 ? 1.0 : 128 % m == 0 ? 128.0 / m : 1.0 + 128.0 / m;
-        const bool shared_lines = blocks > 1 && n % (bf16_out ? 64 : 32) != 0;
-        const double general = std::ceil(units / resident) * per_unit * (0.6 + (bf16_out ? 1.0 : 1.6) * blocks) *
+        const bool shared_lines = blocks > 1 && n % (bf16_out ? 32 : 16) != 0;
+        const double general = std::ceil(units / resident) * per_unit * (0.6 + (bf16_out ? 1.0 : 1.5) * blocks) *
                                (shared_lines ? 3.0 : 1.0);
         const double row = std::max(1.0, tiles * parts / resident) * (k > kChunkK ? 1.25 : 1.0) *
                            (0.9 + 0.75 * static_cast<double>((blocks + 4 * parts - 1) / (4 * parts)));

@@ -526,6 +526,7 @@ def test_context_products_default_to_the_workgroups_their_form_is_compiled_for(b
 @pytest.mark.parametrize("dtype,batch,m,n,k,row_tiles", [
     ("f32", 384, 512, 64, 64, False), ("bf16", 1831, 2048, 16, 40, False), ("bf16", 190, 512, 512, 128, False),
     ("bf16", 384, 512, 512, 64, False), ("f32", 384, 512, 512, 64, True), ("bf16", 473, 33, 64, 64, True),
+    ("bf16", 253, 1024, 96, 96, False), ("bf16", 846, 640, 160, 72, False), ("f32", 672, 1536, 112, 72, False),
     ("bf16", 1000, 128, 300, 64, True), ("bf16", 4, 2048, 2048, 128, True), ("bf16", 512, 16, 936, 128, True)])
 def test_plain_scores_take_the_faster_form(dtype, batch, m, n, k, row_tiles):
     """NT keeps 128-row units of the row stream where row tiles (rounds of 32 rows of a batch
