@@ -123,8 +123,8 @@ int gemm_row_parts(int layout, bool bf16_out, int64_t batch, int m, int n, int k
         // block.  The general form's units are 128 rows of the row stream, dealt whole; a unit
         // starts over in every batch index that it meets.  Its steps take longer in fp32, and
         // where two blocks share 64 bytes of a line (which row tiles store at about the same time;
-        // halves of a line cost nothing: bf16 846 x 640 x 160 (k = 72) 66 -> 82, 253 x 1024 x 96 (k = 96)
-        // 26 -> 36).
+        // halves of a line cost nothing: bf16 846 x 640 x 160 (k = 72) 53 -> 82, 253 x 1024 x 96 (k = 96)
+        // 25 -> 36).
         // A row tile takes 0.9 steps and 0.75 for every four blocks, a quarter more with two
         // slices of k.  Fitted to 4840 shapes (n 16 .. 2048, m 8 .. 2048, 1 to 60 million outputs,
         // both types): 95% get the faster form, or one within 5% of it, the worst one of 1.43
